@@ -224,6 +224,25 @@ struct Dia {
     double stored_bytes() const { return (double)ndiag * (b3 ? 9.0 : 1.0) * (double)stride * val_bytes; }
 };
 
+// Rows of the matrix in another order (level by level, or color by color)
+// for the exact and multicolor Gauss-Seidel sweeps: 64 positions per chunk
+// (one wavefront), entry t of a chunk's positions side by side at
+// ptr[chunk] + 64 t, so a wavefront's loads are contiguous whatever the order
+// (the rows of a level or color lie far apart in the natural-order triangles:
+// every 8-byte value then costs a cache line).  A position's entries run over
+// the row's main triangle, then over the other one, each in column order;
+// col >= 0 marks a main entry, ~col another one, PERM_PAD the end.  In the
+// orders by level a main entry's col is the position of its row in the same
+// order: neighbours in a level tend to need neighbours in the one before it.
+constexpr int32_t PERM_PAD = INT32_MIN;
+struct Perm {
+    int64_t nchunks = 0;
+    int32_t *rows = nullptr; // 64 nchunks row indices, -1 for none
+    int64_t *ptr = nullptr;  // nchunks + 1
+    int32_t *col = nullptr;
+    void *val = nullptr;
+};
+
 // The schedule the setup picked for the sweep kernels.
 enum : int { FMT_SELL = 0, FMT_DIA = 1 };
 
@@ -261,14 +280,13 @@ struct Handle {
     // S_l v rounded to the working precision, formed once per apply by the
     // 32- and 16-bit forms on the diagonal layout (null in float64)
     void *sv = nullptr;
-    // level sets (optional)
-    int nlev_l = 0, nlev_u = 0;
-    int32_t *lev_rows_l = nullptr, *lev_rows_u = nullptr; // rows grouped by level
-    std::vector<int64_t> lev_ptr_l, lev_ptr_u;            // host offsets
-    // multicolor ordering (optional)
-    int ncolors = 0;
-    int32_t *color_rows = nullptr; // rows grouped by color
+    // exact and multicolor Gauss-Seidel (optional): rows by level of the lower
+    // triangle (L the main one), by level of the upper (U the main one), and
+    // by color (color q's rows in chunks color_ptr[q] .. color_ptr[q + 1))
+    int nlev_l = 0, nlev_u = 0, ncolors = 0;
+    Perm PL, PU, PC;
     std::vector<int64_t> color_ptr;
+    unsigned *tri_next = nullptr; // next chunk of the half sweeps in turn (3 counters)
     GmresWork *gw = nullptr;
     CgWork *cw = nullptr;
     const int *stop = nullptr; // device flag: kernels return at once when set (GMRES)
@@ -286,6 +304,7 @@ struct Handle {
 int setup_handle(Handle &h, const gs2_csr &A, const gs2_options &o, hipStream_t s, bool alloc_vecs);
 void free_sell(Sell &S);
 void free_dia(Dia &D);
+void free_perm(Perm &P);
 int choose_lanes(double avg_len, int max_len);
 // out[i] = in[0] + ... + in[i-1] for i < m (device arrays; synchronises s)
 int exclusive_scan_i64(const int64_t *in, int64_t *out, int64_t m, hipStream_t s);

@@ -821,14 +821,121 @@ static int read_err(int *err, hipStream_t s)
     return flags_to_status(f);
 }
 
-// Level sets of the DAGs of L (ascending) and U (descending), computed on the
-// host from a copy of the pattern: level_i = 1 + max level over the
-// triangle's entries of row i.  Rows are then grouped level by level.
+void free_perm(Perm &P)
+{
+    for (void *p : {(void *)P.rows, (void *)P.ptr, (void *)P.col, P.val})
+        if (p) (void)hipFree(p);
+    P = Perm{};
+}
+
+// Stored entries of each chunk: 64 times the longest of its rows (off-diagonal
+// entries); zero at index nchunks, so that an exclusive scan yields the end.
+__global__ __launch_bounds__(256) void k_perm_len(int64_t nchunks, const int32_t *__restrict__ rows,
+                                                  const int32_t *__restrict__ rp, int64_t *__restrict__ len)
+{
+    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t c = g / WAVE;
+    if (c > nchunks) return;
+    const int i = c < nchunks ? rows[g] : -1;
+    int m = i < 0 ? 0 : rp[i + 1] - rp[i] - 1;
+    for (int o = 1; o < WAVE; o <<= 1) m = max(m, __shfl_xor(m, o));
+    if (g % WAVE == 0) len[c] = (int64_t)WAVE * m;
+}
+
+// One thread per position: the row's entries, the main triangle's first
+// (lower = 1: the lower triangle is the main one), scaled and rounded as in
+// k_fill.  A main entry's column goes through `place` when it is given.
+template <typename VT>
+__global__ __launch_bounds__(256) void k_perm_fill(int64_t nchunks, const int32_t *__restrict__ rows,
+                                                   const int64_t *__restrict__ ptr, const int32_t *__restrict__ rp,
+                                                   const int32_t *__restrict__ ci, const double *__restrict__ va,
+                                                   const int32_t *__restrict__ lcnt, int lower,
+                                                   const int32_t *__restrict__ place,
+                                                   const double *__restrict__ sl, const double *__restrict__ sr,
+                                                   int32_t *__restrict__ col, VT *__restrict__ val)
+{
+    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t c = g / WAVE;
+    if (c >= nchunks) return;
+    const int i = rows[g];
+    const int64_t beg = ptr[c];
+    const int steps = (int)((ptr[c + 1] - beg) / WAVE);
+    const int b = i < 0 ? 0 : rp[i], lc = i < 0 ? 0 : lcnt[i], tot = i < 0 ? 0 : rp[i + 1] - b - 1, uc = tot - lc;
+    const int mc = lower ? lc : uc;
+    const double srow = i < 0 ? 0.0 : sl[i];
+    int ovf = 0; // the natural-order triangles report it
+    for (int t = 0; t < steps; ++t) {
+        const int64_t pos = beg + (int64_t)t * WAVE + g % WAVE;
+        if (t >= tot) {
+            col[pos] = PERM_PAD;
+            val[pos] = VT(0);
+            continue;
+        }
+        const bool low = lower ? t < mc : t >= mc;
+        const int k = b + (low ? (lower ? t : t - mc) : lc + 1 + (lower ? t - mc : t));
+        const int j = ci[k];
+        col[pos] = t >= mc ? ~j : place ? place[j] : j;
+        val[pos] = convert_scaled<VT>((srow * va[k]) * sr[j], &ovf);
+    }
+}
+
+// The rows in the given order (-1: no row), 64 per chunk, with their entries;
+// by_place: the main entries name positions of this order instead of rows.
+static int build_perm(Handle &h, Perm &P, std::vector<int32_t> &order, int lower, bool by_place, const gs2_csr &A,
+                      const int32_t *lcnt, hipStream_t s)
+{
+    struct Tmp {
+        int32_t *place = nullptr;
+        ~Tmp()
+        {
+            if (place) (void)hipFree(place);
+        }
+    } tmp;
+    if (by_place) {
+        std::vector<int32_t> place(h.n);
+        for (size_t q = 0; q < order.size(); ++q)
+            if (order[q] >= 0) place[order[q]] = (int32_t)q;
+        GS2_TRY_HIP(hipMalloc(&tmp.place, sizeof(int32_t) * place.size()));
+        GS2_TRY_HIP(hipMemcpyAsync(tmp.place, place.data(), sizeof(int32_t) * place.size(), hipMemcpyHostToDevice, s));
+        GS2_TRY_HIP(hipStreamSynchronize(s));
+    }
+    order.resize((order.size() + WAVE - 1) / WAVE * WAVE, -1);
+    P.nchunks = (int64_t)order.size() / WAVE;
+    int64_t *len = nullptr, total = 0;
+    GS2_TRY_HIP(hipMalloc(&P.rows, sizeof(int32_t) * order.size()));
+    GS2_TRY_HIP(hipMalloc(&P.ptr, sizeof(int64_t) * (P.nchunks + 1)));
+    GS2_TRY_HIP(hipMemcpyAsync(P.rows, order.data(), sizeof(int32_t) * order.size(), hipMemcpyHostToDevice, s));
+    GS2_TRY_HIP(hipMalloc(&len, sizeof(int64_t) * (P.nchunks + 1)));
+    k_perm_len<<<(unsigned)(((P.nchunks + 1) * WAVE + 255) / 256), 256, 0, s>>>(P.nchunks, P.rows, A.rowptr, len);
+    const int st = exclusive_scan_i64(len, P.ptr, P.nchunks + 1, s); // synchronises: `order` may go
+    (void)hipFree(len);
+    GS2_TRY(st);
+    GS2_TRY_HIP(hipMemcpy(&total, P.ptr + P.nchunks, sizeof(int64_t), hipMemcpyDeviceToHost));
+    const size_t vb = h.precision == GS2_FP64 ? 8 : h.precision == GS2_FP32 ? 4 : 2;
+    GS2_TRY_HIP(hipMalloc(&P.col, sizeof(int32_t) * std::max<int64_t>(total, WAVE)));
+    GS2_TRY_HIP(hipMalloc(&P.val, vb * std::max<int64_t>(total, WAVE)));
+    const unsigned g = (unsigned)((P.nchunks * WAVE + 255) / 256);
+    if (h.precision == GS2_FP64)
+        k_perm_fill<double><<<g, 256, 0, s>>>(P.nchunks, P.rows, P.ptr, A.rowptr, A.colind, A.val, lcnt, lower,
+                                              tmp.place, h.sl, h.sr, P.col, (double *)P.val);
+    else if (h.precision == GS2_FP32)
+        k_perm_fill<float><<<g, 256, 0, s>>>(P.nchunks, P.rows, P.ptr, A.rowptr, A.colind, A.val, lcnt, lower,
+                                             tmp.place, h.sl, h.sr, P.col, (float *)P.val);
+    else
+        k_perm_fill<_Float16><<<g, 256, 0, s>>>(P.nchunks, P.rows, P.ptr, A.rowptr, A.colind, A.val, lcnt, lower,
+                                                tmp.place, h.sl, h.sr, P.col, (_Float16 *)P.val);
+    GS2_TRY_HIP(hipGetLastError());
+    if (tmp.place) GS2_TRY_HIP(hipStreamSynchronize(s)); // it goes with this scope
+    return GS2_OK;
+}
+
 // Multicolor ordering (Section 6, multi-threaded Gauss-Seidel): greedy first
 // fit in natural row order on the symmetrised pattern; a row takes the
 // smallest color not held by an earlier row it is coupled to (a_ij or a_ji
-// nonzero).  Rows are then grouped color by color.
-static int build_colors(Handle &h, const std::vector<int32_t> &rp, const std::vector<int32_t> &ci, hipStream_t s)
+// nonzero).  Rows are then grouped color by color, each color from a chunk
+// of its own.
+static int build_colors(Handle &h, const gs2_csr &A, const int32_t *lcnt, const std::vector<int32_t> &rp,
+                        const std::vector<int32_t> &ci, hipStream_t s)
 {
     const int64_t n = h.n;
     // transpose pattern (column -> rows), to see couplings a_ji from earlier rows j
@@ -851,27 +958,31 @@ static int build_colors(Handle &h, const std::vector<int32_t> &rp, const std::ve
         color[i] = c;
         ncol = std::max(ncol, c + 1);
     }
-    std::vector<int64_t> ptr(ncol + 1, 0);
-    for (int64_t i = 0; i < n; ++i) ptr[color[i] + 1]++;
-    for (int c = 0; c < ncol; ++c) ptr[c + 1] += ptr[c];
-    std::vector<int32_t> rows(std::max<int64_t>(n, 1));
-    std::vector<int64_t> pos(ptr.begin(), ptr.end() - 1);
+    std::vector<int64_t> cnt(ncol, 0), ptr(ncol + 1, 0), pos(ncol);
+    for (int64_t i = 0; i < n; ++i) cnt[color[i]]++;
+    for (int c = 0; c < ncol; ++c) {
+        pos[c] = ptr[c] * WAVE;
+        ptr[c + 1] = ptr[c] + (cnt[c] + WAVE - 1) / WAVE;
+    }
+    std::vector<int32_t> rows(ptr[ncol] * WAVE, -1);
     for (int64_t i = 0; i < n; ++i) rows[pos[color[i]]++] = (int32_t)i;
-    GS2_TRY_HIP(hipMalloc(&h.color_rows, sizeof(int32_t) * rows.size()));
-    GS2_TRY_HIP(hipMemcpyAsync(h.color_rows, rows.data(), sizeof(int32_t) * rows.size(), hipMemcpyHostToDevice, s));
-    GS2_TRY_HIP(hipStreamSynchronize(s));
+    GS2_TRY(build_perm(h, h.PC, rows, 1, false, A, lcnt, s));
     h.ncolors = ncol;
     h.color_ptr = std::move(ptr);
     return GS2_OK;
 }
 
-static int build_levels(Handle &h, const gs2_csr &A, hipStream_t s)
+// Level sets of the DAGs of L (ascending) and U (descending), computed on the
+// host from a copy of the pattern: level_i = 1 + max level over the
+// triangle's entries of row i.  Rows are then grouped level by level.
+static int build_levels(Handle &h, const gs2_csr &A, const int32_t *lcnt, hipStream_t s)
 {
     const int64_t n = A.n;
     std::vector<int32_t> rp(n + 1), ci(A.nnz);
     GS2_TRY_HIP(hipMemcpyAsync(rp.data(), A.rowptr, sizeof(int32_t) * (n + 1), hipMemcpyDeviceToHost, s));
     if (A.nnz) GS2_TRY_HIP(hipMemcpyAsync(ci.data(), A.colind, sizeof(int32_t) * A.nnz, hipMemcpyDeviceToHost, s));
     GS2_TRY_HIP(hipStreamSynchronize(s));
+    GS2_TRY_HIP(hipMalloc(&h.tri_next, 3 * sizeof(unsigned)));
     std::vector<int32_t> lev(n);
     for (int lower = 1; lower >= 0; --lower) {
         int nlev = 0;
@@ -885,25 +996,15 @@ static int build_levels(Handle &h, const gs2_csr &A, hipStream_t s)
             lev[i] = lv;
             nlev = std::max(nlev, lv + 1);
         }
-        std::vector<int64_t> ptr(nlev + 1, 0);
-        for (int64_t i = 0; i < n; ++i) ptr[lev[i] + 1]++;
-        for (int l = 0; l < nlev; ++l) ptr[l + 1] += ptr[l];
-        std::vector<int32_t> rows(std::max<int64_t>(n, 1));
-        std::vector<int64_t> pos(ptr.begin(), ptr.end() - 1);
+        std::vector<int64_t> pos(nlev + 1, 0);
+        for (int64_t i = 0; i < n; ++i) pos[lev[i] + 1]++;
+        for (int l = 0; l < nlev; ++l) pos[l + 1] += pos[l];
+        std::vector<int32_t> rows(n);
         for (int64_t i = 0; i < n; ++i) rows[pos[lev[i]]++] = (int32_t)i;
-        int32_t *&d_rows = lower ? h.lev_rows_l : h.lev_rows_u; // owned by the handle from here on
-        GS2_TRY_HIP(hipMalloc(&d_rows, sizeof(int32_t) * rows.size()));
-        GS2_TRY_HIP(hipMemcpyAsync(d_rows, rows.data(), sizeof(int32_t) * rows.size(), hipMemcpyHostToDevice, s));
-        GS2_TRY_HIP(hipStreamSynchronize(s));
-        if (lower) {
-            h.nlev_l = nlev;
-            h.lev_ptr_l = std::move(ptr);
-        } else {
-            h.nlev_u = nlev;
-            h.lev_ptr_u = std::move(ptr);
-        }
+        GS2_TRY(build_perm(h, lower ? h.PL : h.PU, rows, lower, true, A, lcnt, s));
+        (lower ? h.nlev_l : h.nlev_u) = nlev;
     }
-    return build_colors(h, rp, ci, s);
+    return build_colors(h, A, lcnt, rp, ci, s);
 }
 
 static int alloc_vectors(Handle &h)
@@ -1005,7 +1106,7 @@ int setup_handle(Handle &h, const gs2_csr &A, const gs2_options &o, hipStream_t 
         if (alloc_vecs) GS2_TRY_HIP(hipMalloc(&h.yh, prec_bytes(h.precision) * nb));
     }
     GS2_TRY(read_err(sc.err, s));
-    if (o.build_levels) GS2_TRY(build_levels(h, A, s));
+    if (o.build_levels) GS2_TRY(build_levels(h, A, sc.lcnt, s));
     GS2_TRY_HIP(hipStreamSynchronize(s));
     return GS2_OK;
 }
@@ -1021,8 +1122,10 @@ Handle::~Handle()
     free_sell(E);
     free_dia(DL);
     free_dia(DU);
-    for (void *p : {(void *)sl, (void *)sr, xh, xh2, rh, ga, gb, sv, yh, (void *)lev_rows_l, (void *)lev_rows_u,
-                    (void *)color_rows})
+    free_perm(PL);
+    free_perm(PU);
+    free_perm(PC);
+    for (void *p : {(void *)sl, (void *)sr, xh, xh2, rh, ga, gb, sv, yh, (void *)tri_next})
         if (p) (void)hipFree(p);
     if (gw) free_gmres_work(gw);
     if (cw) free_cg_work(cw);

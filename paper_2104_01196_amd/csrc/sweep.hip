@@ -254,80 +254,196 @@ __global__ void k_fill_zero(const int *__restrict__ stop, int64_t n, AT *__restr
     if (i < n) x[i] = AT(0);
 }
 
+// Exact Gauss-Seidel / SOR (compact row update of the sequential loop of
+// Section 6), a whole half sweep in one launch:
+//   x_i = (1 - w) xold_i + w (S_l v_i - sum_main ah_ij xnew_j - sum_other ah_ij xold_j)
+// main = the triangle solved in this sweep, other = the opposite triangle
+// (previous iterate; xold == NULL means 0).
+//
+// The rows come level by level, 64 per chunk (Perm), and the wavefronts take
+// the chunks in that order from a counter.  An unknown is its own flag: xpos
+// (the new iterate by position) starts out holding a NaN pattern that no
+// result keeps (not_ready), a result is stored and read at agent scope (past
+// the caches that other XCDs do not share), and a row waits until the entries
+// it needs are there.  Kept by position, the entries a wavefront polls lie
+// side by side; by row, every lane polled a cache line of its own and the
+// polls of the waiting wavefronts held the chain up (2.64 ms per symmetric
+// sweep of the 96^3 Laplacian).  xnew is the iterate by row for the next half
+// sweep.  A row only waits on chunks handed out before its own, so a wavefront that waits always
+// waits on running ones, however few are resident; rows of one wavefront may
+// depend on each other, so the store sits inside the polling loop, which all
+// lanes leave together.  The wait is bounded all the same (TRI_WAIT_TICKS of
+// the wall clock; the pattern then passes on as NaN).
+//
+// What bounds it is the chain of levels: 1.4 us each (store, load that sees
+// it, row update) against 8 us for a launch per level.  96^3 Laplacian, 286
+// levels per half sweep, symmetric sweep: 4.57 ms with a launch per level,
+// 0.82 ms here.
 template <typename AT>
-__global__ void k_unscale(const int *__restrict__ stop, int64_t n, const AT *__restrict__ xh, const double *__restrict__ sr,
-                          double *__restrict__ z)
+struct Bits;
+template <>
+struct Bits<double> {
+    typedef unsigned long long T;
+    static constexpr T not_ready = 0xfff8a5a5c3c30f0full;
+};
+template <>
+struct Bits<float> {
+    typedef unsigned int T;
+    static constexpr T not_ready = 0xffc5a5c3u;
+};
+
+constexpr int TRI_TB = 256;
+constexpr long long TRI_WAIT_TICKS = 200000000ll; // 2 s at 100 MHz
+
+template <typename VT, typename AT>
+__global__ __launch_bounds__(TRI_TB) void k_tri_sweep(const int *__restrict__ stop, int64_t n, Perm P,
+                                                      const AT *__restrict__ xold, AT *__restrict__ xnew, AT *xpos,
+                                                      AT *__restrict__ xfill,
+                                                      const double *__restrict__ v, const double *__restrict__ sl,
+                                                      const double *__restrict__ sr, AT w, double *__restrict__ z,
+                                                      unsigned *next, unsigned *next_after)
+{
+    using BT = typename Bits<AT>::T;
+    constexpr BT NR = Bits<AT>::not_ready;
+    constexpr int U = 8; // entries per block: a 7-point row in one
+    if (stop && *stop) return;
+    const int lane = threadIdx.x & (WAVE - 1);
+    BT *xb = reinterpret_cast<BT *>(xpos);
+    const VT *__restrict__ val = (const VT *)P.val;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *next_after = 0u;
+    auto take = [&]() -> int64_t {
+        unsigned c = 0;
+        if (lane == 0) c = __hip_atomic_fetch_add(next, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return (int64_t)__builtin_amdgcn_readfirstlane((int)c);
+    };
+    bool late = false; // once a wait has run out, the wavefront waits no more
+    for (int64_t ch = take(); ch < P.nchunks; ch = take()) {
+        const int pos = (int)(ch * WAVE) + lane;
+        const int i = P.rows[pos];
+        const int64_t beg = P.ptr[ch];
+        const int steps = (int)((P.ptr[ch + 1] - beg) / WAVE);
+        if (xfill && pos < n) reinterpret_cast<BT *>(xfill)[pos] = NR;
+        const AT r = i < 0 ? AT(0) : (AT)(v[i] * sl[i]), xo = (xold && i >= 0) ? xold[i] : AT(0);
+        const double s_out = (z && i >= 0) ? sr[i] : 0.0;
+        // a block of the row's entries; those of the other triangle wait for
+        // nothing and are gathered at once
+        struct Block {
+            int cc[U];
+            AT a[U], x[U];
+        };
+        auto load = [&](Block &k, int t) {
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const bool in = t + q < steps;
+                const int64_t p = beg + (int64_t)(in ? t + q : 0) * WAVE + lane;
+                k.cc[q] = in ? P.col[p] : PERM_PAD;
+                k.a[q] = in ? (AT)val[p] : AT(0);
+            }
+#pragma unroll
+            for (int q = 0; q < U; ++q) k.x[q] = (k.cc[q] < 0 && k.cc[q] != PERM_PAD && xold) ? xold[~k.cc[q]] : AT(0);
+        };
+        Block cur, nxt;
+        AT acc = AT(0);
+        int t = 0;
+        load(cur, 0);
+        load(nxt, U);
+        bool open = i >= 0;
+        const long long t0 = wall_clock64();
+        while (__any(open)) {
+            bool ready = open;
+            if (open) {
+                BT b[U]; // all loads issued before the first test
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    b[q] = 0;
+                    if (cur.cc[q] >= 0)
+                        b[q] = __hip_atomic_load(xb + cur.cc[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+#pragma unroll
+                for (int q = 0; q < U; ++q)
+                    if (cur.cc[q] >= 0) {
+                        ready = ready && (b[q] != NR || late);
+                        cur.x[q] = __builtin_bit_cast(AT, b[q]);
+                    }
+            }
+            if (ready) {
+#pragma unroll
+                for (int q = 0; q < U; ++q)
+                    if (cur.cc[q] >= 0 || (cur.cc[q] != PERM_PAD && xold)) acc += cur.a[q] * cur.x[q];
+                t += U;
+                if (t >= steps) {
+                    const AT x = (AT(1) - w) * xo + w * (r - acc);
+                    BT b = __builtin_bit_cast(BT, x);
+                    if (b == NR) b ^= BT(1);
+                    __hip_atomic_store(xb + pos, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (xnew) xnew[i] = x;
+                    if (z) z[i] = s_out * (double)x;
+                    open = false;
+                } else {
+                    cur = nxt;
+                    load(nxt, t + U);
+                }
+            }
+            if (!__any(ready)) {
+                __builtin_amdgcn_s_sleep(1);
+                late = late || wall_clock64() - t0 > TRI_WAIT_TICKS;
+            }
+        }
+    }
+}
+
+// every unknown of the first half sweep not ready, its chunk counter at zero
+template <typename AT>
+__global__ void k_tri_begin(const int *__restrict__ stop, int64_t n, AT *__restrict__ x, unsigned *next)
 {
     if (stop && *stop) return;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) z[i] = sr[i] * (double)xh[i];
+    if (i == 0) *next = 0u;
+    if (i < n) reinterpret_cast<typename Bits<AT>::T *>(x)[i] = Bits<AT>::not_ready;
 }
 
-// One level of a level-scheduled Gauss-Seidel / SOR sweep (compact row
-// update of the sequential loop of Section 6):
-//   x_i = (1 - w) xold_i + w (S_l v_i - sum_main ah_ij xnew_j - sum_other ah_ij xold_j)
-// main = the triangle solved in this sweep (entries already updated),
-// other = the opposite triangle (previous iterate; xold == NULL means 0).
-template <typename VT, typename AT>
-__global__ void k_tri_level(const int *__restrict__ stop, const int32_t *__restrict__ rows, int64_t cnt, int K, SellView M, SellView O,
-                            const AT *__restrict__ xold, AT *__restrict__ xnew, const double *__restrict__ v,
-                            const double *__restrict__ sl, AT w)
-{
-    if (stop && *stop) return;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= cnt) return;
-    const int i = rows[t];
-    const int C = WAVE / K;
-    const int64_t s = i / C;
-    const int lb = (i % C) * K;
-    AT acc = AT(0);
-    {
-        const int64_t beg = M.sp[s], steps = (M.sp[s + 1] - beg) / WAVE;
-        for (int64_t st = 0; st < steps; ++st)
-            for (int q = 0; q < K; ++q) {
-                const int64_t p = beg + st * WAVE + lb + q;
-                acc += (AT)((const VT *)M.val)[p] * xnew[M.col[p]];
-            }
-    }
-    AT xo = AT(0);
-    if (xold) {
-        const int64_t beg = O.sp[s], steps = (O.sp[s + 1] - beg) / WAVE;
-        for (int64_t st = 0; st < steps; ++st)
-            for (int q = 0; q < K; ++q) {
-                const int64_t p = beg + st * WAVE + lb + q;
-                acc += (AT)((const VT *)O.val)[p] * xold[O.col[p]];
-            }
-        xo = xold[i];
-    }
-    xnew[i] = (AT(1) - w) * xo + w * ((AT)(v[i] * sl[i]) - acc);
-}
-
-// One color of a multicolor Gauss-Seidel / SOR sweep: rows of one color are
-// never coupled, so they update in place from the current iterate,
+// One color of a multicolor Gauss-Seidel / SOR sweep (chunks [c0, c1) of the
+// rows by color, a wavefront per chunk): rows of one color are never coupled,
+// so they update in place from the current iterate,
 //   x_i = (1 - w) x_i + w (S_l v_i - sum_{j != i} ah_ij x_j)   (scaled space).
+// xzero: the whole iterate is still zero and is not gathered; z: the row's
+// last update, written out as S_r x as well.  Bandwidth-bound; with the rows
+// picked out of the natural-order triangles each pass moved the lines of
+// every color (151 x 140 x 133, float32, two sweeps of two colors: 171 us,
+// 122 us by color).
 template <typename VT, typename AT>
-__global__ void k_color(const int *__restrict__ stop, const int32_t *__restrict__ rows, int64_t cnt, int K,
-                        SellView L, SellView U, AT *x, const double *__restrict__ v, const double *__restrict__ sl,
-                        AT w)
+__global__ __launch_bounds__(256) void k_color(const int *__restrict__ stop, int64_t c0, int64_t c1, Perm P, int xzero,
+                                               AT *x, const double *__restrict__ v, const double *__restrict__ sl,
+                                               AT w, double *__restrict__ z, const double *__restrict__ sr)
 {
     if (stop && *stop) return;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= cnt) return;
-    const int i = rows[t];
-    const int C = WAVE / K;
-    const int64_t s = i / C;
-    const int lb = (i % C) * K;
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int64_t ch = c0 + (int64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
+    if (ch >= c1) return;
+    const int i = P.rows[ch * WAVE + lane];
+    const int64_t beg = P.ptr[ch];
+    const int steps = xzero ? 0 : (int)((P.ptr[ch + 1] - beg) / WAVE);
+    const VT *__restrict__ val = (const VT *)P.val;
     AT acc = AT(0);
-    for (int part = 0; part < 2; ++part) {
-        const SellView &M = part ? U : L;
-        const int64_t beg = M.sp[s], steps = (M.sp[s + 1] - beg) / WAVE;
-        for (int64_t st = 0; st < steps; ++st)
-            for (int q = 0; q < K; ++q) {
-                const int64_t p = beg + st * WAVE + lb + q;
-                acc += (AT)((const VT *)M.val)[p] * x[M.col[p]];
-            }
+    constexpr int U = 6;
+    for (int t = 0; t < steps; t += U) {
+        int cc[U];
+        AT a[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const bool in = t + q < steps;
+            const int64_t p = beg + (int64_t)(in ? t + q : 0) * WAVE + lane;
+            cc[q] = in ? P.col[p] : PERM_PAD;
+            a[q] = in ? (AT)val[p] : AT(0);
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+            if (cc[q] != PERM_PAD) acc += a[q] * x[cc[q] < 0 ? ~cc[q] : cc[q]];
     }
-    x[i] = (AT(1) - w) * x[i] + w * ((AT)(v[i] * sl[i]) - acc);
+    if (i < 0) return;
+    const AT xn = (AT(1) - w) * x[i] + w * ((AT)(v[i] * sl[i]) - acc);
+    x[i] = xn;
+    if (z) z[i] = sr[i] * (double)xn;
 }
 
 // ------------------------------------------------ diagonal-interleaved passes
@@ -1201,35 +1317,36 @@ struct Launch {
         return GS2_OK;
     }
 
+    // Wavefronts of a half sweep: enough to hold a few levels at once, few
+    // enough that those ahead do not load the memory with polls.  96^3
+    // Laplacian (48 chunks per level), symmetric sweep: 1023 us with 128, 824
+    // with 256 to 1024, 882 with 2048.
+    static unsigned tri_grid(int64_t nchunks, int nlev)
+    {
+        const int64_t per_level = (nchunks + nlev - 1) / std::max(nlev, 1);
+        const int64_t waves = std::min<int64_t>(std::max<int64_t>(8 * per_level, 512), 8192);
+        return (unsigned)std::max<int64_t>(1, (std::min(waves, nchunks) + TRI_TB / WAVE - 1) / (TRI_TB / WAVE));
+    }
+
+    // exact GS/SOR: the half sweeps take turns on two iterates by row (the
+    // previous one and the one being formed) and two by position (the one
+    // being formed and the next one, being marked not ready)
     static int tri(Handle &h, int variant, double omega, const double *v, double *z, hipStream_t s)
     {
-        AT *xa = (AT *)h.xh, *xb = (AT *)h.xh2;
-        const AT w = (AT)omega;
-        const AT *xold = nullptr;
-        AT *xnew = xa;
-        for (int t = 0; t < h.sweeps; ++t) {
-            for (int half = 0; half < 2; ++half) {
-                const bool fwd = half == 0;
-                if (fwd && variant == GS2_BACKWARD) continue;
-                if (!fwd && variant == GS2_FORWARD) continue;
-                k_fill_zero<AT><<<grid_rows(h.n), TB, 0, s>>>(h.stop, h.n, xnew);
-                const Sell &Mt = fwd ? h.L : h.U;
-                const Sell &Ot = fwd ? h.U : h.L;
-                const std::vector<int64_t> &ptr = fwd ? h.lev_ptr_l : h.lev_ptr_u;
-                const int32_t *rows = fwd ? h.lev_rows_l : h.lev_rows_u;
-                const int nlev = fwd ? h.nlev_l : h.nlev_u;
-                for (int l = 0; l < nlev; ++l) {
-                    const int64_t cnt = ptr[l + 1] - ptr[l];
-                    if (cnt <= 0) continue;
-                    Prof pr(s, PK_TRI, (double)cnt * (16.0 + 2 * sizeof(AT)));
-                    k_tri_level<VT, AT><<<(unsigned)((cnt + TB - 1) / TB), TB, 0, s>>>(
-                        h.stop, rows + ptr[l], cnt, Mt.K, view(Mt), view(Ot), xold, xnew, v, h.sl, w);
-                }
-                xold = xnew;
-                xnew = (xnew == xa) ? xb : xa;
-            }
+        AT *byrow[2] = {(AT *)h.xh, (AT *)h.xh2}, *bypos[2] = {(AT *)h.rh, (AT *)h.ga};
+        const int per = variant == GS2_SYMMETRIC ? 2 : 1, H = h.sweeps * per;
+        k_tri_begin<AT><<<grid_rows(h.n), TB, 0, s>>>(h.stop, h.n, bypos[0], h.tri_next);
+        for (int t = 0; t < H; ++t) {
+            const bool fwd = variant == GS2_FORWARD || (variant == GS2_SYMMETRIC && t % 2 == 0);
+            const Perm &P = fwd ? h.PL : h.PU;
+            const bool last = t == H - 1;
+            Prof pr(s, PK_TRI, (double)(h.L.nnz + (t ? h.U.nnz : 0)) * (sizeof(VT) + 4) +
+                                   (double)h.n * (16.0 + 2 * sizeof(AT) + (last ? 16.0 : sizeof(AT))));
+            k_tri_sweep<VT, AT><<<tri_grid(P.nchunks, fwd ? h.nlev_l : h.nlev_u), TRI_TB, 0, s>>>(
+                h.stop, h.n, P, t ? byrow[(t + 1) % 2] : nullptr, last ? nullptr : byrow[t % 2], bypos[t % 2],
+                last ? nullptr : bypos[(t + 1) % 2], v, h.sl, h.sr, (AT)omega, last ? z : nullptr,
+                h.tri_next + t % 3, h.tri_next + (t + 1) % 3);
         }
-        k_unscale<AT><<<grid_rows(h.n), TB, 0, s>>>(h.stop, h.n, xold, h.sr, z);
         return GS2_OK;
     }
 
@@ -1238,23 +1355,19 @@ struct Launch {
     static int mtgs(Handle &h, int variant, double omega, const double *v, double *z, hipStream_t s)
     {
         AT *x = (AT *)h.xh;
-        const AT w = (AT)omega;
+        const int per = variant == GS2_SYMMETRIC ? 2 : 1, H = h.sweeps * per;
         k_fill_zero<AT><<<grid_rows(h.n), TB, 0, s>>>(h.stop, h.n, x);
-        for (int t = 0; t < h.sweeps; ++t)
-            for (int half = 0; half < 2; ++half) {
-                const bool fwd = half == 0;
-                if (fwd && variant == GS2_BACKWARD) continue;
-                if (!fwd && variant == GS2_FORWARD) continue;
-                for (int q = 0; q < h.ncolors; ++q) {
-                    const int c = fwd ? q : h.ncolors - 1 - q;
-                    const int64_t cnt = h.color_ptr[c + 1] - h.color_ptr[c];
-                    if (cnt <= 0) continue;
-                    Prof pr(s, PK_TRI, (double)cnt * (16.0 + 2 * sizeof(AT)));
-                    k_color<VT, AT><<<(unsigned)((cnt + TB - 1) / TB), TB, 0, s>>>(
-                        h.stop, h.color_rows + h.color_ptr[c], cnt, h.L.K, view(h.L), view(h.U), x, v, h.sl, w);
-                }
+        for (int t = 0; t < H; ++t) {
+            const bool fwd = variant == GS2_FORWARD || (variant == GS2_SYMMETRIC && t % 2 == 0);
+            for (int q = 0; q < h.ncolors; ++q) {
+                const int c = fwd ? q : h.ncolors - 1 - q;
+                const int64_t c0 = h.color_ptr[c], c1 = h.color_ptr[c + 1];
+                const int xzero = t == 0 && q == 0;
+                Prof pr(s, PK_TRI, (double)(c1 - c0) * WAVE * (16.0 + 2 * sizeof(AT)));
+                k_color<VT, AT><<<(unsigned)((c1 - c0 + TB / WAVE - 1) / (TB / WAVE)), TB, 0, s>>>(
+                    h.stop, c0, c1, h.PC, xzero, x, v, h.sl, (AT)omega, t == H - 1 ? z : nullptr, h.sr);
             }
-        k_unscale<AT><<<grid_rows(h.n), TB, 0, s>>>(h.stop, h.n, x, h.sr, z);
+        }
         return GS2_OK;
     }
 
