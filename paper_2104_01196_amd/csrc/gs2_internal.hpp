@@ -163,6 +163,9 @@ struct Sell {
     int off_min = 0;
     void *val = nullptr;
     int val_bytes = 8;
+    // the allocations behind the arrays; a triangle built together with
+    // another one may own both of theirs, or none
+    void *mem[2] = {nullptr, nullptr};
     // stream the values and offsets past the caches (set for large triangles)
     int nt = 0;
     int idx_bytes() const { return off ? 2 : 4; }
@@ -188,13 +191,6 @@ constexpr double NT_TRIANGLES_BYTES = 150e6;
 // ran 17 % slower per inner pass (42.0 against 35.8 us).
 constexpr size_t FLUSH_BYTES = size_t(512) << 20;
 
-// Build the 16-bit column offsets of a sliced-ELL array (K lanes per row,
-// slice pointers sp, padded entries, columns col; lane l of slice s holds row
-// s * 64/K + l/K): *off = col - row - *off_min.  *off is left null when the
-// offsets span more than 65535.
-int build_col_offsets(int64_t nslices, int K, const int64_t *sp, const int32_t *col, int64_t padded, uint16_t **off,
-                      int *off_min, hipStream_t s);
-
 // One triangle in the diagonal-interleaved layout (chosen by the setup's
 // timing when the triangle has few distinct offsets col - row, as stencil
 // matrices in their natural ordering do).  Diagonal d holds, for every row
@@ -215,6 +211,7 @@ struct Dia {
     int64_t nnz = 0;    // real entries
     int off[DIA_MAX] = {};
     void *val = nullptr;
+    void *mem = nullptr; // the allocation behind the values of this triangle (and of one built with it)
     int val_bytes = 8;
     int nt = 0; // stream the values with the non-temporal policy
     // 3-row blocks (3 unknowns per node, node-major): off[] holds node
@@ -274,6 +271,7 @@ struct Handle {
     int blocks = 1, local_sweeps = 1;
     Sell E;
     void *yh = nullptr; // frozen copy of the iterate
+    void *vec = nullptr; // one allocation behind the scaling vectors and temporaries
     double *sl = nullptr, *sr = nullptr; // scaling vectors (float64)
     // persistent temporaries (Section 6: allocated once, live with the handle)
     void *xh = nullptr, *xh2 = nullptr, *rh = nullptr, *ga = nullptr, *gb = nullptr;
@@ -306,8 +304,38 @@ void free_sell(Sell &S);
 void free_dia(Dia &D);
 void free_perm(Perm &P);
 int choose_lanes(double avg_len, int max_len);
-// out[i] = in[0] + ... + in[i-1] for i < m (device arrays; synchronises s)
-int exclusive_scan_i64(const int64_t *in, int64_t *out, int64_t m, hipStream_t s);
+// out[i] = in[0] + ... + in[i-1] for i < m (device arrays; tmp: scan_tmp(m)
+// elements)
+int exclusive_scan_i64(const int64_t *in, int64_t *out, int64_t m, int64_t *tmp, hipStream_t s);
+int64_t scan_tmp(int64_t m);
+
+// What one pass over a CSR pattern finds (scan_pattern): error bits, entries
+// of the strict triangles, the longest row without its diagonal, the smallest
+// and largest col - row, the distinct col - row (0 among them if a diagonal
+// entry exists) and, for n a multiple of 3, the distinct node offsets
+// c/3 - r/3 below and above the diagonal; all ascending.  many_d / many_b:
+// more than two triangles of DIA_MAX could hold, lists not complete.
+struct Pattern {
+    int err = 0, maxlen = 0, lo = 0, hi = 0;
+    int64_t nl = 0, nu = 0;
+    bool many_d = false, many_b = false;
+    std::vector<int> d, bl, bu;
+};
+struct PatternDev;
+size_t pattern_dev_bytes();
+// dev: pattern_dev_bytes() of device memory.  With lcnt, the values are
+// checked too and the rows' triangle counts and scalings written.
+// Synchronises s.
+int scan_pattern(const gs2_csr &A, int32_t *lcnt, int32_t *ucnt, double *sl, double *sr, PatternDev *dev, Pattern &out,
+                 hipStream_t s);
+// Bytes rounded up so that what follows in one allocation stays aligned.
+inline size_t aligned(size_t b) { return (b + 255) / 256 * 256; }
+
+// Schedules chosen by timing, process-wide and keyed by the shape of the
+// problem (get: false when there is none yet).
+bool choice_get(const std::string &key, int *choice);
+void choice_put(const std::string &key, int choice);
+std::string shape_key(int64_t n, double avg, int maxlen, int prec);
 
 // sweep.hip
 int apply_gs2(Handle &h, const double *v, double *z, hipStream_t s);

@@ -53,8 +53,10 @@ struct GmresWork {
     int64_t n = 0;
     int m = 0;
     int nb = 0; // workgroups of the vector kernels
+    void *mem = nullptr; // one allocation behind the device arrays
     double *V = nullptr, *Z = nullptr, *w = nullptr, *w2 = nullptr, *part = nullptr;
     GState *st = nullptr;
+    PatternDev *pat = nullptr;
     GHeader *hdr = nullptr; // pinned host copy
     // HIP graph of one restart cycle (captured on its own stream, launched on the caller's)
     hipStream_t cap = nullptr;
@@ -98,8 +100,7 @@ void free_gmres_work(GmresWork *g)
     if (g->graph) (void)hipGraphDestroy(g->graph);
     if (g->cap) (void)hipStreamDestroy(g->cap);
     sella_free(g->A);
-    for (void *p : {(void *)g->V, (void *)g->Z, (void *)g->w, (void *)g->w2, (void *)g->part, (void *)g->st})
-        if (p) (void)hipFree(p);
+    if (g->mem) (void)hipFree(g->mem);
     if (g->hdr) (void)hipHostFree(g->hdr);
     delete g;
 }
@@ -113,15 +114,24 @@ static int alloc_work(GmresWork **out, int64_t n, int m)
     g->nb = (int)std::max<int64_t>(1, (n + RB - 1) / RB);
     const size_t N = (size_t)std::max<int64_t>(n, 1);
     int st = GS2_OK;
-    auto A = [&](void **p, size_t bytes) {
-        if (st == GS2_OK && hipMalloc(p, bytes) != hipSuccess) st = GS2_ERR_NOMEM;
+    size_t total = 0;
+    auto place = [&](void *base) {
+        total = 0;
+        auto at = [&](auto &p, size_t bytes) {
+            if (base) p = (std::decay_t<decltype(p)>)((char *)base + total);
+            total += aligned(bytes);
+        };
+        at(g->V, sizeof(double) * N * (m + 1));
+        at(g->Z, sizeof(double) * N * m);
+        at(g->w, sizeof(double) * N);
+        at(g->w2, sizeof(double) * N);
+        at(g->part, sizeof(double) * (size_t)g->nb * (2 * MAXM + 3)); // delayed CGS2: 2j+3 per block
+        at(g->st, sizeof(GState));
+        at(g->pat, pattern_dev_bytes());
     };
-    A((void **)&g->V, sizeof(double) * N * (m + 1));
-    A((void **)&g->Z, sizeof(double) * N * m);
-    A((void **)&g->w, sizeof(double) * N);
-    A((void **)&g->w2, sizeof(double) * N);
-    A((void **)&g->part, sizeof(double) * (size_t)g->nb * (2 * MAXM + 3)); // delayed CGS2: 2j+3 per block
-    A((void **)&g->st, sizeof(GState));
+    place(nullptr);
+    if (hipMalloc(&g->mem, total) != hipSuccess) st = GS2_ERR_NOMEM;
+    else place(g->mem);
     if (st == GS2_OK && hipHostMalloc((void **)&g->hdr, sizeof(GHeader), hipHostMallocDefault) != hipSuccess)
         st = GS2_ERR_NOMEM;
     if (st != GS2_OK) {
@@ -982,8 +992,8 @@ static int precondition(int kind, gs2_handle *P, const double *v, double *z, int
 constexpr int64_t SPMV_TUNE_MIN_ROWS = 65536;
 
 // Loads in flight of the two delayed basis passes (all groups of one width:
-// block_multidot's and k_dcgs_update_pairs' G), decided once per workspace
-// by timing both widths of each pass at step min(m - 1, 24) on the zeroed
+// block_multidot's and k_dcgs_update_pairs' G), decided once per size bucket
+// and restart in the process by timing both widths of each pass at step min(m - 1, 24) on the zeroed
 // basis (best of three batches of three launches after a warm-up batch; a
 // narrow variant must win by 3 %).  The narrow width then runs from the
 // crossover step.  Small bases (fewer than BASIS_TUNE_MIN_ROWS rows, or a
@@ -1001,6 +1011,14 @@ static int tune_basis(GmresWork *W, int req, hipStream_t s)
     }
     if (req != 0 || n < BASIS_TUNE_MIN_ROWS || W->m < 16 || n % 2) {
         W->basis_tuned = req != 0 ? 2 : 1;
+        return GS2_OK;
+    }
+    const std::string key = "V_" + shape_key(n, W->m, 0, GS2_FP64);
+    int known = 0;
+    if (choice_get(key, &known)) {
+        if (known & 1) W->dot_narrow = DOT_NARROW_FROM;
+        if (known & 2) W->upd_narrow = UPD_NARROW_FROM;
+        W->basis_tuned = 1;
         return GS2_OK;
     }
     const int jt = std::min(W->m - 1, 24), nb = W->nb;
@@ -1038,6 +1056,7 @@ static int tune_basis(GmresWork *W, int req, hipStream_t s)
     GS2_TRY_HIP(hipGetLastError());
     if (dn < 0.97f * dw) W->dot_narrow = DOT_NARROW_FROM;
     if (un < 0.97f * uw) W->upd_narrow = UPD_NARROW_FROM;
+    choice_put(key, (dn < 0.97f * dw ? 1 : 0) | (un < 0.97f * uw ? 2 : 0));
     W->basis_tuned = 1;
     return GS2_OK;
 }
@@ -1097,7 +1116,8 @@ static int build_layout(SellA &S, const gs2_csr &A, int sel, const std::vector<i
 // 16-byte value loads) or, failing that, the 3-row block copy at one and
 // two nodes per lane.  fmt GS2_FORMAT_AUTO times them (one product each;
 // a later candidate must win by 3 %) on matrices of at least
-// SPMV_TUNE_MIN_ROWS rows; GS2_FORMAT_SELL / _DIA / _BLOCK3 force a layout
+// SPMV_TUNE_MIN_ROWS rows, once per shape in the process (as the sweep
+// schedules); GS2_FORMAT_SELL / _DIA / _BLOCK3 force a layout
 // (the diagonal one at two rows per lane, the block one at two nodes per
 // lane, falling back to sliced ELL when A does not qualify).
 static int prepare_matrix(GmresWork *W, const gs2_csr &A, int fmt, hipStream_t s)
@@ -1108,17 +1128,20 @@ static int prepare_matrix(GmresWork *W, const gs2_csr &A, int fmt, hipStream_t s
         return sella_fill_values(S, A, false, s);
     sella_free(S);
     std::vector<int> offs;
-    int hst = GS2_OK;
-    const bool dia_ok = fmt != GS2_FORMAT_SELL && fmt != GS2_FORMAT_BLOCK3 && sella_dia_offsets(A, offs, s, &hst);
-    GS2_TRY(hst);
-    const bool b3_ok = !dia_ok && fmt != GS2_FORMAT_SELL && fmt != GS2_FORMAT_DIA && sella_b3_offsets(A, offs, s, &hst);
-    GS2_TRY(hst);
+    Pattern pat;
+    if (fmt != GS2_FORMAT_SELL) GS2_TRY(scan_pattern(A, nullptr, nullptr, nullptr, nullptr, W->pat, pat, s));
+    const bool dia_ok = fmt != GS2_FORMAT_SELL && fmt != GS2_FORMAT_BLOCK3 && sella_dia_offsets(A, pat, offs);
+    const bool b3_ok = !dia_ok && fmt != GS2_FORMAT_SELL && fmt != GS2_FORMAT_DIA && sella_b3_offsets(A, pat, offs);
     const int K0 = sella_rule_lanes(A);
     int sel = K0, tuned = 0;
+    const std::string key = "A_" + shape_key(A.n, (double)A.nnz / (double)A.n, pat.maxlen, GS2_FP64) + "_d" +
+                            std::to_string(dia_ok || b3_ok ? offs.size() : 0) + (b3_ok ? "b" : "");
     if (fmt == GS2_FORMAT_DIA && dia_ok) {
         sel = -2;
     } else if (fmt == GS2_FORMAT_BLOCK3 && b3_ok) {
         sel = -12;
+    } else if (fmt == GS2_FORMAT_AUTO && A.n >= SPMV_TUNE_MIN_ROWS && choice_get(key, &sel)) {
+        tuned = 1;
     } else if (fmt == GS2_FORMAT_AUTO && A.n >= SPMV_TUNE_MIN_ROWS) {
         std::vector<int> cands{K0};
         if (K0 < WAVE) cands.push_back(2 * K0);
@@ -1145,6 +1168,7 @@ static int prepare_matrix(GmresWork *W, const gs2_csr &A, int fmt, hipStream_t s
             }
         }
         tuned = 1;
+        choice_put(key, sel);
     }
     if (S.sel != sel || !(S.val || S.dval)) GS2_TRY(build_layout(S, A, sel, offs, s));
     S.tuned = tuned;

@@ -54,7 +54,7 @@ __global__ void k_sella_fill(int64_t n, int64_t nslices, int K, const int32_t *_
 
 void sella_free(SellA &S)
 {
-    for (void *p : {(void *)S.sp, (void *)S.col, (void *)S.val, (void *)S.dval})
+    for (void *p : {S.mem[0], S.mem[1]})
         if (p) (void)hipFree(p);
     S = SellA{};
 }
@@ -107,63 +107,6 @@ __global__ __launch_bounds__(256) void k_copy_fill(int64_t n, int R, const int32
     }
 }
 
-// Distinct node offsets c/3 - r/3, ascending (host copy of the pattern);
-// false unless n is a multiple of 3, there are at most DIA_MAX of them and
-// the blocks store at most 1.5x the entries.
-static bool b3A_offsets(const gs2_csr &A, std::vector<int> &offs, hipStream_t s, int *st)
-{
-    *st = GS2_OK;
-    offs.clear();
-    const int64_t n = A.n;
-    if (n % 3 != 0) return false;
-    std::vector<int32_t> rp(n + 1), ci(std::max<int64_t>(A.nnz, 1));
-    if (hipMemcpyAsync(rp.data(), A.rowptr, sizeof(int32_t) * (n + 1), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        (A.nnz && hipMemcpyAsync(ci.data(), A.colind, sizeof(int32_t) * A.nnz, hipMemcpyDeviceToHost, s) !=
-                      hipSuccess) ||
-        hipStreamSynchronize(s) != hipSuccess) {
-        *st = GS2_ERR_HIP;
-        return false;
-    }
-    for (int64_t i = 0; i < n; ++i)
-        for (int32_t k = rp[i]; k < rp[i + 1]; ++k) {
-            const int d = (int)((int64_t)ci[k] / 3 - i / 3);
-            auto it = std::lower_bound(offs.begin(), offs.end(), d);
-            if (it == offs.end() || *it != d) {
-                if ((int)offs.size() == DIA_MAX) return false;
-                offs.insert(it, d);
-            }
-        }
-    return 3.0 * (double)offs.size() * (double)n <= 1.5 * (double)A.nnz + 3.0 * (double)KRB * offs.size();
-}
-
-// Distinct offsets col - row of the whole pattern, ascending (host copy of
-// the pattern); false when there are more than DIA_MAX or the diagonals
-// would store more than 1.5x the entries.
-static bool diaA_offsets(const gs2_csr &A, std::vector<int> &offs, hipStream_t s, int *st)
-{
-    *st = GS2_OK;
-    offs.clear();
-    const int64_t n = A.n;
-    std::vector<int32_t> rp(n + 1), ci(std::max<int64_t>(A.nnz, 1));
-    if (hipMemcpyAsync(rp.data(), A.rowptr, sizeof(int32_t) * (n + 1), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        (A.nnz && hipMemcpyAsync(ci.data(), A.colind, sizeof(int32_t) * A.nnz, hipMemcpyDeviceToHost, s) !=
-                      hipSuccess) ||
-        hipStreamSynchronize(s) != hipSuccess) {
-        *st = GS2_ERR_HIP;
-        return false;
-    }
-    for (int64_t i = 0; i < n; ++i)
-        for (int32_t k = rp[i]; k < rp[i + 1]; ++k) {
-            const int d = (int)((int64_t)ci[k] - i);
-            auto it = std::lower_bound(offs.begin(), offs.end(), d);
-            if (it == offs.end() || *it != d) {
-                if ((int)offs.size() == DIA_MAX) return false;
-                offs.insert(it, d);
-            }
-        }
-    return (double)offs.size() * (double)n <= 1.5 * (double)A.nnz + (double)KRB * offs.size();
-}
-
 int sella_build_dia(SellA &S, const gs2_csr &A, int R, const std::vector<int> &offs, hipStream_t s)
 {
     sella_free(S);
@@ -174,7 +117,8 @@ int sella_build_dia(SellA &S, const gs2_csr &A, int R, const std::vector<int> &o
     S.dstride = std::max<int64_t>(1, (A.n + KRB - 1) / KRB) * KRB;
     for (int d = 0; d < DIA_MAX; ++d) S.doff[d] = d < S.ndiag ? offs[d] : 0;
     const size_t bytes = sizeof(double) * (size_t)std::max(S.ndiag, 1) * (size_t)S.dstride;
-    GS2_TRY_HIP(hipMalloc(&S.dval, bytes));
+    GS2_TRY_HIP(hipMalloc(&S.mem[0], bytes));
+    S.dval = (double *)S.mem[0];
     GS2_TRY_HIP(hipMemsetAsync(S.dval, 0, bytes, s));
     S.sel = -R;
     return GS2_OK;
@@ -190,7 +134,8 @@ int sella_build_b3(SellA &S, const gs2_csr &A, int R, const std::vector<int> &of
     S.dstride = std::max<int64_t>(1, (A.n / 3 + KRB - 1) / KRB) * KRB; // nodes
     for (int d = 0; d < DIA_MAX; ++d) S.doff[d] = d < S.ndiag ? offs[d] : 0;
     const size_t bytes = sizeof(double) * 9 * (size_t)std::max(S.ndiag, 1) * (size_t)S.dstride;
-    GS2_TRY_HIP(hipMalloc(&S.dval, bytes));
+    GS2_TRY_HIP(hipMalloc(&S.mem[0], bytes));
+    S.dval = (double *)S.mem[0];
     GS2_TRY_HIP(hipMemsetAsync(S.dval, 0, bytes, s));
     S.sel = -10 - R;
     return GS2_OK;
@@ -230,22 +175,29 @@ int sella_fill_values(SellA &S, const gs2_csr &A, bool with_col, hipStream_t s)
 // Lanes per row: from K0 (the rule: the mean row length, as for the
 // triangles), K grows while a few long rows would pad the copy beyond twice
 // the entries.
-static int sella_structure(SellA &S, const gs2_csr &A, int K0, int64_t *len, hipStream_t s)
+static int sella_structure(SellA &S, const gs2_csr &A, int K0, hipStream_t s)
 {
     const int tb = 256;
     for (int K = K0;; K *= 2) {
         S.K = K;
         S.C = WAVE / K;
         S.nslices = (A.n + S.C - 1) / S.C;
-        k_sella_len<<<(unsigned)((S.nslices + 1 + tb - 1) / tb), tb, 0, s>>>(A.n, S.nslices, K, A.rowptr, len);
-        GS2_TRY(exclusive_scan_i64(len, S.sp, S.nslices + 1, s));
+        const int64_t m = S.nslices + 1;
+        // pointers, lengths, scan totals
+        if (S.mem[0]) GS2_TRY_HIP(hipFree(S.mem[0]));
+        S.mem[0] = nullptr;
+        GS2_TRY_HIP(hipMalloc(&S.mem[0], sizeof(int64_t) * (2 * m + scan_tmp(m))));
+        S.sp = (int64_t *)S.mem[0];
+        k_sella_len<<<(unsigned)((m + tb - 1) / tb), tb, 0, s>>>(A.n, S.nslices, K, A.rowptr, S.sp + m);
+        GS2_TRY(exclusive_scan_i64(S.sp + m, S.sp, m, S.sp + 2 * m, s));
         GS2_TRY_HIP(hipMemcpyAsync(&S.padded, S.sp + S.nslices, sizeof(int64_t), hipMemcpyDeviceToHost, s));
         GS2_TRY_HIP(hipStreamSynchronize(s));
         if (K == WAVE || S.padded <= 2 * A.nnz + WAVE * S.nslices) break;
     }
-    const int64_t alloc = std::max<int64_t>(S.padded, WAVE);
-    GS2_TRY_HIP(hipMalloc(&S.col, sizeof(int32_t) * alloc));
-    GS2_TRY_HIP(hipMalloc(&S.val, sizeof(double) * alloc));
+    const size_t cnt = (size_t)std::max<int64_t>(S.padded, WAVE), vb = aligned(sizeof(double) * cnt);
+    GS2_TRY_HIP(hipMalloc(&S.mem[1], vb + sizeof(int32_t) * cnt));
+    S.val = (double *)S.mem[1];
+    S.col = (int32_t *)((char *)S.mem[1] + vb);
     return GS2_OK;
 }
 
@@ -258,14 +210,7 @@ int sella_build_sell(SellA &S, const gs2_csr &A, int K0, hipStream_t s)
     sella_free(S);
     S.n = A.n;
     S.nnz = A.nnz;
-    int64_t *len = nullptr;
-    int st = GS2_OK;
-    const int64_t max_slices = A.n; // K = 64: one row per slice
-    if (hipMalloc(&S.sp, sizeof(int64_t) * (max_slices + 1)) != hipSuccess ||
-        hipMalloc(&len, sizeof(int64_t) * (max_slices + 1)) != hipSuccess)
-        st = GS2_ERR_NOMEM;
-    if (st == GS2_OK) st = sella_structure(S, A, K0, len, s);
-    if (len) (void)hipFree(len);
+    int st = sella_structure(S, A, K0, s);
     if (st == GS2_OK) {
         S.sel = S.K;
         st = sella_fill_values(S, A, true, s);
@@ -274,15 +219,25 @@ int sella_build_sell(SellA &S, const gs2_csr &A, int K0, hipStream_t s)
     return st;
 }
 
-bool sella_dia_offsets(const gs2_csr &A, std::vector<int> &offs, hipStream_t s, int *st)
+// The offsets for a copy without column indices; the stored values (padding
+// included) may be at most 1.5 times the entries.
+bool sella_dia_offsets(const gs2_csr &A, const Pattern &P, std::vector<int> &offs)
 {
-    return A.n > 0 && A.n <= (int64_t(1) << 30) && diaA_offsets(A, offs, s, st);
+    if (P.many_d || A.n <= 0 || A.n > (int64_t(1) << 30) || (int)P.d.size() > DIA_MAX) return false;
+    offs = P.d;
+    return (double)offs.size() * (double)A.n <= 1.5 * (double)A.nnz + (double)KRB * offs.size();
 }
 
-bool sella_b3_offsets(const gs2_csr &A, std::vector<int> &offs, hipStream_t s, int *st)
+bool sella_b3_offsets(const gs2_csr &A, const Pattern &P, std::vector<int> &offs)
 {
-    return A.n > 0 && A.n <= (int64_t(1) << 30) && b3A_offsets(A, offs, s, st);
+    if (P.many_b || A.n <= 0 || A.n > (int64_t(1) << 30)) return false;
+    offs = P.bl;
+    offs.insert(offs.end(), P.bu.begin(), P.bu.end());
+    if (std::binary_search(P.d.begin(), P.d.end(), 0) || P.many_d) offs.push_back(0); // a diagonal entry
+    std::sort(offs.begin(), offs.end());
+    offs.erase(std::unique(offs.begin(), offs.end()), offs.end());
+    return (int)offs.size() <= DIA_MAX &&
+           3.0 * (double)offs.size() * (double)A.n <= 1.5 * (double)A.nnz + 3.0 * (double)KRB * offs.size();
 }
 
 } // namespace gs2
-

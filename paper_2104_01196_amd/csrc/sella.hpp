@@ -33,6 +33,7 @@ struct SellA {
     int64_t *sp = nullptr; // nslices + 1 offsets (multiples of 64)
     int32_t *col = nullptr;
     double *val = nullptr;
+    void *mem[2] = {nullptr, nullptr}; // the allocations behind the arrays
     // Diagonal-interleaved alternative for matrices with at most DIA_MAX
     // distinct offsets col - row (stencils in natural order): diagonal d holds
     // a_{i, i + off[d]} for every row i (0 where absent), rows in blocks of
@@ -102,14 +103,14 @@ int sella_rule_lanes(const gs2_csr &A);
 // sliced ELL with at least K0 lanes per row, values filled
 int sella_build_sell(SellA &S, const gs2_csr &A, int K0, hipStream_t s);
 // A's distinct offsets when it qualifies for the diagonal copy (<= DIA_MAX
-// offsets, stored diagonals <= 1.5x the entries); *st reports HIP failures
-bool sella_dia_offsets(const gs2_csr &A, std::vector<int> &offs, hipStream_t s, int *st);
+// offsets, stored diagonals <= 1.5x the entries)
+bool sella_dia_offsets(const gs2_csr &A, const Pattern &P, std::vector<int> &offs);
 // diagonal copy with R rows per lane (zeroed; fill with sella_fill_values)
 int sella_build_dia(SellA &S, const gs2_csr &A, int R, const std::vector<int> &offs, hipStream_t s);
 // A's distinct node offsets c/3 - r/3 when it qualifies for the 3-row
 // block copy (n divisible by 3, <= DIA_MAX offsets, the blocks storing <=
-// 1.5x the entries); *st reports HIP failures
-bool sella_b3_offsets(const gs2_csr &A, std::vector<int> &offs, hipStream_t s, int *st);
+// 1.5x the entries)
+bool sella_b3_offsets(const gs2_csr &A, const Pattern &P, std::vector<int> &offs);
 // 3-row block copy for the product kernel with R nodes per lane (zeroed;
 // fill with sella_fill_values)
 int sella_build_b3(SellA &S, const gs2_csr &A, int R, const std::vector<int> &offs, hipStream_t s);

@@ -24,62 +24,200 @@ static int flags_to_status(int f)
     return GS2_OK;
 }
 
-// One thread per row: structural checks, triangle counts, diagonal.
-__global__ void k_validate(int64_t n, int64_t nnz, const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
-                           const double *__restrict__ va, int32_t *__restrict__ lcnt, int32_t *__restrict__ ucnt,
-                           double *__restrict__ d, int *__restrict__ err)
+// ------------------------------------------------------- pattern scan
+//
+// One pass over the CSR input: structural checks, triangle counts, scaling
+// vectors, and the distinct offsets that decide whether the diagonal or the
+// 3-row block layout fits.  LN threads per row take every LN-th entry.  The
+// distinct offsets collect in hash tables in LDS (a stencil's entries find
+// theirs on the first probe), which every workgroup folds into the device's
+// at its end; a table that meets more keys than two triangles could have is
+// given up.  64^3 elasticity (61 M entries): 0.50 ms, where the checks alone
+// with one thread per row took 2.0 ms and the offsets a copy of the pattern
+// and a loop on the host.  90 x 84 x 77 diffusion (4 M entries): 0.11 ms.
+constexpr int PT_SLOTS = 128, PT_MOST = 2 * DIA_MAX + 1, PT_EMPTY = INT32_MIN;
+
+struct PatternDev {
+    int err, maxlen, lo, hi, many_d, many_b;
+    unsigned long long nl, nu;
+    int d[PT_SLOTS], bl[PT_SLOTS], bu[PT_SLOTS];
+};
+size_t pattern_dev_bytes() { return aligned(sizeof(PatternDev)); }
+
+__global__ void k_pattern_init(PatternDev *st)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == 0 && (rp[0] != 0 || rp[n] != nnz)) atomicOr(err, ERRF_BAD_CSR);
-    if (i >= n) return;
-    const int64_t b = rp[i], e = rp[i + 1];
-    if (b < 0 || e < b || e > nnz) {
-        atomicOr(err, ERRF_BAD_CSR);
-        return;
+    const int t = threadIdx.x;
+    if (t < PT_SLOTS) st->d[t] = st->bl[t] = st->bu[t] = PT_EMPTY;
+    if (t == 0) {
+        st->err = st->maxlen = st->lo = st->hi = st->many_d = st->many_b = 0;
+        st->nl = st->nu = 0;
     }
-    int prev = -1, nl = 0, nu = 0, found = 0, f = 0;
-    double dv = 0.0;
-    for (int64_t k = b; k < e; ++k) {
-        const int c = ci[k];
-        if (c <= prev || c >= n) f |= ERRF_BAD_CSR;
-        prev = c;
-        const double v = va[k];
-        if (!isfinite(v)) f |= ERRF_NONFINITE;
-        if (c < i) ++nl;
-        else if (c == i) { found = 1; dv = v; }
-        else ++nu;
-    }
-    if (!found || dv == 0.0) f |= ERRF_ZERO_DIAG;
-    if (f) atomicOr(err, f);
-    lcnt[i] = nl;
-    ucnt[i] = nu;
-    d[i] = dv;
 }
 
-__global__ void k_scaling(int64_t n, const double *__restrict__ d, double *__restrict__ sl, double *__restrict__ sr)
+// false when the table has no room for the key
+__device__ __forceinline__ bool table_add(int *keys, int key)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const double s = 1.0 / sqrt(fabs(d[i]));
-    sr[i] = s;
-    sl[i] = d[i] < 0.0 ? -s : s;
+    unsigned h = (unsigned)key * 2654435761u >> 25;
+    for (int p = 0; p < PT_SLOTS; ++p) {
+        const int k = keys[h];
+        if (k == key) return true;
+        if (k == PT_EMPTY) {
+            const int old = atomicCAS(&keys[h], PT_EMPTY, key);
+            if (old == PT_EMPTY || old == key) return true;
+        }
+        h = (h + 1) % PT_SLOTS;
+    }
+    return false;
 }
 
-// Stored entries of each slice: 64 * ceil(longest row / K).  The extra
-// element at index nslices is zero so that an exclusive scan yields the end.
-__global__ void k_slice_len(int64_t n, int64_t nslices, int K, const int32_t *__restrict__ cnt,
-                            int64_t *__restrict__ len)
+template <int LN, bool VALUES>
+__global__ __launch_bounds__(256) void k_scan_pattern(int64_t n, int64_t nnz, const int32_t *__restrict__ rp,
+                                                      const int32_t *__restrict__ ci, const double *__restrict__ va,
+                                                      int32_t *__restrict__ lcnt, int32_t *__restrict__ ucnt,
+                                                      double *__restrict__ sl, double *__restrict__ sr,
+                                                      PatternDev *st)
 {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s > nslices) return;
-    if (s == nslices) { len[s] = 0; return; }
-    const int C = WAVE / K;
-    int m = 0;
-    for (int r = 0; r < C; ++r) {
-        const int64_t row = s * C + r;
-        if (row < n) m = max(m, cnt[row]);
+    __shared__ int td[PT_SLOTS], tl[PT_SLOTS], tu[PT_SLOTS], many[2], sums[4];
+    __shared__ unsigned long long cnt[2];
+    const int t = threadIdx.x, q = t % LN;
+    for (int k = t; k < PT_SLOTS; k += 256) td[k] = tl[k] = tu[k] = PT_EMPTY;
+    if (t == 0) {
+        many[0] = st->many_d;
+        many[1] = n % 3 != 0 || st->many_b;
+        sums[0] = sums[1] = sums[2] = sums[3] = 0;
+        cnt[0] = cnt[1] = 0;
     }
-    len[s] = (int64_t)WAVE * ((m + K - 1) / K);
+    __syncthreads();
+    int f = 0, longest = 0, lo = 0, hi = 0;
+    unsigned long long nls = 0, nus = 0;
+    if (blockIdx.x == 0 && t == 0 && (rp[0] != 0 || rp[n] != nnz)) f |= ERRF_BAD_CSR;
+    const int64_t step = (int64_t)gridDim.x * (256 / LN);
+    for (int64_t i = (int64_t)blockIdx.x * (256 / LN) + t / LN; i < n; i += step) {
+        const int64_t b = rp[i], e = rp[i + 1];
+        if (b < 0 || e < b || e > nnz) {
+            f |= ERRF_BAD_CSR;
+            continue;
+        }
+        int nl = 0, nu = 0, found = 0;
+        double dv = 0.0;
+        const int node = (int)i / 3;
+        for (int64_t k = b + q; k < e; k += LN) {
+            const int c = ci[k];
+            const bool bad = c <= (k > b ? ci[k - 1] : -1) || c >= n;
+            double v = 0.0;
+            if constexpr (VALUES) {
+                v = va[k];
+                if (!isfinite(v)) f |= ERRF_NONFINITE;
+            }
+            if (c < i) ++nl;
+            else if (c > i) ++nu;
+            else {
+                found = 1;
+                dv = v;
+            }
+            if (bad) {
+                f |= ERRF_BAD_CSR;
+                continue;
+            }
+            const int d = (int)(c - i);
+            lo = min(lo, d);
+            hi = max(hi, d);
+            if (!many[0] && !table_add(td, d)) many[0] = 1;
+            if (!many[1] && d != 0 && !table_add(d < 0 ? tl : tu, c / 3 - node)) many[1] = 1;
+        }
+#pragma unroll
+        for (int o = 1; o < LN; o <<= 1) {
+            nl += __shfl_xor(nl, o);
+            nu += __shfl_xor(nu, o);
+            found |= __shfl_xor(found, o);
+            dv += __shfl_xor(dv, o);
+        }
+        if (q == 0) {
+            nls += nl;
+            nus += nu;
+            longest = max(longest, (int)(e - b) - 1);
+            if constexpr (VALUES) {
+                if (!found || dv == 0.0) f |= ERRF_ZERO_DIAG;
+                lcnt[i] = nl;
+                ucnt[i] = nu;
+                const double sc = 1.0 / sqrt(fabs(dv));
+                sr[i] = sc;
+                sl[i] = dv < 0.0 ? -sc : sc;
+            }
+        }
+    }
+    if (f) atomicOr(&sums[0], f);
+    if (longest) atomicMax(&sums[1], longest);
+    if (lo) atomicMin(&sums[2], lo);
+    if (hi) atomicMax(&sums[3], hi);
+    if (nls) atomicAdd(&cnt[0], nls);
+    if (nus) atomicAdd(&cnt[1], nus);
+    __syncthreads();
+    if (t == 0) {
+        if (sums[0]) atomicOr(&st->err, sums[0]);
+        // a plain read first: after a few workgroups the extremes stand
+        if (sums[1] > st->maxlen) atomicMax(&st->maxlen, sums[1]);
+        if (sums[2] < st->lo) atomicMin(&st->lo, sums[2]);
+        if (sums[3] > st->hi) atomicMax(&st->hi, sums[3]);
+        atomicAdd(&st->nl, cnt[0]);
+        atomicAdd(&st->nu, cnt[1]);
+    }
+    // the keys into the device's tables (found by a plain read after the first workgroups)
+    if (t < PT_SLOTS) {
+        if (td[t] != PT_EMPTY && !many[0] && !table_add(st->d, td[t])) many[0] = 1;
+        if (!many[1] && tl[t] != PT_EMPTY && !table_add(st->bl, tl[t])) many[1] = 1;
+        if (!many[1] && tu[t] != PT_EMPTY && !table_add(st->bu, tu[t])) many[1] = 1;
+    }
+    __syncthreads();
+    if (t == 0) {
+        if (many[0]) st->many_d = 1;
+        if (many[1]) st->many_b = 1;
+    }
+}
+
+static void table_list(const int *keys, std::vector<int> &out, bool &many)
+{
+    for (int k = 0; k < PT_SLOTS; ++k)
+        if (keys[k] != PT_EMPTY) out.push_back(keys[k]);
+    std::sort(out.begin(), out.end());
+    many = many || (int)out.size() > PT_MOST;
+}
+
+int scan_pattern(const gs2_csr &A, int32_t *lcnt, int32_t *ucnt, double *sl, double *sr, PatternDev *dev, Pattern &out,
+                 hipStream_t s)
+{
+    out = Pattern{};
+    k_pattern_init<<<1, PT_SLOTS, 0, s>>>(dev);
+    // 8 threads per row for stencil rows, 32 for long ones; 16 groups of rows
+    // and more per workgroup, 2048 workgroups at most, so that folding the
+    // tables and counts, one workgroup after the other, stays small
+    const bool wide = A.nnz > 24 * A.n;
+    const int per = 256 / (wide ? 32 : 8);
+    const int64_t groups = (A.n + per - 1) / per;
+    const unsigned g = (unsigned)std::min<int64_t>(groups, std::min<int64_t>(std::max<int64_t>(256, groups / 16), 2048));
+    if (lcnt) {
+        if (wide) k_scan_pattern<32, true><<<g, 256, 0, s>>>(A.n, A.nnz, A.rowptr, A.colind, A.val, lcnt, ucnt, sl, sr, dev);
+        else k_scan_pattern<8, true><<<g, 256, 0, s>>>(A.n, A.nnz, A.rowptr, A.colind, A.val, lcnt, ucnt, sl, sr, dev);
+    } else {
+        if (wide) k_scan_pattern<32, false><<<g, 256, 0, s>>>(A.n, A.nnz, A.rowptr, A.colind, nullptr, nullptr, nullptr, nullptr, nullptr, dev);
+        else k_scan_pattern<8, false><<<g, 256, 0, s>>>(A.n, A.nnz, A.rowptr, A.colind, nullptr, nullptr, nullptr, nullptr, nullptr, dev);
+    }
+    GS2_TRY_HIP(hipGetLastError());
+    PatternDev h;
+    GS2_TRY_HIP(hipMemcpyAsync(&h, dev, sizeof(h), hipMemcpyDeviceToHost, s));
+    GS2_TRY_HIP(hipStreamSynchronize(s));
+    out.err = h.err;
+    out.maxlen = h.maxlen;
+    out.lo = h.lo;
+    out.hi = h.hi;
+    out.nl = (int64_t)h.nl;
+    out.nu = (int64_t)h.nu;
+    out.many_d = h.many_d != 0;
+    out.many_b = A.n % 3 != 0 || h.many_b != 0;
+    table_list(h.d, out.d, out.many_d);
+    table_list(h.bl, out.bl, out.many_b);
+    table_list(h.bu, out.bu, out.many_b);
+    return GS2_OK;
 }
 
 // IEEE binary16 round-to-nearest-even of a float64, by integer manipulation of
@@ -135,50 +273,61 @@ __device__ __forceinline__ _Float16 convert_scaled<_Float16>(double v, int *ovf)
 // off-block lower entries first and the off-block upper entries last.
 enum : int { PART_L = 0, PART_U = 1, PART_E = 2 };
 
-struct Ranges {
-    int32_t *off1 = nullptr, *cnt1 = nullptr, *off2 = nullptr, *cnt2 = nullptr, *tot = nullptr;
+struct Rows {
+    const int32_t *rp, *ci, *lcnt, *ucnt;
+    int64_t n, bs;
 };
 
-__global__ void k_ranges(int64_t n, const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
-                         const int32_t *__restrict__ lcnt, const int32_t *__restrict__ ucnt, int64_t bs, int part,
-                         Ranges R)
+struct Range {
+    int o1, c1, o2, c2;
+};
+
+__device__ __forceinline__ Range row_range(const Rows &A, int part, int64_t i)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int64_t b0 = (i / bs) * bs, b1 = b0 + bs < n ? b0 + bs : n;
-    const int lc = lcnt[i], uc = ucnt[i];
-    const int64_t r = rp[i];
+    const int lc = A.lcnt[i], uc = A.ucnt[i];
     int lo = 0, hi = 0;
-    while (lo < lc && ci[r + lo] < b0) ++lo;
-    while (hi < uc && ci[r + lc + uc - hi] >= b1) ++hi;
-    int o1 = 0, c1 = 0, o2 = 0, c2 = 0;
-    if (part == PART_L) {
-        o1 = lo;
-        c1 = lc - lo;
-    } else if (part == PART_U) {
-        o1 = lc + 1;
-        c1 = uc - hi;
-    } else {
-        o1 = 0;
-        c1 = lo;
-        o2 = lc + 1 + uc - hi;
-        c2 = hi;
+    if (A.bs < A.n) {
+        const int64_t b0 = (i / A.bs) * A.bs, b1 = b0 + A.bs < A.n ? b0 + A.bs : A.n, r = A.rp[i];
+        while (lo < lc && A.ci[r + lo] < b0) ++lo;
+        while (hi < uc && A.ci[r + lc + uc - hi] >= b1) ++hi;
     }
-    R.off1[i] = o1;
-    R.cnt1[i] = c1;
-    R.off2[i] = o2;
-    R.cnt2[i] = c2;
-    R.tot[i] = c1 + c2;
+    if (part == PART_L) return Range{lo, lc - lo, 0, 0};
+    if (part == PART_U) return Range{lc + 1, uc - hi, 0, 0};
+    return Range{0, lo, lc + 1 + uc - hi, hi};
+}
+
+// Stored entries of each slice of a part: 64 * ceil(longest row / K), one
+// lane per row.  The extra element at index nslices is zero so that an
+// exclusive scan yields the end.  Adds the part's entries to *total, if given
+// (one workgroup after the other: only where the pattern scan's count does
+// not hold, with several blocks).
+__global__ __launch_bounds__(256) void k_slice_len(Rows A, int part, int64_t nslices, int K, int64_t *__restrict__ len,
+                                                   unsigned long long *total)
+{
+    const int C = WAVE / K;
+    const int64_t row = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    int c = 0;
+    if (row < A.n) {
+        const Range r = row_range(A, part, row);
+        c = r.c1 + r.c2;
+    }
+    int m = c;
+    for (int o = 1; o < C; o <<= 1) m = max(m, __shfl_xor(m, o));
+    if (total) {
+        int sum = c;
+        for (int o = 1; o < WAVE; o <<= 1) sum += __shfl_xor(sum, o);
+        if (threadIdx.x % WAVE == 0 && sum) atomicAdd(total, (unsigned long long)sum);
+    }
+    if (row % C == 0 && row / C <= nslices) len[row / C] = row / C == nslices ? 0 : (int64_t)WAVE * ((m + K - 1) / K);
 }
 
 // One thread per (slice, lane): writes the lane's entries of its row, the
 // value (s_l[i] * a_ij) * s_r[j] rounded once to VT, padding with
-// (own column, 0).
+// (own column, 0); with off, the columns' 16-bit form col - row - off_min too.
 template <typename VT>
-__global__ void k_fill(int64_t n, int64_t nslices, int K, const int32_t *__restrict__ rp,
-                       const int32_t *__restrict__ ci, const double *__restrict__ va, Ranges R,
-                       const double *__restrict__ sl, const double *__restrict__ sr,
-                       const int64_t *__restrict__ sp, int32_t *__restrict__ col, VT *__restrict__ val,
+__global__ void k_fill(Rows A, int part, int64_t nslices, int K, const double *__restrict__ va,
+                       const double *__restrict__ sl, const double *__restrict__ sr, const int64_t *__restrict__ sp,
+                       int32_t *__restrict__ col, uint16_t *__restrict__ off, int off_min, VT *__restrict__ val,
                        int *__restrict__ err)
 {
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -187,175 +336,55 @@ __global__ void k_fill(int64_t n, int64_t nslices, int K, const int32_t *__restr
     const int l = (int)(gid % WAVE);
     const int C = WAVE / K;
     const int r = l / K, q = l % K;
-    const int64_t row = s * C + r;
+    const int64_t row = s * C + r, n = A.n;
     const int64_t beg = sp[s];
     const int steps = (int)((sp[s + 1] - beg) / WAVE);
-    const int c_row = row < n ? R.tot[row] : 0;
-    const int c1 = row < n ? R.cnt1[row] : 0;
-    const int64_t base = row < n ? (int64_t)rp[row] : 0;
-    const int o1 = row < n ? R.off1[row] : 0, o2 = row < n ? R.off2[row] : 0;
+    const Range rg = row < n ? row_range(A, part, row) : Range{0, 0, 0, 0};
+    const int64_t base = row < n ? (int64_t)A.rp[row] : 0;
     const int32_t pad_col = (int32_t)(row < n ? row : n - 1);
     const double srow = row < n ? sl[row] : 0.0;
     int ovf = 0;
     for (int t = 0; t < steps; ++t) {
         const int e = t * K + q;
         const int64_t pos = beg + (int64_t)t * WAVE + l;
-        if (e < c_row) {
-            const int64_t idx = base + (e < c1 ? o1 + e : o2 + (e - c1));
-            const int32_t c = ci[idx];
-            const double sc = (srow * va[idx]) * sr[c];
-            col[pos] = c;
-            val[pos] = convert_scaled<VT>(sc, &ovf);
-        } else {
-            col[pos] = pad_col;
-            val[pos] = VT(0);
+        int32_t c = pad_col;
+        VT v = VT(0);
+        if (e < rg.c1 + rg.c2) {
+            const int64_t idx = base + (e < rg.c1 ? rg.o1 + e : rg.o2 + (e - rg.c1));
+            c = A.ci[idx];
+            v = convert_scaled<VT>((srow * va[idx]) * sr[c], &ovf);
         }
+        col[pos] = c;
+        val[pos] = v;
+        if (off) off[pos] = (uint16_t)(c - (int)row - off_min);
     }
     if (ovf) atomicOr(err, ERRF_FP16);
 }
 
 void free_sell(Sell &S)
 {
-    if (S.slice_ptr) (void)hipFree(S.slice_ptr);
-    if (S.col) (void)hipFree(S.col);
-    if (S.off) (void)hipFree(S.off);
-    if (S.val) (void)hipFree(S.val);
+    for (void *&p : S.mem) {
+        if (p) (void)hipFree(p);
+        p = nullptr;
+    }
     S.slice_ptr = nullptr;
     S.col = nullptr;
     S.off = nullptr;
     S.val = nullptr;
 }
 
-// One thread per (slice, lane): d = col - row for each of its entries.
-// Pass 0 folds the smallest and largest d into mm[0], mm[1]; pass 1 writes
-// d - dmin.
-__global__ void k_col_offsets(int64_t nslices, int K, const int64_t *__restrict__ sp, const int32_t *__restrict__ col,
-                              int pass, int dmin, uint16_t *__restrict__ off, int *__restrict__ mm)
-{
-    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t s = gid / WAVE;
-    if (s >= nslices) return;
-    const int l = (int)(gid % WAVE);
-    const int64_t row = s * (WAVE / K) + l / K;
-    const int64_t beg = sp[s];
-    const int steps = (int)((sp[s + 1] - beg) / WAVE);
-    int lo = 0x7fffffff, hi = -0x7fffffff;
-    for (int t = 0; t < steps; ++t) {
-        const int64_t pos = beg + (int64_t)t * WAVE + l;
-        const int d = (int)((int64_t)col[pos] - row);
-        if (pass == 0) {
-            lo = d < lo ? d : lo;
-            hi = d > hi ? d : hi;
-        } else {
-            off[pos] = (uint16_t)(d - dmin);
-        }
-    }
-    if (pass == 0 && steps > 0) {
-        atomicMin(&mm[0], lo);
-        atomicMax(&mm[1], hi);
-    }
-}
-
-int build_col_offsets(int64_t nslices, int K, const int64_t *sp, const int32_t *col, int64_t padded, uint16_t **off,
-                      int *off_min, hipStream_t s)
-{
-    *off = nullptr;
-    *off_min = 0;
-    if (nslices <= 0) return GS2_OK;
-    int *mm = nullptr;
-    GS2_TRY_HIP(hipMalloc(&mm, 2 * sizeof(int)));
-    const int init[2] = {0x7fffffff, -0x7fffffff};
-    int h[2] = {0, 0};
-    const int tb = 256;
-    const unsigned grid = (unsigned)((nslices * WAVE + tb - 1) / tb);
-    int st = GS2_OK;
-    // a blocking copy: init lives on this stack frame
-    if (hipStreamSynchronize(s) != hipSuccess || hipMemcpy(mm, init, sizeof(init), hipMemcpyHostToDevice) != hipSuccess)
-        st = GS2_ERR_HIP;
-    if (st == GS2_OK) {
-        k_col_offsets<<<grid, tb, 0, s>>>(nslices, K, sp, col, 0, 0, nullptr, mm);
-        if (hipGetLastError() != hipSuccess || hipMemcpyAsync(h, mm, sizeof(h), hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess)
-            st = GS2_ERR_HIP;
-    }
-    (void)hipFree(mm);
-    if (st != GS2_OK) return st;
-    if (h[0] > h[1] || (int64_t)h[1] - (int64_t)h[0] > 65535) return GS2_OK; // no entries, or too wide: 32 bits
-    uint16_t *o = nullptr;
-    GS2_TRY_HIP(hipMalloc(&o, sizeof(uint16_t) * std::max<int64_t>(padded, WAVE)));
-    k_col_offsets<<<grid, tb, 0, s>>>(nslices, K, sp, col, 1, h[0], o, nullptr);
-    if (hipGetLastError() != hipSuccess) {
-        (void)hipFree(o);
-        return GS2_ERR_HIP;
-    }
-    *off = o;
-    *off_min = h[0];
-    return GS2_OK;
-}
-
 // ------------------------------------------- diagonal-interleaved triangles
 
 void free_dia(Dia &D)
 {
-    if (D.val) (void)hipFree(D.val);
-    D.val = nullptr;
+    if (D.mem) (void)hipFree(D.mem);
+    D.mem = D.val = nullptr;
 }
 
 struct DiaOffs {
     int nd;
     int off[DIA_MAX];
 };
-
-// Distinct offsets col - row of the strictly lower and upper parts, ascending,
-// and their entry counts, from a host copy of the pattern.  False when either
-// part has more than DIA_MAX offsets.  Columns are sorted within a row, so a
-// row's offsets ascend; each is looked up by binary search.
-static bool dia_offsets(const std::vector<int32_t> &rp, const std::vector<int32_t> &ci, int64_t n,
-                        std::vector<int> &offL, std::vector<int> &offU, int64_t &nnzL, int64_t &nnzU)
-{
-    offL.clear();
-    offU.clear();
-    nnzL = nnzU = 0;
-    for (int64_t i = 0; i < n; ++i) {
-        for (int32_t k = rp[i]; k < rp[i + 1]; ++k) {
-            const int d = (int)((int64_t)ci[k] - i);
-            if (d == 0) continue;
-            std::vector<int> &o = d < 0 ? offL : offU;
-            (d < 0 ? nnzL : nnzU)++;
-            auto it = std::lower_bound(o.begin(), o.end(), d);
-            if (it == o.end() || *it != d) {
-                if ((int)o.size() == DIA_MAX) return false;
-                o.insert(it, d);
-            }
-        }
-    }
-    return true;
-}
-
-// The same for 3-row blocks (n a multiple of 3): distinct node offsets c/3 -
-// r/3 of the strictly lower entries (c < r, node offsets <= 0) and of the
-// strictly upper ones (node offsets >= 0).  False when n is not a multiple
-// of 3 or either part has more than DIA_MAX node offsets.
-static bool b3_offsets(const std::vector<int32_t> &rp, const std::vector<int32_t> &ci, int64_t n,
-                       std::vector<int> &offL, std::vector<int> &offU)
-{
-    offL.clear();
-    offU.clear();
-    if (n % 3 != 0) return false;
-    for (int64_t i = 0; i < n; ++i) {
-        for (int32_t k = rp[i]; k < rp[i + 1]; ++k) {
-            if ((int64_t)ci[k] == i) continue;
-            const int d = (int)((int64_t)ci[k] / 3 - i / 3);
-            std::vector<int> &o = (int64_t)ci[k] < i ? offL : offU;
-            auto it = std::lower_bound(o.begin(), o.end(), d);
-            if (it == o.end() || *it != d) {
-                if ((int)o.size() == DIA_MAX) return false;
-                o.insert(it, d);
-            }
-        }
-    }
-    return true;
-}
 
 // One thread per row: the row's entries of one part go to their diagonal at
 // the row's interleaved position, value (s_l[i] * a_ij) * s_r[j] rounded once
@@ -417,15 +446,12 @@ __global__ void k_b3_fill(int64_t n, int R, const int32_t *__restrict__ rp, cons
     if (ovf) atomicOr(err, ERRF_FP16);
 }
 
-// Build one triangle (lower or upper) in the diagonal-interleaved layout
-// with R rows per lane, or in the 3-row block layout with R nodes per lane;
-// rows (nodes) are padded to whole workgroups of the sweep kernels
-// (DIA_THREADS * R of them) so that every launched lane has a slot.
-static int build_dia(Dia &D, int64_t n, int precision, int lower, int R, const std::vector<int> &offs, int64_t nnz,
-                     const gs2_csr &A, const int32_t *lcnt, const double *sl, const double *sr, int *err,
-                     hipStream_t s, int b3 = 0)
+// Describe one triangle in the diagonal-interleaved layout with R rows per
+// lane, or in the 3-row block layout with R nodes per lane; rows (nodes) are
+// padded to whole workgroups of the sweep kernels (DIA_THREADS * R of them)
+// so that every launched lane has a slot.  Returns its bytes.
+static size_t shape_dia(Dia &D, int64_t n, int precision, int R, const std::vector<int> &offs, int64_t nnz, int b3)
 {
-    free_dia(D);
     D.ndiag = (int)offs.size();
     D.R = R;
     D.nnz = nnz;
@@ -433,39 +459,25 @@ static int build_dia(Dia &D, int64_t n, int precision, int lower, int R, const s
     D.val_bytes = precision == GS2_FP64 ? 8 : precision == GS2_FP32 ? 4 : 2;
     const int64_t wg = (int64_t)DIA_THREADS * R, units = b3 ? n / 3 : n;
     D.stride = std::max<int64_t>(1, (units + wg - 1) / wg) * wg;
+    for (int d = 0; d < DIA_MAX; ++d) D.off[d] = d < D.ndiag ? offs[d] : 0;
+    return aligned((size_t)std::max(1, D.ndiag) * (b3 ? 9 : 1) * (size_t)D.stride * D.val_bytes);
+}
+
+template <typename VT>
+static void fill_dia(const Dia &D, int64_t n, int lower, const gs2_csr &A, const int32_t *lcnt, const double *sl,
+                     const double *sr, int *err, hipStream_t s)
+{
+    if (D.ndiag == 0 || n == 0) return;
     DiaOffs o;
     o.nd = D.ndiag;
-    for (int d = 0; d < DIA_MAX; ++d) {
-        D.off[d] = d < D.ndiag ? offs[d] : 0;
-        o.off[d] = D.off[d];
-    }
-    const size_t bytes = (size_t)std::max(1, D.ndiag) * (b3 ? 9 : 1) * (size_t)D.stride * D.val_bytes;
-    GS2_TRY_HIP(hipMalloc(&D.val, bytes));
-    GS2_TRY_HIP(hipMemsetAsync(D.val, 0, bytes, s));
-    if (D.ndiag == 0 || n == 0) return GS2_OK;
-    const int tb = 256;
-    const unsigned g = (unsigned)((n + tb - 1) / tb);
-    if (b3) {
-        if (precision == GS2_FP64)
-            k_b3_fill<double><<<g, tb, 0, s>>>(n, R, A.rowptr, A.colind, A.val, lcnt, lower, o, sl, sr, D.stride,
-                                               (double *)D.val, err);
-        else if (precision == GS2_FP32)
-            k_b3_fill<float><<<g, tb, 0, s>>>(n, R, A.rowptr, A.colind, A.val, lcnt, lower, o, sl, sr, D.stride,
-                                              (float *)D.val, err);
-        else
-            k_b3_fill<_Float16><<<g, tb, 0, s>>>(n, R, A.rowptr, A.colind, A.val, lcnt, lower, o, sl, sr, D.stride,
-                                                 (_Float16 *)D.val, err);
-    } else if (precision == GS2_FP64)
-        k_dia_fill<double><<<g, tb, 0, s>>>(n, R, A.rowptr, A.colind, A.val, lcnt, lower, o, sl, sr, D.stride,
-                                            (double *)D.val, err);
-    else if (precision == GS2_FP32)
-        k_dia_fill<float><<<g, tb, 0, s>>>(n, R, A.rowptr, A.colind, A.val, lcnt, lower, o, sl, sr, D.stride,
-                                           (float *)D.val, err);
+    for (int d = 0; d < DIA_MAX; ++d) o.off[d] = D.off[d];
+    const unsigned g = (unsigned)((n + 255) / 256);
+    if (D.b3)
+        k_b3_fill<VT><<<g, 256, 0, s>>>(n, D.R, A.rowptr, A.colind, A.val, lcnt, lower, o, sl, sr, D.stride, (VT *)D.val,
+                                        err);
     else
-        k_dia_fill<_Float16><<<g, tb, 0, s>>>(n, R, A.rowptr, A.colind, A.val, lcnt, lower, o, sl, sr, D.stride,
-                                              (_Float16 *)D.val, err);
-    GS2_TRY_HIP(hipGetLastError());
-    return GS2_OK;
+        k_dia_fill<VT><<<g, 256, 0, s>>>(n, D.R, A.rowptr, A.colind, A.val, lcnt, lower, o, sl, sr, D.stride,
+                                         (VT *)D.val, err);
 }
 
 // ------------------------------------------------------- exclusive scan
@@ -534,20 +546,16 @@ __global__ __launch_bounds__(SCAN_TB) void k_scan_add(int64_t *__restrict__ out,
     if (i < m) out[i] += bsum[i / SCAN_BLOCK];
 }
 
-int exclusive_scan_i64(const int64_t *in, int64_t *out, int64_t m, hipStream_t s)
+int64_t scan_tmp(int64_t m) { return (m + SCAN_BLOCK - 1) / SCAN_BLOCK; }
+
+int exclusive_scan_i64(const int64_t *in, int64_t *out, int64_t m, int64_t *tmp, hipStream_t s)
 {
     if (m <= 0) return GS2_OK;
-    const int64_t nb = (m + SCAN_BLOCK - 1) / SCAN_BLOCK;
-    int64_t *bsum = nullptr;
-    GS2_TRY_HIP(hipMalloc(&bsum, sizeof(int64_t) * nb));
-    k_scan_local<<<(unsigned)nb, SCAN_TB, 0, s>>>(in, out, m, bsum);
-    k_scan_sums<<<1, SCAN_TB, 0, s>>>(bsum, nb);
-    k_scan_add<<<(unsigned)((m + SCAN_TB - 1) / SCAN_TB), SCAN_TB, 0, s>>>(out, m, bsum);
-    const hipError_t e = hipGetLastError();
-    const hipError_t e2 = hipStreamSynchronize(s);
-    (void)hipFree(bsum);
-    GS2_TRY_HIP(e);
-    GS2_TRY_HIP(e2);
+    const int64_t nb = scan_tmp(m);
+    k_scan_local<<<(unsigned)nb, SCAN_TB, 0, s>>>(in, out, m, tmp);
+    k_scan_sums<<<1, SCAN_TB, 0, s>>>(tmp, nb);
+    k_scan_add<<<(unsigned)((m + SCAN_TB - 1) / SCAN_TB), SCAN_TB, 0, s>>>(out, m, tmp);
+    GS2_TRY_HIP(hipGetLastError());
     return GS2_OK;
 }
 
@@ -561,52 +569,27 @@ int choose_lanes(double avg_len, int max_len)
     return 16;
 }
 
-static int build_one(Sell &S, int64_t n, int K, int precision, const gs2_csr &A, const Ranges &R,
-                     const double *sl, const double *sr, int *err, hipStream_t s)
+// Timed choices, process-wide, keyed by the size bucket, rounded mean row
+// length, longest-row bucket, precision and what else the choice depends on.
+static std::mutex g_choice_mu;
+static std::map<std::string, int> g_choices;
+
+bool choice_get(const std::string &key, int *choice)
 {
-    const int32_t *cnt = R.tot;
-    free_sell(S);
-    S.n = n;
-    S.K = K;
-    S.C = WAVE / K;
-    S.nslices = (n + S.C - 1) / S.C;
-    S.val_bytes = precision == GS2_FP64 ? 8 : precision == GS2_FP32 ? 4 : 2;
-    int64_t *len = nullptr;
-    GS2_TRY_HIP(hipMalloc(&S.slice_ptr, sizeof(int64_t) * (S.nslices + 1)));
-    GS2_TRY_HIP(hipMalloc(&len, sizeof(int64_t) * (S.nslices + 1)));
-    const int tb = 256;
-    k_slice_len<<<(unsigned)((S.nslices + 1 + tb - 1) / tb), tb, 0, s>>>(n, S.nslices, K, cnt, len);
-    GS2_TRY(exclusive_scan_i64(len, S.slice_ptr, S.nslices + 1, s));
-    GS2_TRY_HIP(hipMemcpyAsync(&S.padded, S.slice_ptr + S.nslices, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    GS2_TRY_HIP(hipStreamSynchronize(s));
-    (void)hipFree(len);
-    const int64_t alloc = std::max<int64_t>(S.padded, WAVE);
-    GS2_TRY_HIP(hipMalloc(&S.col, sizeof(int32_t) * alloc));
-    GS2_TRY_HIP(hipMalloc(&S.val, (size_t)S.val_bytes * alloc));
-    const int64_t threads = S.nslices * WAVE;
-    const unsigned grid = (unsigned)((threads + tb - 1) / tb);
-    if (S.nslices > 0) {
-        if (precision == GS2_FP64)
-            k_fill<double><<<grid, tb, 0, s>>>(n, S.nslices, K, A.rowptr, A.colind, A.val, R, sl, sr, S.slice_ptr,
-                                               S.col, (double *)S.val, err);
-        else if (precision == GS2_FP32)
-            k_fill<float><<<grid, tb, 0, s>>>(n, S.nslices, K, A.rowptr, A.colind, A.val, R, sl, sr, S.slice_ptr,
-                                              S.col, (float *)S.val, err);
-        else
-            k_fill<_Float16><<<grid, tb, 0, s>>>(n, S.nslices, K, A.rowptr, A.colind, A.val, R, sl, sr, S.slice_ptr,
-                                                 S.col, (_Float16 *)S.val, err);
-        GS2_TRY_HIP(hipGetLastError());
-        GS2_TRY(build_col_offsets(S.nslices, K, S.slice_ptr, S.col, S.padded, &S.off, &S.off_min, s));
-    }
-    return GS2_OK;
+    std::lock_guard<std::mutex> lk(g_choice_mu);
+    auto it = g_choices.find(key);
+    if (it == g_choices.end()) return false;
+    *choice = it->second;
+    return true;
 }
 
-// Process-wide cache of autotuned lane counts, keyed by the size bucket,
-// rounded mean row length, longest-row bucket and precision.
-static std::mutex g_tune_mu;
-static std::map<std::string, int> g_tune_cache;
+void choice_put(const std::string &key, int choice)
+{
+    std::lock_guard<std::mutex> lk(g_choice_mu);
+    g_choices[key] = choice;
+}
 
-static std::string tune_key(int64_t n, double avg, int maxlen, int prec)
+std::string shape_key(int64_t n, double avg, int maxlen, int prec)
 {
     int nb = 0;
     while ((int64_t(1) << nb) < n) ++nb;
@@ -617,37 +600,112 @@ static std::string tune_key(int64_t n, double avg, int maxlen, int prec)
     return buf;
 }
 
+// Device scratch of one setup, in one allocation.
 struct SetupScratch {
+    void *mem = nullptr;
     int32_t *lcnt = nullptr, *ucnt = nullptr;
-    double *d = nullptr;
     int *err = nullptr;
-    Ranges R;
+    PatternDev *dev = nullptr;
+    Pattern pat;
+    int alloc(int64_t n)
+    {
+        const size_t cnt = aligned(sizeof(int32_t) * n);
+        GS2_TRY_HIP(hipMalloc(&mem, 2 * cnt + pattern_dev_bytes() + aligned(sizeof(int))));
+        char *p = (char *)mem;
+        lcnt = (int32_t *)p;
+        ucnt = (int32_t *)(p + cnt);
+        dev = (PatternDev *)(p + 2 * cnt);
+        err = (int *)(p + 2 * cnt + pattern_dev_bytes());
+        return GS2_OK;
+    }
     ~SetupScratch()
     {
-        for (void *p : {(void *)lcnt, (void *)ucnt, (void *)d, (void *)err, (void *)R.off1, (void *)R.cnt1,
-                        (void *)R.off2, (void *)R.cnt2, (void *)R.tot})
-            if (p) (void)hipFree(p);
+        if (mem) (void)hipFree(mem);
     }
 };
 
-// Ranges of part `part` for every row, then the part itself in sliced-ELL.
-static int build_part(Handle &h, Sell &S, int part, int K, const gs2_csr &A, SetupScratch &sc, hipStream_t s)
+template <typename VT>
+static void fill_part(const Handle &h, const Sell &S, int part, const Rows &R, const gs2_csr &A, int *err, hipStream_t s)
 {
-    const int64_t bs = h.blocks > 1 ? (h.n + h.blocks - 1) / h.blocks : std::max<int64_t>(h.n, 1);
-    k_ranges<<<(unsigned)((h.n + 255) / 256), 256, 0, s>>>(h.n, A.rowptr, A.colind, sc.lcnt, sc.ucnt, bs, part, sc.R);
-    GS2_TRY_HIP(hipGetLastError());
-    return build_one(S, h.n, K, h.precision, A, sc.R, h.sl, h.sr, sc.err, s);
+    k_fill<VT><<<(unsigned)((S.nslices * WAVE + 255) / 256), 256, 0, s>>>(R, part, S.nslices, S.K, A.val, h.sl, h.sr,
+                                                                         S.slice_ptr, S.col, S.off, S.off_min,
+                                                                         (VT *)S.val, err);
 }
 
-static int64_t count_total(const int32_t *tot, int64_t n, hipStream_t s, int *st)
+// The parts [first, last] in sliced-ELL with K lanes per row, their slice
+// pointers in one allocation and their entries in another, both owned by the
+// first.  16-bit column offsets where the pattern's span allows them.
+static int build_parts(Handle &h, int first, int last, int K, const gs2_csr &A, const SetupScratch &sc, hipStream_t s)
 {
-    std::vector<int32_t> t(n);
-    *st = GS2_OK;
-    if (n && hipMemcpyAsync(t.data(), tot, sizeof(int32_t) * n, hipMemcpyDeviceToHost, s) != hipSuccess) *st = GS2_ERR_HIP;
-    if (hipStreamSynchronize(s) != hipSuccess) *st = GS2_ERR_HIP;
-    int64_t c = 0;
-    for (int32_t v : t) c += v;
-    return c;
+    Sell *const part[3] = {&h.L, &h.U, &h.E};
+    const int np = last - first + 1;
+    const int64_t n = h.n;
+    const Rows R{A.rowptr, A.colind, sc.lcnt, sc.ucnt, n, h.blocks > 1 ? (n + h.blocks - 1) / h.blocks : n};
+    const int vb = h.precision == GS2_FP64 ? 8 : h.precision == GS2_FP32 ? 4 : 2;
+    const int64_t C = WAVE / K, ns = (n + C - 1) / C, tmp = scan_tmp(ns + 1);
+    for (int q = first; q <= last; ++q) free_sell(*part[q]);
+    Sell &own = *part[first];
+    // per part: pointers, lengths, scan totals, entry count
+    const int64_t per = 2 * (ns + 1) + tmp + 1;
+    GS2_TRY_HIP(hipMalloc(&own.mem[0], sizeof(int64_t) * per * np));
+    int64_t *base = (int64_t *)own.mem[0];
+    int64_t ends[3][2];
+    for (int q = 0; q < np; ++q) {
+        Sell &S = *part[first + q];
+        S.n = n;
+        S.K = K;
+        S.C = (int)C;
+        S.nslices = ns;
+        S.val_bytes = vb;
+        S.slice_ptr = base + q * per;
+        int64_t *len = S.slice_ptr + ns + 1, *tot = len + ns + 1 + tmp;
+        const bool count = h.blocks > 1;
+        if (count) GS2_TRY_HIP(hipMemsetAsync(tot, 0, sizeof(int64_t), s));
+        k_slice_len<<<(unsigned)((ns * C + 1 + 255) / 256), 256, 0, s>>>(R, first + q, ns, K, len,
+                                                                       count ? (unsigned long long *)tot : nullptr);
+        GS2_TRY(exclusive_scan_i64(len, S.slice_ptr, ns + 1, len + ns + 1, s));
+        GS2_TRY_HIP(hipMemcpyAsync(&ends[q][0], S.slice_ptr + ns, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+        ends[q][1] = first + q == PART_L ? sc.pat.nl : sc.pat.nu;
+        if (count) GS2_TRY_HIP(hipMemcpyAsync(&ends[q][1], tot, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    }
+    GS2_TRY_HIP(hipStreamSynchronize(s));
+    size_t bytes = 0, at[3][3];
+    for (int q = 0; q < np; ++q) {
+        Sell &S = *part[first + q];
+        S.padded = ends[q][0];
+        S.nnz = ends[q][1];
+        // padding sits at offset 0, and past the last row up to 63 below it
+        const int64_t lo = std::min<int64_t>(first + q == PART_U ? 0 : sc.pat.lo, 1 - WAVE);
+        const int64_t hi = first + q == PART_L ? 0 : sc.pat.hi;
+        const bool narrow = S.nnz > 0 && hi - lo <= 65535;
+        S.off_min = narrow ? (int)lo : 0;
+        const size_t cnt = (size_t)std::max<int64_t>(S.padded, WAVE);
+        at[q][0] = bytes;
+        at[q][1] = at[q][0] + aligned(cnt * sizeof(int32_t));
+        at[q][2] = at[q][1] + aligned(cnt * vb);
+        bytes = at[q][2] + (narrow ? aligned(cnt * sizeof(uint16_t)) : 0);
+        S.off = narrow ? (uint16_t *)1 : nullptr; // placed below
+    }
+    GS2_TRY_HIP(hipMalloc(&own.mem[1], bytes));
+    for (int q = 0; q < np; ++q) {
+        Sell &S = *part[first + q];
+        char *m = (char *)own.mem[1];
+        S.col = (int32_t *)(m + at[q][0]);
+        S.val = m + at[q][1];
+        if (S.off) S.off = (uint16_t *)(m + at[q][2]);
+        if (h.precision == GS2_FP64) fill_part<double>(h, S, first + q, R, A, sc.err, s);
+        else if (h.precision == GS2_FP32) fill_part<float>(h, S, first + q, R, A, sc.err, s);
+        else fill_part<_Float16>(h, S, first + q, R, A, sc.err, s);
+    }
+    GS2_TRY_HIP(hipGetLastError());
+    return GS2_OK;
+}
+
+static int build_triangles(Handle &h, int K, const gs2_csr &A, const SetupScratch &sc, hipStream_t s)
+{
+    GS2_TRY(build_parts(h, PART_L, PART_U, K, A, sc, s));
+    h.L.nt = h.U.nt = h.L.stored_bytes() + h.U.stored_bytes() > NT_TRIANGLES_BYTES ? 1 : 0;
+    return GS2_OK;
 }
 
 // The setup's flush buffer (FLUSH_BYTES of zeros, read before each timed
@@ -655,10 +713,12 @@ static int64_t count_total(const int32_t *tot, int64_t n, hipStream_t s, int *st
 // memory for it the passes are timed back to back.
 struct FlushBuffer {
     Handle &h;
-    FlushBuffer(Handle &hh, bool on, hipStream_t s) : h(hh)
+    hipStream_t s;
+    FlushBuffer(Handle &hh, hipStream_t ss) : h(hh), s(ss) {}
+    // called where a timing begins
+    void hold()
     {
-        h.flush = nullptr;
-        if (!on) return;
+        if (h.flush) return;
         if (hipMalloc(&h.flush, FLUSH_BYTES) != hipSuccess) {
             h.flush = nullptr;
             (void)hipGetLastError();
@@ -677,18 +737,18 @@ struct FlushBuffer {
     }
 };
 
-// Schedules of the diagonal layout chosen by timing, per (size bucket, mean
-// row length, longest-row bucket, precision, diagonal counts).
+// Schedules of the diagonal layout chosen by timing (packed into one number).
 struct DiaChoice {
     int fmt, R, lds, remap, b3;
+    int pack() const { return fmt | R << 4 | lds << 8 | remap << 9 | b3 << 10; }
+    static DiaChoice unpack(int v) { return DiaChoice{v & 15, v >> 4 & 15, v >> 8 & 1, v >> 9 & 1, v >> 10 & 1}; }
 };
-static std::map<std::string, DiaChoice> g_dia_cache;
 
 // Decide the layout of the GS2 / JR passes: keep the sliced-ELL triangles, or
 // build diagonal-interleaved copies (Dia: scalar diagonals, or 3-row blocks
 // along node offsets) and time them against sliced ELL.
-static int choose_format(Handle &h, const gs2_csr &A, const gs2_options &o, SetupScratch &sc, hipStream_t s,
-                         bool can_time, const std::string &key_base)
+static int choose_format(Handle &h, const gs2_csr &A, const gs2_options &o, SetupScratch &sc, FlushBuffer &flush,
+                         hipStream_t s, bool can_time, const std::string &key_base)
 {
     h.fmt = FMT_SELL;
     h.lds = 0;
@@ -698,30 +758,22 @@ static int choose_format(Handle &h, const gs2_csr &A, const gs2_options &o, Setu
     if (o.format == GS2_FORMAT_AUTO && !(can_time && o.autotune)) return GS2_OK;
     const int64_t n = h.n;
     const bool any = h.blocks == 1 && n > 0 && n <= (int64_t(1) << 30);
-    std::vector<int> offL, offU, boffL, boffU;
-    int64_t nnzL = 0, nnzU = 0;
+    std::vector<int> offL, offU;
+    const std::vector<int> &boffL = sc.pat.bl, &boffU = sc.pat.bu;
+    const int64_t nnzL = sc.pat.nl, nnzU = sc.pat.nu;
     bool dia_ok = false, b3_ok = false;
     if (any) {
-        std::vector<int32_t> rp(n + 1), ci(std::max<int64_t>(A.nnz, 1));
-        GS2_TRY_HIP(hipMemcpyAsync(rp.data(), A.rowptr, sizeof(int32_t) * (n + 1), hipMemcpyDeviceToHost, s));
-        if (A.nnz)
-            GS2_TRY_HIP(hipMemcpyAsync(ci.data(), A.colind, sizeof(int32_t) * A.nnz, hipMemcpyDeviceToHost, s));
-        GS2_TRY_HIP(hipStreamSynchronize(s));
-        if (o.format != GS2_FORMAT_BLOCK3) {
-            dia_ok = dia_offsets(rp, ci, n, offL, offU, nnzL, nnzU);
-            // stored diagonal entries (padding included) at most 1.5x the real ones
-            dia_ok = dia_ok && (double)offL.size() * n <= 1.5 * nnzL + 64.0 * offL.size() &&
-                     (double)offU.size() * n <= 1.5 * nnzU + 64.0 * offU.size();
+        // stored diagonal entries (padding included) at most 1.5x the real ones
+        auto fits = [n](const std::vector<int> &off, int64_t nnz, double rows) {
+            return (int)off.size() <= DIA_MAX && rows * off.size() * n <= 1.5 * nnz + rows * 64.0 * off.size();
+        };
+        if (o.format != GS2_FORMAT_BLOCK3 && !sc.pat.many_d) {
+            for (int d : sc.pat.d)
+                if (d) (d < 0 ? offL : offU).push_back(d);
+            dia_ok = fits(offL, nnzL, 1.0) && fits(offU, nnzU, 1.0);
         }
-        if (!dia_ok && o.format != GS2_FORMAT_DIA) {
-            nnzL = nnzU = 0; // dia_offsets may have stopped part way
-            for (int64_t i = 0; i < n; ++i)
-                for (int32_t k = rp[i]; k < rp[i + 1]; ++k)
-                    if ((int64_t)ci[k] != i) ((int64_t)ci[k] < i ? nnzL : nnzU)++;
-            b3_ok = b3_offsets(rp, ci, n, boffL, boffU) &&
-                    3.0 * boffL.size() * n <= 1.5 * nnzL + 192.0 * boffL.size() &&
-                    3.0 * boffU.size() * n <= 1.5 * nnzU + 192.0 * boffU.size();
-        }
+        if (!dia_ok && o.format != GS2_FORMAT_DIA && !sc.pat.many_b)
+            b3_ok = fits(boffL, nnzL, 3.0) && fits(boffU, nnzU, 3.0);
     }
     h.DL.ndiag = dia_ok ? (int)offL.size() : b3_ok ? (int)boffL.size() : 0;
     h.DU.ndiag = dia_ok ? (int)offU.size() : b3_ok ? (int)boffU.size() : 0;
@@ -743,9 +795,23 @@ static int choose_format(Handle &h, const gs2_csr &A, const gs2_options &o, Setu
     std::vector<int> rms;
     if (o.xcd_ranges == 0) rms = {1, 0};
     else rms = {o.xcd_ranges == 2 ? 1 : 0};
+    // both triangles, in one allocation
     auto build = [&](int R) -> int {
-        GS2_TRY(build_dia(h.DL, n, h.precision, 1, R, b3 ? boffL : offL, nnzL, A, sc.lcnt, h.sl, h.sr, sc.err, s, b3));
-        GS2_TRY(build_dia(h.DU, n, h.precision, 0, R, b3 ? boffU : offU, nnzU, A, sc.lcnt, h.sl, h.sr, sc.err, s, b3));
+        free_dia(h.DL);
+        free_dia(h.DU);
+        const size_t bl = shape_dia(h.DL, n, h.precision, R, b3 ? boffL : offL, nnzL, b3);
+        const size_t bu = shape_dia(h.DU, n, h.precision, R, b3 ? boffU : offU, nnzU, b3);
+        GS2_TRY_HIP(hipMalloc(&h.DL.mem, bl + bu));
+        GS2_TRY_HIP(hipMemsetAsync(h.DL.mem, 0, bl + bu, s));
+        h.DL.val = h.DL.mem;
+        h.DU.val = (char *)h.DL.mem + bl;
+        for (int lower = 1; lower >= 0; --lower) {
+            const Dia &D = lower ? h.DL : h.DU;
+            if (h.precision == GS2_FP64) fill_dia<double>(D, n, lower, A, sc.lcnt, h.sl, h.sr, sc.err, s);
+            else if (h.precision == GS2_FP32) fill_dia<float>(D, n, lower, A, sc.lcnt, h.sl, h.sr, sc.err, s);
+            else fill_dia<_Float16>(D, n, lower, A, sc.lcnt, h.sl, h.sr, sc.err, s);
+        }
+        GS2_TRY_HIP(hipGetLastError());
         h.DL.nt = h.DU.nt = h.DL.stored_bytes() + h.DU.stored_bytes() > NT_TRIANGLES_BYTES ? 1 : 0;
         return GS2_OK;
     };
@@ -764,16 +830,11 @@ static int choose_format(Handle &h, const gs2_csr &A, const gs2_options &o, Setu
                   o.lds_staging, o.xcd_ranges);
     const std::string key = key_base + kb;
     DiaChoice ch{FMT_SELL, 0, 0, 1, 0};
-    bool cached = false;
-    {
-        std::lock_guard<std::mutex> lk(g_tune_mu);
-        auto it = g_dia_cache.find(key);
-        if (it != g_dia_cache.end()) {
-            ch = it->second;
-            cached = true;
-        }
-    }
-    if (!cached) {
+    int packed = 0;
+    if (choice_get(key, &packed)) {
+        ch = DiaChoice::unpack(packed);
+    } else {
+        flush.hold();
         float best = 1e30f;
         if (o.format == GS2_FORMAT_AUTO) {
             h.fmt = FMT_SELL;
@@ -795,8 +856,7 @@ static int choose_format(Handle &h, const gs2_csr &A, const gs2_options &o, Setu
                     }
                 }
         }
-        std::lock_guard<std::mutex> lk(g_tune_mu);
-        g_dia_cache[key] = ch;
+        choice_put(key, ch.pack());
     }
     h.tuned = 1;
     if (ch.fmt == FMT_SELL) {
@@ -886,9 +946,11 @@ static int build_perm(Handle &h, Perm &P, std::vector<int32_t> &order, int lower
 {
     struct Tmp {
         int32_t *place = nullptr;
+        int64_t *len = nullptr;
         ~Tmp()
         {
             if (place) (void)hipFree(place);
+            if (len) (void)hipFree(len);
         }
     } tmp;
     if (by_place) {
@@ -901,16 +963,15 @@ static int build_perm(Handle &h, Perm &P, std::vector<int32_t> &order, int lower
     }
     order.resize((order.size() + WAVE - 1) / WAVE * WAVE, -1);
     P.nchunks = (int64_t)order.size() / WAVE;
-    int64_t *len = nullptr, total = 0;
+    int64_t total = 0;
     GS2_TRY_HIP(hipMalloc(&P.rows, sizeof(int32_t) * order.size()));
     GS2_TRY_HIP(hipMalloc(&P.ptr, sizeof(int64_t) * (P.nchunks + 1)));
     GS2_TRY_HIP(hipMemcpyAsync(P.rows, order.data(), sizeof(int32_t) * order.size(), hipMemcpyHostToDevice, s));
-    GS2_TRY_HIP(hipMalloc(&len, sizeof(int64_t) * (P.nchunks + 1)));
-    k_perm_len<<<(unsigned)(((P.nchunks + 1) * WAVE + 255) / 256), 256, 0, s>>>(P.nchunks, P.rows, A.rowptr, len);
-    const int st = exclusive_scan_i64(len, P.ptr, P.nchunks + 1, s); // synchronises: `order` may go
-    (void)hipFree(len);
-    GS2_TRY(st);
-    GS2_TRY_HIP(hipMemcpy(&total, P.ptr + P.nchunks, sizeof(int64_t), hipMemcpyDeviceToHost));
+    GS2_TRY_HIP(hipMalloc(&tmp.len, sizeof(int64_t) * (P.nchunks + 1 + scan_tmp(P.nchunks + 1))));
+    k_perm_len<<<(unsigned)(((P.nchunks + 1) * WAVE + 255) / 256), 256, 0, s>>>(P.nchunks, P.rows, A.rowptr, tmp.len);
+    GS2_TRY(exclusive_scan_i64(tmp.len, P.ptr, P.nchunks + 1, tmp.len + P.nchunks + 1, s));
+    GS2_TRY_HIP(hipMemcpyAsync(&total, P.ptr + P.nchunks, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    GS2_TRY_HIP(hipStreamSynchronize(s)); // `order` may go
     const size_t vb = h.precision == GS2_FP64 ? 8 : h.precision == GS2_FP32 ? 4 : 2;
     GS2_TRY_HIP(hipMalloc(&P.col, sizeof(int32_t) * std::max<int64_t>(total, WAVE)));
     GS2_TRY_HIP(hipMalloc(&P.val, vb * std::max<int64_t>(total, WAVE)));
@@ -925,7 +986,7 @@ static int build_perm(Handle &h, Perm &P, std::vector<int32_t> &order, int lower
         k_perm_fill<_Float16><<<g, 256, 0, s>>>(P.nchunks, P.rows, P.ptr, A.rowptr, A.colind, A.val, lcnt, lower,
                                                 tmp.place, h.sl, h.sr, P.col, (_Float16 *)P.val);
     GS2_TRY_HIP(hipGetLastError());
-    if (tmp.place) GS2_TRY_HIP(hipStreamSynchronize(s)); // it goes with this scope
+    GS2_TRY_HIP(hipStreamSynchronize(s)); // tmp goes with this scope
     return GS2_OK;
 }
 
@@ -1007,15 +1068,27 @@ static int build_levels(Handle &h, const gs2_csr &A, const int32_t *lcnt, hipStr
     return build_colors(h, A, lcnt, rp, ci, s);
 }
 
-static int alloc_vectors(Handle &h)
+// The scaling vectors and, with work, the applies' temporaries.
+static int alloc_vectors(Handle &h, bool work)
 {
-    const size_t vb = prec_bytes(h.precision) * (size_t)std::max<int64_t>(h.n, 1);
-    GS2_TRY_HIP(hipMalloc(&h.xh, vb));
-    GS2_TRY_HIP(hipMalloc(&h.xh2, vb));
-    GS2_TRY_HIP(hipMalloc(&h.rh, vb));
-    GS2_TRY_HIP(hipMalloc(&h.ga, vb));
-    GS2_TRY_HIP(hipMalloc(&h.gb, vb));
-    if (h.precision != GS2_FP64) GS2_TRY_HIP(hipMalloc(&h.sv, vb));
+    const size_t n = (size_t)std::max<int64_t>(h.n, 1), d = aligned(sizeof(double) * n);
+    const size_t vb = aligned(prec_bytes(h.precision) * n);
+    const bool sv = h.precision != GS2_FP64, yh = h.blocks > 1;
+    GS2_TRY_HIP(hipMalloc(&h.vec, 2 * d + (work ? (5 + sv + yh) * vb : 0)));
+    char *p = (char *)h.vec;
+    h.sl = (double *)p;
+    h.sr = (double *)(p + d);
+    if (!work) return GS2_OK;
+    p += 2 * d;
+    for (void **q : {&h.xh, &h.xh2, &h.rh, &h.ga, &h.gb}) {
+        *q = p;
+        p += vb;
+    }
+    if (sv) {
+        h.sv = p;
+        p += vb;
+    }
+    if (yh) h.yh = p;
     return GS2_OK;
 }
 
@@ -1024,87 +1097,43 @@ int setup_handle(Handle &h, const gs2_csr &A, const gs2_options &o, hipStream_t 
     const int64_t n = A.n;
     if (n == 0) return GS2_OK;
     SetupScratch sc;
-    const size_t nb = (size_t)std::max<int64_t>(n, 1);
-    GS2_TRY_HIP(hipMalloc(&sc.lcnt, sizeof(int32_t) * nb));
-    GS2_TRY_HIP(hipMalloc(&sc.ucnt, sizeof(int32_t) * nb));
-    GS2_TRY_HIP(hipMalloc(&sc.d, sizeof(double) * nb));
-    GS2_TRY_HIP(hipMalloc(&sc.err, sizeof(int)));
-    for (int32_t **p : {&sc.R.off1, &sc.R.cnt1, &sc.R.off2, &sc.R.cnt2, &sc.R.tot})
-        GS2_TRY_HIP(hipMalloc(p, sizeof(int32_t) * nb));
-    GS2_TRY_HIP(hipMalloc(&h.sl, sizeof(double) * nb));
-    GS2_TRY_HIP(hipMalloc(&h.sr, sizeof(double) * nb));
+    GS2_TRY(sc.alloc(n));
+    GS2_TRY(alloc_vectors(h, alloc_vecs));
     GS2_TRY_HIP(hipMemsetAsync(sc.err, 0, sizeof(int), s));
-    const int tb = 256;
-    const unsigned g = (unsigned)((n + tb) / tb);
-    k_validate<<<g, tb, 0, s>>>(n, A.nnz, A.rowptr, A.colind, A.val, sc.lcnt, sc.ucnt, sc.d, sc.err);
-    GS2_TRY_HIP(hipGetLastError());
-    GS2_TRY(read_err(sc.err, s));
-    k_scaling<<<g, tb, 0, s>>>(n, sc.d, h.sl, h.sr);
-    GS2_TRY_HIP(hipGetLastError());
+    GS2_TRY(scan_pattern(A, sc.lcnt, sc.ucnt, h.sl, h.sr, sc.dev, sc.pat, s));
+    GS2_TRY(flags_to_status(sc.pat.err));
 
     // row-length statistics of L (U has the same count for symmetric patterns)
     const double avg = n ? (double)(A.nnz - n) / (2.0 * n) : 0.0;
-    int maxlen = 0;
-    {
-        std::vector<int32_t> rp(n + 1);
-        GS2_TRY_HIP(hipMemcpyAsync(rp.data(), A.rowptr, sizeof(int32_t) * (n + 1), hipMemcpyDeviceToHost, s));
-        GS2_TRY_HIP(hipStreamSynchronize(s));
-        for (int64_t i = 0; i < n; ++i) maxlen = std::max(maxlen, rp[i + 1] - rp[i] - 1);
-    }
-    if (alloc_vecs) GS2_TRY(alloc_vectors(h));
+    const int maxlen = sc.pat.maxlen;
+    const std::string shape = shape_key(n, avg, maxlen, h.precision);
 
     int K = o.lanes_per_row;
     if (K != 0 && (K < 1 || K > 64 || (K & (K - 1)))) return GS2_ERR_ARG;
+    const bool can_time = alloc_vecs && n >= 4096;
     // the schedule timing below reads the flush buffer before each timed pass
-    FlushBuffer flush(h, o.autotune && alloc_vecs && n >= 4096, s);
+    FlushBuffer flush(h, s);
     if (K == 0) {
         K = choose_lanes(avg, maxlen);
-        if (o.autotune && alloc_vecs && n >= 4096) {
-            const std::string key = tune_key(n, avg, maxlen, h.precision);
-            int cached = 0;
-            {
-                std::lock_guard<std::mutex> lk(g_tune_mu);
-                auto it = g_tune_cache.find(key);
-                if (it != g_tune_cache.end()) cached = it->second;
+        if (o.autotune && can_time && !choice_get("K_" + shape, &K)) {
+            flush.hold();
+            float best = 1e30f;
+            // each candidate is timed on one inner pass over L and one residual pass
+            // over L and U, with the cache policy its stored size implies
+            for (int cand = 1; cand <= 16; cand *= 2) {
+                if (cand > 1 && cand > 2 * std::max(1.0, avg)) break;
+                GS2_TRY(build_triangles(h, cand, A, sc, s));
+                float ms = 0.f;
+                GS2_TRY(time_inner_pass(h, s, &ms, true));
+                // a wider candidate must win by more than the timing noise
+                if (ms < 0.97f * best) { best = ms; K = cand; }
             }
-            if (cached) {
-                K = cached;
-            } else {
-                float best = 1e30f;
-                int bestK = K;
-                // each candidate is timed on one inner pass over L and one residual pass
-                // over L and U, with the cache policy its stored size implies
-                for (int cand = 1; cand <= 16; cand *= 2) {
-                    if (cand > 1 && cand > 2 * std::max(1.0, avg)) break;
-                    GS2_TRY(build_part(h, h.L, PART_L, cand, A, sc, s));
-                    GS2_TRY(build_part(h, h.U, PART_U, cand, A, sc, s));
-                    h.L.nt = h.U.nt = h.L.stored_bytes() + h.U.stored_bytes() > NT_TRIANGLES_BYTES ? 1 : 0;
-                    float ms = 0.f;
-                    GS2_TRY(time_inner_pass(h, s, &ms, true));
-                    // a wider candidate must win by more than the timing noise
-                    if (ms < 0.97f * best) { best = ms; bestK = cand; }
-                }
-                K = bestK;
-                std::lock_guard<std::mutex> lk(g_tune_mu);
-                g_tune_cache[key] = K;
-            }
+            choice_put("K_" + shape, K);
         }
     }
-    int cst = GS2_OK;
-    GS2_TRY(build_part(h, h.L, PART_L, K, A, sc, s));
-    h.L.nnz = count_total(sc.R.tot, n, s, &cst);
-    GS2_TRY(cst);
-    GS2_TRY(build_part(h, h.U, PART_U, K, A, sc, s));
-    h.U.nnz = count_total(sc.R.tot, n, s, &cst);
-    GS2_TRY(cst);
-    h.L.nt = h.U.nt = h.L.stored_bytes() + h.U.stored_bytes() > NT_TRIANGLES_BYTES ? 1 : 0;
-    GS2_TRY(choose_format(h, A, o, sc, s, alloc_vecs && n >= 4096, tune_key(n, avg, maxlen, h.precision)));
-    if (h.blocks > 1) {
-        GS2_TRY(build_part(h, h.E, PART_E, K, A, sc, s));
-        h.E.nnz = count_total(sc.R.tot, n, s, &cst);
-        GS2_TRY(cst);
-        if (alloc_vecs) GS2_TRY_HIP(hipMalloc(&h.yh, prec_bytes(h.precision) * nb));
-    }
+    GS2_TRY(build_triangles(h, K, A, sc, s));
+    GS2_TRY(choose_format(h, A, o, sc, flush, s, can_time, shape));
+    if (h.blocks > 1) GS2_TRY(build_parts(h, PART_E, PART_E, K, A, sc, s));
     GS2_TRY(read_err(sc.err, s));
     if (o.build_levels) GS2_TRY(build_levels(h, A, sc.lcnt, s));
     GS2_TRY_HIP(hipStreamSynchronize(s));
@@ -1125,7 +1154,7 @@ Handle::~Handle()
     free_perm(PL);
     free_perm(PU);
     free_perm(PC);
-    for (void *p : {(void *)sl, (void *)sr, xh, xh2, rh, ga, gb, sv, yh, (void *)tri_next})
+    for (void *p : {vec, (void *)tri_next})
         if (p) (void)hipFree(p);
     if (gw) free_gmres_work(gw);
     if (cw) free_cg_work(cw);
