@@ -69,44 +69,70 @@ __device__ __forceinline__ double block_sum(double v, double *red)
     return s;
 }
 
+// Orders a wavefront's LDS accesses before and after (its lanes run in step).
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // (one lane) Apply rotations 0..jc-1 to col (jc+1 entries used).  The entry
 // carried from one rotation to the next stays in a register, so the chain
-// is two multiply-adds per rotation; the loads run ahead of it.
-__device__ __forceinline__ void apply_rotations(const double *__restrict__ cs, const double *__restrict__ sn,
-                                                double *__restrict__ col, int jc)
+// is two multiply-adds per rotation; a block's loads are issued before its
+// first rotation.  The fused operations are written out here and below, so
+// that every kernel these are part of rounds alike.
+__device__ __forceinline__ void apply_rotations(const double *cs, const double *sn, double *col, int jc)
 {
+    constexpr int U = 4;
     double carry = col[0];
-    for (int k = 0; k < jc; ++k) {
-        const double x = col[k + 1];
-        col[k] = cs[k] * carry + sn[k] * x;
-        carry = -sn[k] * carry + cs[k] * x;
+    for (int k0 = 0; k0 < jc; k0 += U) {
+        double c[U], s[U], x[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int k = k0 + q < jc ? k0 + q : jc - 1;
+            c[q] = cs[k];
+            s[q] = sn[k];
+            x[q] = col[k + 1];
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+            if (k0 + q < jc) {
+                col[k0 + q] = fma(c[q], carry, s[q] * x[q]);
+                carry = fma(-s[q], carry, c[q] * x[q]);
+            }
     }
     col[jc] = carry;
 }
 
-// (one lane) Apply the committed rotations 0..jc-1 of the state ls (in
+// (one wavefront) Apply the committed rotations 0..jc-1 of the state ls (in
 // LDS) to col (jc+2 entries), form rotation jc, store column jc of R into H
-// (global) and advance the residual recurrence g.
-__device__ inline bool commit_column(GState *ls, double *__restrict__ H, double *col, int jc)
+// (row stride ldh) and advance the residual recurrence g.  col is complete
+// on entry (wave_fence).
+__device__ inline bool commit_column(GState *ls, double *__restrict__ H, int ldh, double *col, int jc)
 {
-    apply_rotations(ls->cs, ls->sn, col, jc);
+    const int ln = threadIdx.x & (WAVE - 1);
+    if (ln == 0) apply_rotations(ls->cs, ls->sn, col, jc);
+    wave_fence();
     const double rho = hypot(col[jc], col[jc + 1]);
     if (!isfinite(rho)) {
-        ls->status = GS2_ERR_NONFINITE;
+        if (ln == 0) ls->status = GS2_ERR_NONFINITE;
         return false;
     }
     if (rho == 0.0) {
-        ls->status = GS2_BREAKDOWN_EXACT;
+        if (ln == 0) ls->status = GS2_BREAKDOWN_EXACT;
         return false;
     }
     const double c = col[jc] / rho, sn = col[jc + 1] / rho;
-    ls->cs[jc] = c;
-    ls->sn[jc] = sn;
-    col[jc] = rho;
-    for (int k = 0; k <= jc; ++k) H[k * MAXM + jc] = col[k];
-    const double gj = ls->g[jc];
-    ls->g[jc + 1] = -sn * gj;
-    ls->g[jc] = c * gj;
+    for (int k = ln; k < jc; k += WAVE) H[k * ldh + jc] = col[k];
+    if (ln == 0) {
+        H[jc * ldh + jc] = rho;
+        ls->cs[jc] = c;
+        ls->sn[jc] = sn;
+        const double gj = ls->g[jc];
+        ls->g[jc + 1] = -sn * gj;
+        ls->g[jc] = c * gj;
+    }
+    wave_fence();
     return true;
 }
 
@@ -122,8 +148,8 @@ __device__ inline bool reorth_scalars(const GState *st, int j, const double *as,
     if (t < WAVE) {
         double aa = 0.0, ac = 0.0;
         for (int k = ln; k < j; k += WAVE) {
-            aa += as[k] * as[k];
-            ac += as[k] * cs_[k];
+            aa = fma(as[k], as[k], aa);
+            ac = fma(as[k], cs_[k], ac);
         }
         aa = wave_sum(aa);
         ac = wave_sum(ac);
@@ -140,16 +166,103 @@ __device__ inline bool reorth_scalars(const GState *st, int j, const double *as,
     return ok;
 }
 
-// The step's serial work (one workgroup): correct and commit column j-1
-// ([ht + nu a; nu alpha]) now that u's reorthogonalisation is known, store
-// the new tentative column [c, e], form ||w'|| from the partials, the
-// tentative rotation of column j and the residual estimate, and either stop
-// the cycle or advance j (the next tentative vector keeps its scale 1/||w'||
-// in zs[j+1]).  When u fell into span(Q) the cycle ends on the tentative
-// column j-1.  The work is latency-bound: the whole workgroup (KT threads)
-// stages the state (all but H) in LDS together with the partial sums, so one
-// round trip to memory precedes the serial work of one lane, and writes it
-// back.
+// (one wavefront) The step's serial work on the state ls (in LDS): correct
+// and commit column j-1 ([ht + nu a; nu alpha]) now that u's
+// reorthogonalisation is known, store the new tentative column [c, e], take
+// ||w'||^2 = tot, form the tentative rotation of column j and the residual
+// estimate, and either stop the cycle or advance j (the next tentative vector
+// keeps its scale 1/||w'|| in zs[j+1]).  When u fell into span(Q) (!ok) the
+// cycle ends on the tentative column j-1.  Only the two chains of rotations
+// run in one lane; with all of it there, the work took 5 us at 30 columns.
+__device__ inline void dcgs_finish_wave(GState *ls, double *__restrict__ H, int ldh, double *col, bool ok,
+                                        double alpha, double e, double a2, double tot)
+{
+    const int ln = threadIdx.x & (WAVE - 1);
+    const bool one = ln == 0;
+    const int j = ls->j;
+    const double nu_prev = ls->nu;
+    if (!ok) {
+        int kk = j - 1;
+        if (!isfinite(a2)) {
+            if (one) ls->status = GS2_ERR_NONFINITE;
+        } else {
+            for (int k = ln; k < j; k += WAVE) col[k] = ls->ht[k];
+            if (one) col[j] = nu_prev;
+            wave_fence();
+            if (commit_column(ls, H, ldh, col, j - 1)) kk = j;
+        }
+        if (one) {
+            ls->kk = kk;
+            ls->done = 1;
+        }
+        return;
+    }
+    if (j > 0) {
+        for (int k = ln; k < j; k += WAVE) col[k] = fma(nu_prev, ls->hA[k], ls->ht[k]);
+        if (one) col[j] = nu_prev * alpha;
+        wave_fence();
+        if (!commit_column(ls, H, ldh, col, j - 1)) {
+            if (one) {
+                ls->kk = j - 1;
+                ls->done = 1;
+            }
+            return;
+        }
+    }
+    // tentative column j: [c, e; ||w'||]
+    const double nu = sqrt(tot);
+    for (int k = ln; k < j; k += WAVE) {
+        const double c = ls->hB[k];
+        ls->ht[k] = c;
+        col[k] = c;
+    }
+    if (one) {
+        ls->inv_alpha = 1.0 / alpha;
+        ls->e = e;
+        ls->ht[j] = e;
+        ls->nu = nu;
+        col[j] = e;
+        col[j + 1] = nu;
+    }
+    wave_fence();
+    if (one) apply_rotations(ls->cs, ls->sn, col, j);
+    wave_fence();
+    const double rho = hypot(col[j], col[j + 1]);
+    if (!isfinite(rho) || !isfinite(nu)) {
+        if (one) {
+            ls->status = GS2_ERR_NONFINITE;
+            ls->done = 1;
+            ls->kk = j;
+        }
+        return;
+    }
+    const double est = rho > 0.0 ? fabs(col[j + 1] / rho * ls->g[j]) : 0.0;
+    const bool breakdown = nu <= 1e-14 * sqrt(ls->wn2);
+    if (est <= ls->rtol * ls->bnorm || breakdown || j + 1 >= ls->maxsteps) {
+        wave_fence();
+        for (int k = ln; k < j; k += WAVE) col[k] = ls->ht[k];
+        if (one) {
+            col[j] = e;
+            col[j + 1] = nu;
+        }
+        wave_fence();
+        const bool good = commit_column(ls, H, ldh, col, j);
+        if (one) {
+            ls->kk = good ? j + 1 : j;
+            ls->done = 1;
+        }
+    } else if (one) {
+        ls->kk = j + 1;
+        ls->inv = 1.0 / nu;
+        ls->zs[j + 1] = 1.0 / nu;
+        ls->j = j + 1;
+    }
+}
+
+// The step's serial work (one workgroup, KT threads).  It is latency-bound:
+// the whole workgroup stages the state (all but H) in LDS together with the
+// partial sums, so one round trip to memory precedes the serial work of one
+// wavefront, and writes it back.
 __device__ __forceinline__ void dcgs_finish_block(const double *__restrict__ part, int nb, GState *__restrict__ st)
 {
     __shared__ unsigned long long sw[GSTATE_SMALL_WORDS];
@@ -178,63 +291,8 @@ __device__ __forceinline__ void dcgs_finish_block(const double *__restrict__ par
     const int j = ls->j;
     double alpha, e, a2;
     const bool ok = reorth_scalars(ls, j, ls->hA, ls->hB, sc, &alpha, &e, &a2);
-    if (t == 0) {
-        const double nu_prev = ls->nu;
-        if (!ok) {
-            if (!isfinite(a2)) {
-                ls->status = GS2_ERR_NONFINITE;
-                ls->kk = j - 1;
-            } else {
-                for (int k = 0; k < j; ++k) col[k] = ls->ht[k];
-                col[j] = nu_prev;
-                ls->kk = commit_column(ls, st->H, col, j - 1) ? j : j - 1;
-            }
-            ls->done = 1;
-        } else {
-            bool good = true;
-            if (j > 0) {
-                for (int k = 0; k < j; ++k) col[k] = ls->ht[k] + nu_prev * ls->hA[k];
-                col[j] = nu_prev * alpha;
-                good = commit_column(ls, st->H, col, j - 1);
-            }
-            if (!good) {
-                ls->kk = j - 1;
-                ls->done = 1;
-            }
-        }
-        if (ok && !ls->done) {
-            ls->inv_alpha = 1.0 / alpha;
-            ls->e = e;
-            // tentative column j: [c, e; ||w'||]
-            for (int k = 0; k < j; ++k) ls->ht[k] = ls->hB[k];
-            ls->ht[j] = e;
-            const double nu = sqrt(tot);
-            ls->nu = nu;
-            for (int k = 0; k <= j; ++k) col[k] = ls->ht[k];
-            col[j + 1] = nu;
-            apply_rotations(ls->cs, ls->sn, col, j);
-            const double rho = hypot(col[j], col[j + 1]);
-            if (!isfinite(rho) || !isfinite(nu)) {
-                ls->status = GS2_ERR_NONFINITE;
-                ls->done = 1;
-                ls->kk = j;
-            } else {
-                const double est = rho > 0.0 ? fabs(col[j + 1] / rho * ls->g[j]) : 0.0;
-                const bool breakdown = nu <= 1e-14 * sqrt(ls->wn2);
-                ls->kk = j + 1;
-                if (est <= ls->rtol * ls->bnorm || breakdown || j + 1 >= ls->maxsteps) {
-                    for (int k = 0; k <= j; ++k) col[k] = ls->ht[k];
-                    col[j + 1] = nu;
-                    if (!commit_column(ls, st->H, col, j)) ls->kk = j;
-                    ls->done = 1;
-                } else {
-                    ls->inv = 1.0 / nu;
-                    ls->zs[j + 1] = 1.0 / nu;
-                    ls->j = j + 1;
-                }
-            }
-        }
-    }
+    // (tot is valid in thread 0 only)
+    if (t < WAVE) dcgs_finish_wave(ls, st->H, MAXM, col, ok, alpha, e, a2, read_lane(tot, 0));
     __syncthreads();
     unsigned long long *gwo = reinterpret_cast<unsigned long long *>(st);
     for (int k = t; k < GSTATE_SMALL_WORDS; k += KT) gwo[k] = sw[k];

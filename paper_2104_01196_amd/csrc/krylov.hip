@@ -20,6 +20,7 @@
 
 #include "dcgs_state.hpp"
 #include "gs2_internal.hpp"
+#include "resident.hpp"
 #include "sella.hpp"
 
 namespace gs2 {
@@ -57,6 +58,11 @@ struct GmresWork {
     double *V = nullptr, *Z = nullptr, *w = nullptr, *w2 = nullptr, *part = nullptr;
     GState *st = nullptr;
     PatternDev *pat = nullptr;
+    // one-launch solves (resident.hip) of small systems: exchanged vectors and
+    // partial sums, barrier words, and the record they leave (pinned host)
+    double *rex = nullptr, *rpart = nullptr;
+    unsigned *rbar = nullptr;
+    ResInfo *rinfo = nullptr;
     GHeader *hdr = nullptr; // pinned host copy
     // HIP graph of one restart cycle (captured on its own stream, launched on the caller's)
     hipStream_t cap = nullptr;
@@ -102,6 +108,7 @@ void free_gmres_work(GmresWork *g)
     sella_free(g->A);
     if (g->mem) (void)hipFree(g->mem);
     if (g->hdr) (void)hipHostFree(g->hdr);
+    if (g->rinfo) (void)hipHostFree(g->rinfo);
     delete g;
 }
 
@@ -128,10 +135,19 @@ static int alloc_work(GmresWork **out, int64_t n, int m)
         at(g->part, sizeof(double) * (size_t)g->nb * (2 * MAXM + 3)); // delayed CGS2: 2j+3 per block
         at(g->st, sizeof(GState));
         at(g->pat, pattern_dev_bytes());
+        if (n <= RES_MAX_N) {
+            at(g->rex, sizeof(double) * 3 * N);
+            at(g->rpart, sizeof(double) * RES_MAX_GROUPS * (2 * RES_MAX_M + 4));
+            at(g->rbar, sizeof(unsigned) * 4);
+        }
     };
     place(nullptr);
     if (hipMalloc(&g->mem, total) != hipSuccess) st = GS2_ERR_NOMEM;
     else place(g->mem);
+    if (st == GS2_OK && g->rbar &&
+        (hipMemset(g->rbar, 0, sizeof(unsigned) * 4) != hipSuccess ||
+         hipHostMalloc((void **)&g->rinfo, sizeof(ResInfo), hipHostMallocDefault) != hipSuccess))
+        st = GS2_ERR_NOMEM;
     if (st == GS2_OK && hipHostMalloc((void **)&g->hdr, sizeof(GHeader), hipHostMallocDefault) != hipSuccess)
         st = GS2_ERR_NOMEM;
     if (st != GS2_OK) {
@@ -198,10 +214,10 @@ __device__ __forceinline__ void block_multidot(int64_t n, int64_t r0, const doub
         for (int s = 0; s < QR; ++s) {
             const int i = ln + (wv * QR + s) * WAVE;
             const double a = al[i], b = TWO ? bl[i] : 0.0;
-            aa += a * a;
+            aa = fma(a, a, aa);
             if (TWO) {
-                ab += a * b;
-                bb += b * b;
+                ab = fma(a, b, ab);
+                bb = fma(b, b, bb);
             }
         }
         aa = wave_sum(aa);
@@ -287,7 +303,7 @@ __global__ __launch_bounds__(KT) void k_true_resid(SellAView A, DiaAView D, int6
         if (row < n) {
             const double r = b[row] - wl[i];
             out[row] = r;
-            s += r * r;
+            s = fma(r, r, s);
         }
     }
     s = block_sum(s, red);
@@ -302,7 +318,7 @@ __global__ __launch_bounds__(KT) void k_norm_part(int64_t n, const double *__res
     double s = 0.0;
     for (int u = 0; u < RB / KT; ++u) {
         const int64_t row = r0 + threadIdx.x + u * KT;
-        if (row < n) s += b[row] * b[row];
+        if (row < n) s = fma(b[row], b[row], s);
     }
     s = block_sum(s, red);
     if (threadIdx.x == 0) part[blockIdx.x] = s;
@@ -699,7 +715,7 @@ __global__ __launch_bounds__(KT) void k_dcgs_update(int64_t n, double *__restric
         const double wp = aw[q] - e * qv;
         u[row] = qv;
         wn[row] = wp;
-        s += wp * wp;
+        s = fma(wp, wp, s);
     }
     s = block_sum(s, red);
     if (t == 0) part[blockIdx.x] = s;
@@ -1178,6 +1194,80 @@ static int prepare_matrix(GmresWork *W, const gs2_csr &A, int fmt, hipStream_t s
     return GS2_OK;
 }
 
+// Lanes per row whose sums the handle's passes add.
+static int sum_lanes(const Handle &h) { return h.fmt == FMT_DIA ? 1 : h.L.K; }
+
+// Whether a solve runs in one launch (resident.hip): small, unpreconditioned
+// or preconditioned by GS2 or JR on one block, default orthogonalisation, rows
+// short enough for a thread each, no choice of the launches' schedules asked
+// for and no per-kernel timing.  Either way gives the same bits.
+static bool resident_fits(const GmresWork *W, const gs2_handle *P, int m, int kind)
+{
+    return P && W->rbar && m <= RES_MAX_M && P->h.orth == 0 && P->h.blocks == 1 && W->A.sel == 1 &&
+           sum_lanes(P->h) <= RES_MAX_LANES &&
+           P->h.spmv_fmt == GS2_FORMAT_AUTO && P->h.basis_req == 0 && !prof_on() &&
+           (kind == GS2_PREC_NONE || kind == GS2_PREC_GS2 || kind == GS2_PREC_JR);
+}
+
+static ResSell res_view(int64_t *sp, const int32_t *col, const void *val, int K)
+{
+    int lk = 0;
+    while ((1 << lk) < K) ++lk;
+    return ResSell{sp, col, val, lk};
+}
+
+// The solve in one launch; *given_up when its workgroups could not meet.
+static int resident_solve(GmresWork *W, const double *b, double *x, int m, double rtol, int maxit, int kind,
+                          gs2_handle *P, gs2_solve_info *info, hipStream_t s, bool *given_up)
+{
+    const Handle &h = P->h;
+    const size_t N = (size_t)h.n;
+    ResArgs a{};
+    a.n = (int)h.n;
+    a.G = W->nb;
+    a.m = m;
+    a.maxit = maxit;
+    a.stag = h.stag_cycles == 0 ? 50 : h.stag_cycles;
+    a.kind = kind;
+    a.sweeps = h.sweeps;
+    a.inner = h.inner;
+    a.variant = h.variant;
+    a.compact = h.compact;
+    a.rtol = rtol;
+    a.omega = h.omega;
+    a.gamma = h.gamma;
+    a.L = res_view(h.L.slice_ptr, h.L.col, h.L.val, h.L.K);
+    a.U = res_view(h.U.slice_ptr, h.U.col, h.U.val, h.U.K);
+    a.A = res_view(W->A.sp, W->A.col, W->A.val, W->A.K);
+    a.sl = h.sl;
+    a.sr = h.sr;
+    a.b = b;
+    a.x = x;
+    a.V = W->V;
+    a.Z = W->Z;
+    a.se = W->rex;
+    a.ze = W->rex + N;
+    a.xe = W->rex + 2 * N;
+    a.part = W->rpart;
+    a.xh = h.xh;
+    a.xh2 = h.xh2;
+    a.rh = h.rh;
+    a.ga = h.ga;
+    a.gb = h.gb;
+    a.bar = W->rbar;
+    a.info = W->rinfo;
+    GS2_TRY(resident_launch(h.precision, sum_lanes(h), a, s));
+    GS2_TRY_HIP(hipStreamSynchronize(s));
+    const ResInfo r = *W->rinfo;
+    *given_up = r.status == RES_GIVEN_UP;
+    if (*given_up) return GS2_OK;
+    info->iterations = r.iterations;
+    info->restarts = r.restarts;
+    info->relres = r.relres;
+    info->converged = r.converged;
+    return r.status;
+}
+
 static int gmres_impl(const gs2_csr &A, const double *b, double *x, int m, double rtol, int maxit, int kind,
                       gs2_handle *P, gs2_solve_info *info, hipStream_t s)
 {
@@ -1205,6 +1295,11 @@ static int gmres_impl(const gs2_csr &A, const double *b, double *x, int m, doubl
     const unsigned gE = (unsigned)((n + 255) / 256);
     GS2_TRY(prepare_matrix(W, A, P ? P->h.spmv_fmt : GS2_FORMAT_AUTO, s));
     GS2_TRY(tune_basis(W, P ? P->h.basis_req : 0, s));
+    if (resident_fits(W, P, m, kind)) {
+        bool given_up = false;
+        const int st = resident_solve(W, b, x, m, rtol, maxit, kind, P, info, s, &given_up);
+        if (!given_up) return st;
+    }
     const SellAView AS = view(W->A);
     const DiaAView AD = dview(W->A);
     const int K = W->A.sel;
@@ -1291,8 +1386,10 @@ static int gmres_impl(const gs2_csr &A, const double *b, double *x, int m, doubl
         // a GS2 or JR pass: it needs only step j's partial sums and the state,
         // and the pass needs neither.  The last step's runs alone.
         const bool fuse_fin = orth == 0 && P && (kind == GS2_PREC_GS2 || kind == GS2_PREC_JR);
-        // the second basis pass loads pairs of rows when every column is 16-byte aligned
-        const bool pairs = n % 2 == 0;
+        // the second basis pass loads pairs of rows when every column is
+        // 16-byte aligned; below the size solved in one launch it keeps that
+        // launch's order of summation
+        const bool pairs = n % 2 == 0 && n > RES_MAX_N;
         const int nbu = pairs ? (int)((n + 2 * UPD_PAIRS * KT - 1) / (2 * UPD_PAIRS * KT)) : nb;
         auto enqueue_cycle = [&](hipStream_t cs) -> int {
             k_cycle_init<<<1, 64, 0, cs>>>(st, steps, rtol);

@@ -209,7 +209,9 @@ __global__ __launch_bounds__(256) void k_resid(const int *__restrict__ stop, int
         const AT a = K > 1 ? group_sum<K>(acc[u]) : acc[u];
         const int64_t row = (s0 + u) * (WAVE / K) + lane / K;
         if ((K > 1 && (lane & (K - 1))) || row >= n) continue;
-        const AT r = ((AT)(v[row] * sl[row]) - cdiag * xh[row]) - a;
+        // (the fused operation written out: S_l v is rounded by itself, as
+        // where it is formed once per apply)
+        const AT r = fma(-cdiag, xh[row], (AT)(v[row] * sl[row])) - a;
         finish<AT>(dst, row, r, w, rh, const_cast<AT *>(xh), xout, z, sr);
     }
 }
