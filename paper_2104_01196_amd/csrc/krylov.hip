@@ -69,8 +69,7 @@ struct GmresWork {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     CycleKey key;
-    SellA A;         // the solver's copy of the system matrix
-    int fmt_req = -1; // the layout request it was built for
+    Product prod;    // the solver's copy of the system matrix
     // Arnoldi steps from which the delayed passes keep fewer loads in flight
     // (INT_MAX: never), timed once per workspace (tune_basis); basis_tuned 1
     // decided there, 2 forced by the handle's request
@@ -105,7 +104,7 @@ void free_gmres_work(GmresWork *g)
     if (g->exec) (void)hipGraphExecDestroy(g->exec);
     if (g->graph) (void)hipGraphDestroy(g->graph);
     if (g->cap) (void)hipStreamDestroy(g->cap);
-    sella_free(g->A);
+    sella_free(g->prod.A);
     if (g->mem) (void)hipFree(g->mem);
     if (g->hdr) (void)hipHostFree(g->hdr);
     if (g->rinfo) (void)hipHostFree(g->rinfo);
@@ -528,11 +527,17 @@ __global__ __launch_bounds__(KT) void k_spmv_dot2(SellAView A, DiaAView D, int64
 // outputs (196.3 against 197.3 ms per 192^3 solve).  Every launched wavefront loads in bounds (the copy is padded to
 // 1024-row workgroups and a clamped column only meets a stored zero); rows
 // past n are not written.
-template <int R, int ND>
+//
+// DOT (conjugate gradients): w = A z with the workgroup's sum of w.z in
+// part[blockIdx.x]; stop, when set, ends the launch.
+template <int R, int ND, bool DOT = false>
 __global__ __launch_bounds__(KT) void k_dia_spmv(DiaAView A, int64_t n, const double *__restrict__ z,
-                                                 double *__restrict__ w, const GState *__restrict__ st)
+                                                 double *__restrict__ w, const GState *__restrict__ st,
+                                                 const int *__restrict__ stop = nullptr,
+                                                 double *__restrict__ part = nullptr)
 {
     using V2 = double __attribute__((ext_vector_type(2)));
+    if (DOT && stop && *stop) return;
     if (st && st->done) return;
     const double zsc = st ? st->zs[st->j] : 1.0;
     const int wv = threadIdx.x / WAVE, ln = threadIdx.x & (WAVE - 1);
@@ -568,6 +573,17 @@ __global__ __launch_bounds__(KT) void k_dia_spmv(DiaAView A, int64_t n, const do
         const int64_t row = base + k * WAVE + ln;
         if (row < n) __builtin_nontemporal_store(zsc * acc[k], &w[row]);
     }
+    if constexpr (DOT) {
+        __shared__ double red[KT / WAVE];
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const int64_t row = base + k * WAVE + ln;
+            if (row < n) s += acc[k] * z[row];
+        }
+        s = block_sum(s, red);
+        if (threadIdx.x == 0) part[blockIdx.x] = s;
+    }
 }
 
 // w = zs[j] (A z) from the 3-row block copy (node-major planes), a lane
@@ -576,10 +592,14 @@ __global__ __launch_bounds__(KT) void k_dia_spmv(DiaAView A, int64_t n, const do
 // coalesced loads), forming its three rows' sums in the order b3_rows uses.
 // The planes are padded to whole 1024-node groups, so every load is in
 // bounds; nodes past n/3 are not written.
-template <int NB>
+// DOT as in k_dia_spmv.
+template <int NB, bool DOT = false>
 __global__ __launch_bounds__(KT) void k_b3_spmv(DiaAView A, int64_t n, const double *__restrict__ z,
-                                                double *__restrict__ w, const GState *__restrict__ st)
+                                                double *__restrict__ w, const GState *__restrict__ st,
+                                                const int *__restrict__ stop = nullptr,
+                                                double *__restrict__ part = nullptr)
 {
+    if (DOT && stop && *stop) return;
     if (st && st->done) return;
     const double zsc = st ? st->zs[st->j] : 1.0;
     const int wv = threadIdx.x / WAVE, ln = threadIdx.x & (WAVE - 1);
@@ -620,6 +640,40 @@ __global__ __launch_bounds__(KT) void k_b3_spmv(DiaAView A, int64_t n, const dou
 #pragma unroll
             for (int k = 0; k < 3; ++k) __builtin_nontemporal_store(zsc * acc[b][k], &w[3 * i + k]);
     }
+    if constexpr (DOT) {
+        __shared__ double red[KT / WAVE];
+        double s = 0.0;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int64_t i = g0 + b * WAVE + ln;
+            if (i < nn)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) s += acc[b][k] * z[3 * i + k];
+        }
+        s = block_sum(s, red);
+        if (threadIdx.x == 0) part[blockIdx.x] = s;
+    }
+}
+
+// w = A z on sliced ELL with the workgroup's sum of w.z in part[blockIdx.x].
+template <int SEL>
+__global__ __launch_bounds__(KT) void k_sell_spmv_dot(SellAView A, DiaAView D, int64_t n, const double *__restrict__ z,
+                                                      double *__restrict__ w, const int *__restrict__ stop,
+                                                      double *__restrict__ part)
+{
+    __shared__ double wl[RB];
+    __shared__ double red[KT / WAVE];
+    if (stop && *stop) return;
+    const int64_t r0 = (int64_t)blockIdx.x * RB;
+    mat_rows<SEL, KT / WAVE>(A, D, n, r0, z, wl);
+    double s = 0.0;
+    for (int i = threadIdx.x; i < RB; i += KT)
+        if (r0 + i < n) {
+            w[r0 + i] = wl[i];
+            s += wl[i] * z[r0 + i];
+        }
+    s = block_sum(s, red);
+    if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
 template <int G>
@@ -1080,16 +1134,16 @@ static int tune_basis(GmresWork *W, int req, hipStream_t s)
 // Time of one product in the layout sel (best of three batches of five
 // launches after a warm-up batch; timing-only events): w2 = b - A w, or for
 // the block copy the kernel the solver's steps use, w2 = A w.
-static int time_product(GmresWork *W, int sel, hipStream_t s, float *ms)
+static int time_product(const Product &W, int sel, hipStream_t s, float *ms)
 {
-    const int64_t n = W->n;
-    const int nb = W->nb;
-    const SellAView AS = view(W->A);
-    const DiaAView AD = dview(W->A);
+    const int64_t n = W.A.n;
+    const int nb = (int)((n + RB - 1) / RB);
+    const SellAView AS = view(W.A);
+    const DiaAView AD = dview(W.A);
     hipEvent_t e0, e1;
     GS2_TRY_HIP(hipEventCreateWithFlags(&e0, hipEventDisableSystemFence));
     GS2_TRY_HIP(hipEventCreateWithFlags(&e1, hipEventDisableSystemFence));
-    k_zero64<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n, W->w);
+    k_zero64<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n, W.in);
     float best = 1e30f;
     for (int rep = 0; rep < 4; ++rep) {
         GS2_TRY_HIP(hipEventRecord(e0, s));
@@ -1097,10 +1151,10 @@ static int time_product(GmresWork *W, int sel, hipStream_t s, float *ms)
             if (sel <= -10) {
                 const int R = -sel - 10;
                 const unsigned gD = (unsigned)((n / 3 + (int64_t)KT * R - 1) / ((int64_t)KT * R));
-                if (R == 2) k_b3_spmv<2><<<gD, KT, 0, s>>>(AD, n, W->w, W->w2, nullptr);
-                else k_b3_spmv<1><<<gD, KT, 0, s>>>(AD, n, W->w, W->w2, nullptr);
+                if (R == 2) k_b3_spmv<2><<<gD, KT, 0, s>>>(AD, n, W.in, W.out, nullptr);
+                else k_b3_spmv<1><<<gD, KT, 0, s>>>(AD, n, W.in, W.out, nullptr);
             } else {
-                GS2_SPMV_DISPATCH(sel, k_true_resid, (unsigned)nb, AS, AD, n, W->w, W->w, W->w2, W->part, nb);
+                GS2_SPMV_DISPATCH(sel, k_true_resid, (unsigned)nb, AS, AD, n, W.in, W.in, W.out, W.part, nb);
             }
         }
         GS2_TRY_HIP(hipEventRecord(e1, s));
@@ -1115,16 +1169,17 @@ static int time_product(GmresWork *W, int sel, hipStream_t s, float *ms)
     return GS2_OK;
 }
 
-static int build_layout(SellA &S, const gs2_csr &A, int sel, const std::vector<int> &offs, hipStream_t s)
+static int build_layout(SellA &S, const gs2_csr &A, int sel, const std::vector<int> &offs, int *flag,
+                        hipStream_t s)
 {
     if (sel > 0) return sella_build_sell(S, A, sel, s);
     if (sel <= -10) GS2_TRY(sella_build_b3(S, A, -sel - 10, offs, s));
     else GS2_TRY(sella_build_dia(S, A, -sel, offs, s));
-    return sella_fill_values(S, A, false, s);
+    return sella_fill_values(S, A, false, s, flag);
 }
 
 // The layout of the solver's copy of A, chosen once per CSR pattern (keyed
-// by its row-pointer and column arrays and sizes) and kept with the
+// by its row-pointer and column arrays and sizes, or compared) and kept with the
 // workspace; the values are copied again at every solve, so values changed
 // in place between solves are honoured.  Candidates: sliced ELL at the
 // lanes per row the mean row length suggests and at twice that, and, when
@@ -1136,16 +1191,17 @@ static int build_layout(SellA &S, const gs2_csr &A, int sel, const std::vector<i
 // schedules); GS2_FORMAT_SELL / _DIA / _BLOCK3 force a layout
 // (the diagonal one at two rows per lane, the block one at two nodes per
 // lane, falling back to sliced ELL when A does not qualify).
-static int prepare_matrix(GmresWork *W, const gs2_csr &A, int fmt, hipStream_t s)
+int prepare_product(Product &W, const gs2_csr &A, int fmt, hipStream_t s, int *flag)
 {
-    SellA &S = W->A;
-    if (S.rp == A.rowptr && S.ci == A.colind && S.n == A.n && S.nnz == A.nnz && (S.val || S.dval) &&
-        W->fmt_req == fmt)
-        return sella_fill_values(S, A, false, s);
+    SellA &S = W.A;
+    if ((flag || (S.rp == A.rowptr && S.ci == A.colind)) && S.n == A.n && S.nnz == A.nnz && (S.val || S.dval) &&
+        W.fmt_req == fmt)
+        return sella_fill_values(S, A, false, s, flag);
     sella_free(S);
+    W.fmt_req = -1;
     std::vector<int> offs;
     Pattern pat;
-    if (fmt != GS2_FORMAT_SELL) GS2_TRY(scan_pattern(A, nullptr, nullptr, nullptr, nullptr, W->pat, pat, s));
+    if (fmt != GS2_FORMAT_SELL) GS2_TRY(scan_pattern(A, nullptr, nullptr, nullptr, nullptr, W.pat, pat, s));
     const bool dia_ok = fmt != GS2_FORMAT_SELL && fmt != GS2_FORMAT_BLOCK3 && sella_dia_offsets(A, pat, offs);
     const bool b3_ok = !dia_ok && fmt != GS2_FORMAT_SELL && fmt != GS2_FORMAT_DIA && sella_b3_offsets(A, pat, offs);
     const int K0 = sella_rule_lanes(A);
@@ -1172,7 +1228,7 @@ static int prepare_matrix(GmresWork *W, const gs2_csr &A, int fmt, hipStream_t s
         float best = 1e30f;
         std::vector<int> timed;
         for (int c : cands) {
-            GS2_TRY(build_layout(S, A, c, offs, s));
+            GS2_TRY(build_layout(S, A, c, offs, flag, s));
             // the padding rule may widen a sliced-ELL candidate to one already timed
             if (std::find(timed.begin(), timed.end(), S.sel) != timed.end()) continue;
             timed.push_back(S.sel);
@@ -1186,12 +1242,42 @@ static int prepare_matrix(GmresWork *W, const gs2_csr &A, int fmt, hipStream_t s
         tuned = 1;
         choice_put(key, sel);
     }
-    if (S.sel != sel || !(S.val || S.dval)) GS2_TRY(build_layout(S, A, sel, offs, s));
+    if (S.sel != sel || !(S.val || S.dval)) GS2_TRY(build_layout(S, A, sel, offs, flag, s));
     S.tuned = tuned;
     S.rp = A.rowptr; // complete: key it
     S.ci = A.colind;
-    W->fmt_req = fmt;
+    W.fmt_req = fmt;
     return GS2_OK;
+}
+
+int product_dot(const Product &W, const double *z, double *w, const int *stop, double *part, hipStream_t s)
+{
+    const int64_t n = W.A.n;
+    const SellAView AS = view(W.A);
+    const DiaAView AD = dview(W.A);
+    const int K = W.A.sel, R = K <= -10 ? -K - 10 : K < 0 ? -K : 1;
+    const int64_t units = K <= -10 ? n / 3 : n; // nodes or rows
+    const unsigned gD = (unsigned)((units + (int64_t)KT * R - 1) / ((int64_t)KT * R));
+    if (K == -12) k_b3_spmv<2, true><<<gD, KT, 0, s>>>(AD, n, z, w, nullptr, stop, part);
+    else if (K == -11) k_b3_spmv<1, true><<<gD, KT, 0, s>>>(AD, n, z, w, nullptr, stop, part);
+    else if (K == -2 && AD.ndiag == 7) k_dia_spmv<2, 7, true><<<gD, KT, 0, s>>>(AD, n, z, w, nullptr, stop, part);
+    else if (K == -1 && AD.ndiag == 7) k_dia_spmv<1, 7, true><<<gD, KT, 0, s>>>(AD, n, z, w, nullptr, stop, part);
+    else if (K == -2) k_dia_spmv<2, 0, true><<<gD, KT, 0, s>>>(AD, n, z, w, nullptr, stop, part);
+    else if (K == -1) k_dia_spmv<1, 0, true><<<gD, KT, 0, s>>>(AD, n, z, w, nullptr, stop, part);
+    else {
+        const unsigned g = (unsigned)((n + RB - 1) / RB);
+        GS2_SPMV_DISPATCH(K, k_sell_spmv_dot, g, AS, AD, n, z, w, stop, part);
+        return (int)g;
+    }
+    return (int)gD;
+}
+
+int product_resid(const Product &W, const double *x, const double *b, double *r, double *part, hipStream_t s)
+{
+    const int64_t n = W.A.n;
+    const int nb = (int)((n + RB - 1) / RB);
+    GS2_SPMV_DISPATCH(W.A.sel, k_true_resid, (unsigned)nb, view(W.A), dview(W.A), n, x, b, r, part, nb);
+    return nb;
 }
 
 // Lanes per row whose sums the handle's passes add.
@@ -1203,7 +1289,7 @@ static int sum_lanes(const Handle &h) { return h.fmt == FMT_DIA ? 1 : h.L.K; }
 // for and no per-kernel timing.  Either way gives the same bits.
 static bool resident_fits(const GmresWork *W, const gs2_handle *P, int m, int kind)
 {
-    return P && W->rbar && m <= RES_MAX_M && P->h.orth == 0 && P->h.blocks == 1 && W->A.sel == 1 &&
+    return P && W->rbar && m <= RES_MAX_M && P->h.orth == 0 && P->h.blocks == 1 && W->prod.A.sel == 1 &&
            sum_lanes(P->h) <= RES_MAX_LANES &&
            P->h.spmv_fmt == GS2_FORMAT_AUTO && P->h.basis_req == 0 && !prof_on() &&
            (kind == GS2_PREC_NONE || kind == GS2_PREC_GS2 || kind == GS2_PREC_JR);
@@ -1238,7 +1324,7 @@ static int resident_solve(GmresWork *W, const double *b, double *x, int m, doubl
     a.gamma = h.gamma;
     a.L = res_view(h.L.slice_ptr, h.L.col, h.L.val, h.L.K);
     a.U = res_view(h.U.slice_ptr, h.U.col, h.U.val, h.U.K);
-    a.A = res_view(W->A.sp, W->A.col, W->A.val, W->A.K);
+    a.A = res_view(W->prod.A.sp, W->prod.A.col, W->prod.A.val, W->prod.A.K);
     a.sl = h.sl;
     a.sr = h.sr;
     a.b = b;
@@ -1293,16 +1379,20 @@ static int gmres_impl(const gs2_csr &A, const double *b, double *x, int m, doubl
     const int nb = W->nb;
     const unsigned gN = (unsigned)nb;
     const unsigned gE = (unsigned)((n + 255) / 256);
-    GS2_TRY(prepare_matrix(W, A, P ? P->h.spmv_fmt : GS2_FORMAT_AUTO, s));
+    W->prod.in = W->w;
+    W->prod.out = W->w2;
+    W->prod.part = W->part;
+    W->prod.pat = W->pat;
+    GS2_TRY(prepare_product(W->prod, A, P ? P->h.spmv_fmt : GS2_FORMAT_AUTO, s));
     GS2_TRY(tune_basis(W, P ? P->h.basis_req : 0, s));
     if (resident_fits(W, P, m, kind)) {
         bool given_up = false;
         const int st = resident_solve(W, b, x, m, rtol, maxit, kind, P, info, s, &given_up);
         if (!given_up) return st;
     }
-    const SellAView AS = view(W->A);
-    const DiaAView AD = dview(W->A);
-    const int K = W->A.sel;
+    const SellAView AS = view(W->prod.A);
+    const DiaAView AD = dview(W->prod.A);
+    const int K = W->prod.A.sel;
     GState *st = W->st;
     GHeader *hdr = W->hdr;
     if (P) P->h.stop = &st->done;
@@ -1346,7 +1436,7 @@ static int gmres_impl(const gs2_csr &A, const double *b, double *x, int m, doubl
     int ref_cycle = 0;
     // algorithmic bytes: SpMV with A (entries, slice pointers, z gathered once,
     // w written), and one pass over nk Krylov vectors
-    const double spmv_b = sella_bytes(W->A);
+    const double spmv_b = sella_bytes(W->prod.A);
     const double red_b = 8.0 * nb;
     for (;;) {
         prof_set_step(cycles, -1);
@@ -1502,7 +1592,7 @@ static int gmres_impl(const gs2_csr &A, const double *b, double *x, int m, doubl
         // and parameters (with a handle: its work space outlives the call).
         // Per-kernel event profiling needs the launches one by one.
         if (P && g_graphs.load() && !prof_on()) {
-            const CycleKey key{A.rowptr, A.colind, A.val, b, x, P, W->A.sel < 0 ? (const void *)W->A.dval : W->A.val,
+            const CycleKey key{A.rowptr, A.colind, A.val, b, x, P, W->prod.A.sel < 0 ? (const void *)W->prod.A.dval : W->prod.A.val,
                                kind, m, steps, rtol, orth};
             if (!(W->exec && W->key == key)) GS2_TRY(capture_cycle(W, key, enqueue_cycle));
             GS2_TRY_HIP(hipGraphLaunch(W->exec, s));
@@ -1527,13 +1617,13 @@ extern "C" int gs2_gmres_schedule(const gs2_handle *H, int *format, int *lanes_p
 {
     if (!H) return GS2_ERR_ARG;
     const GmresWork *W = H->h.gw;
-    const bool built = W && (W->A.val || W->A.dval);
-    const int sel = built ? W->A.sel : 0;
+    const bool built = W && (W->prod.A.val || W->prod.A.dval);
+    const int sel = built ? W->prod.A.sel : 0;
     if (format) *format = !built ? 0 : sel <= -10 ? GS2_FORMAT_BLOCK3 : sel < 0 ? GS2_FORMAT_DIA : GS2_FORMAT_SELL;
     if (lanes_per_row) *lanes_per_row = sel > 0 ? sel : 0;
     if (rows_per_lane) *rows_per_lane = sel <= -10 ? -sel - 10 : sel < 0 ? -sel : 0;
-    if (ndiag) *ndiag = sel < 0 ? W->A.ndiag : 0;
-    if (tuned) *tuned = built ? W->A.tuned : 0;
+    if (ndiag) *ndiag = sel < 0 ? W->prod.A.ndiag : 0;
+    if (tuned) *tuned = built ? W->prod.A.tuned : 0;
     return GS2_OK;
 }
 

@@ -27,11 +27,12 @@ __global__ void k_sella_len(int64_t n, int64_t nslices, int K, const int32_t *__
 }
 
 // One thread per (slice, lane): lane l = r*K + q holds entries t*K + q of
-// row r at step t; padding is (own column, 0).  Columns only when with_col.
+// row r at step t; padding is (own column, 0).  Columns are written when
+// with_col, else compared when flag is set (FILL_CHANGED).
 __global__ void k_sella_fill(int64_t n, int64_t nslices, int K, const int32_t *__restrict__ rp,
                              const int32_t *__restrict__ ci, const double *__restrict__ va,
                              const int64_t *__restrict__ sp, int with_col, int32_t *__restrict__ col,
-                             double *__restrict__ val)
+                             double *__restrict__ val, int *__restrict__ flag)
 {
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t s = gid / WAVE;
@@ -43,13 +44,16 @@ __global__ void k_sella_fill(int64_t n, int64_t nslices, int K, const int32_t *_
     const int64_t b = row < n ? rp[row] : 0;
     const int len = row < n ? rp[row + 1] - rp[row] : 0;
     const int32_t pad = (int32_t)(row < n ? row : n - 1);
+    bool changed = len > steps * K;
     for (int t = 0; t < steps; ++t) {
         const int e = t * K + q;
         const int64_t pos = beg + (int64_t)t * WAVE + l;
         const bool real = e < len;
         if (with_col) col[pos] = real ? ci[b + e] : pad;
+        else if (flag && real && col[pos] != ci[b + e]) changed = true;
         val[pos] = real ? va[b + e] : 0.0;
     }
+    if (flag && changed) atomicOr(flag, FILL_CHANGED);
 }
 
 void sella_free(SellA &S)
@@ -64,47 +68,72 @@ struct DiaOffsA {
     int off[DIA_MAX];
 };
 
-// Values of the diagonal (B3 = false) or 3-row block (B3 = true) copy, LANES
-// threads per row, each taking every LANES-th entry of the row: entry (i, c)
-// goes to diagonal t (the index of c - i among the offsets) at row i's
+// Values of the diagonal (B3 = false) or 3-row block (B3 = true) copy: entry
+// (i, c) goes to diagonal t (the index of c - i among the offsets) at row i's
 // position (interleaved by R rows per lane), or to plane
 // 9 t + 3 (i mod 3) + (c mod 3) (t the index of the node offset c/3 - i/3)
-// at node i/3's position.  The offsets are found by binary search in
-// an LDS copy.  Entries of rows past n and absent entries keep the zeros
-// written at allocation.  This runs at every solve (the values may have
-// changed in place): one thread per row walking its entries took 2.3 ms per
-// solve on the 64^3 elasticity matrix.
-template <int LANES, bool B3>
-__global__ __launch_bounds__(256) void k_copy_fill(int64_t n, int R, const int32_t *__restrict__ rp,
-                                                   const int32_t *__restrict__ ci, const double *__restrict__ va,
-                                                   DiaOffsA o, int64_t stride, double *__restrict__ val)
+// at node i/3's position.  A workgroup forms its tile, FILL_ROWS rows or
+// FILL_NODES nodes of every plane, in LDS and writes it whole, absent entries
+// as zeros, in stores of full 128-byte lines.  This runs at every solve (the
+// values may have changed in place); bound by the copy's bytes.  Storing each
+// entry on its own, 8 bytes to as many planes as a row has entries, took
+// 1.46 ms per solve on the 64^3 elasticity matrix (27 node offsets), this 0.52.
+// flag: FILL_CHANGED where an entry has no place in the layout,
+// FILL_UNSORTED where a row's columns do not increase.
+constexpr int FILL_ROWS = 128, FILL_NODES = 16, FILL_TB = 256;
+
+template <bool B3>
+__global__ __launch_bounds__(FILL_TB) void k_copy_fill(int64_t n, int R, const int32_t *__restrict__ rp,
+                                                       const int32_t *__restrict__ ci,
+                                                       const double *__restrict__ va, DiaOffsA o, int64_t stride,
+                                                       double *__restrict__ val, int *__restrict__ flag)
 {
+    constexpr int T = B3 ? FILL_NODES : FILL_ROWS, ROWS = B3 ? 3 * T : T, LANES = B3 ? 16 : 8;
+    constexpr int LD = T + 1; // an odd leading dimension: a row's entries fall into different banks
+    extern __shared__ double tile[];
     __shared__ int soff[DIA_MAX];
     if (threadIdx.x == 0) {
 #pragma unroll
         for (int d = 0; d < DIA_MAX; ++d) soff[d] = o.off[d];
     }
+    const int planes = B3 ? 9 * o.nd : o.nd;
+    for (int k = threadIdx.x; k < planes * LD; k += FILL_TB) tile[k] = 0.0;
     __syncthreads();
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t i = g / LANES;
-    if (i >= n) return;
-    int64_t pos = i / 3;
-    if constexpr (!B3) {
-        const int64_t blk = (int64_t)WAVE * R;
-        pos = (i / blk) * blk + (i % WAVE) * R + (i % blk) / WAVE;
-    }
-    for (int32_t k = rp[i] + (int32_t)(g % LANES); k < rp[i + 1]; k += LANES) {
-        const int64_t c = ci[k];
-        const int d = B3 ? (int)(c / 3 - i / 3) : (int)(c - i);
-        int lo = 0, hi = o.nd - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (soff[mid] < d) lo = mid + 1;
-            else hi = mid;
+    const int32_t i0 = (int32_t)blockIdx.x * ROWS;
+    int bad = 0;
+    for (int l = threadIdx.x / LANES; l < ROWS; l += FILL_TB / LANES) {
+        const int32_t i = i0 + l;
+        if (i >= n) break;
+        int pos = l / 3;
+        if constexpr (!B3) {
+            const int blk = WAVE * R;
+            pos = (l / blk) * blk + (l % WAVE) * R + (l % blk) / WAVE;
         }
-        if (soff[lo] == d)
-            val[(int64_t)(B3 ? 9 * lo + 3 * (int)(i - 3 * (i / 3)) + (int)(c - 3 * (c / 3)) : lo) * stride + pos] = va[k];
+        const int32_t b = rp[i], e = rp[i + 1], node = i / 3;
+        for (int32_t k = b + (int32_t)(threadIdx.x % LANES); k < e; k += LANES) {
+            const int32_t c = ci[k];
+            if (k > b && ci[k - 1] >= c) bad |= FILL_UNSORTED;
+            const int32_t d = B3 ? c / 3 - node : c - i;
+            // where a row has an entry for every offset before c's, the
+            // entry's number tells the offset's; else a binary search
+            int lo = min(B3 ? (k - b) / 3 : k - b, o.nd - 1);
+            if (soff[lo] != d) {
+                int hi = o.nd - 1;
+                lo = 0;
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (soff[mid] < d) lo = mid + 1;
+                    else hi = mid;
+                }
+            }
+            if (soff[lo] != d) bad |= FILL_CHANGED;
+            else tile[(B3 ? 9 * lo + 3 * (i - 3 * node) + (c - 3 * (c / 3)) : lo) * LD + pos] = va[k];
+        }
     }
+    if (flag && bad) atomicOr(flag, bad);
+    __syncthreads();
+    double *out = val + (int64_t)blockIdx.x * T;
+    for (int k = threadIdx.x; k < planes * T; k += FILL_TB) out[(int64_t)(k / T) * stride + k % T] = tile[(k / T) * LD + k % T];
 }
 
 int sella_build_dia(SellA &S, const gs2_csr &A, int R, const std::vector<int> &offs, hipStream_t s)
@@ -142,31 +171,29 @@ int sella_build_b3(SellA &S, const gs2_csr &A, int R, const std::vector<int> &of
 }
 
 // copy A's values into the built layout
-int sella_fill_values(SellA &S, const gs2_csr &A, bool with_col, hipStream_t s)
+int sella_fill_values(SellA &S, const gs2_csr &A, bool with_col, hipStream_t s, int *flag)
 {
     const int tb = 256;
-    if (S.sel <= -10) {
-        if (A.n > 0) {
+    if (S.sel < 0) {
+        if (A.n > 0 && S.ndiag > 0) {
             DiaOffsA o;
             o.nd = S.ndiag;
             for (int d = 0; d < DIA_MAX; ++d) o.off[d] = S.doff[d];
-            constexpr int LN = 32; // 81 entries per row for 27-point 3-dof stencils
-            k_copy_fill<LN, true><<<(unsigned)((A.n * LN + tb - 1) / tb), tb, 0, s>>>(A.n, 1, A.rowptr, A.colind,
-                                                                                      A.val, o, S.dstride, S.dval);
-        }
-    } else if (S.sel < 0) {
-        if (A.n > 0) {
-            DiaOffsA o;
-            o.nd = S.ndiag;
-            for (int d = 0; d < DIA_MAX; ++d) o.off[d] = S.doff[d];
-            constexpr int LN = 8; // 7-point stencils: one entry per lane
-            k_copy_fill<LN, false><<<(unsigned)((A.n * LN + tb - 1) / tb), tb, 0, s>>>(A.n, S.dR, A.rowptr, A.colind,
-                                                                                       A.val, o, S.dstride, S.dval);
+            if (S.sel <= -10) {
+                const unsigned g = (unsigned)((A.n / 3 + FILL_NODES - 1) / FILL_NODES);
+                k_copy_fill<true><<<g, FILL_TB, sizeof(double) * 9 * o.nd * (FILL_NODES + 1), s>>>(
+                    A.n, 1, A.rowptr, A.colind, A.val, o, S.dstride, S.dval, flag);
+            } else {
+                const unsigned g = (unsigned)((A.n + FILL_ROWS - 1) / FILL_ROWS);
+                k_copy_fill<false><<<g, FILL_TB, sizeof(double) * o.nd * (FILL_ROWS + 1), s>>>(
+                    A.n, S.dR, A.rowptr, A.colind, A.val, o, S.dstride, S.dval, flag);
+            }
         }
     } else if (S.nslices > 0) {
         const int64_t threads = S.nslices * WAVE;
         k_sella_fill<<<(unsigned)((threads + tb - 1) / tb), tb, 0, s>>>(A.n, S.nslices, S.K, A.rowptr, A.colind,
-                                                                       A.val, S.sp, with_col ? 1 : 0, S.col, S.val);
+                                                                       A.val, S.sp, with_col ? 1 : 0, S.col, S.val,
+                                                                       flag);
     }
     GS2_TRY_HIP(hipGetLastError());
     return GS2_OK;

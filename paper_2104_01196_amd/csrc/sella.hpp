@@ -95,8 +95,34 @@ inline double sella_bytes(const SellA &S)
     return 12.0 * (double)S.nnz + 8.0 * (double)(S.nslices + 1) + 16.0 * (double)S.n;
 }
 
+// A solver's copy of the system matrix and what choosing its layout needs: two
+// vectors and a partial sum per KRB rows to time products with, and
+// pattern_dev_bytes() of device memory.
+constexpr int FILL_CHANGED = 1, FILL_UNSORTED = 2;
+
+struct Product {
+    SellA A;
+    int fmt_req = -1; // the layout request it was built for
+    double *in = nullptr, *out = nullptr, *part = nullptr;
+    PatternDev *pat = nullptr;
+};
+
+// krylov.hip: the copy in the layout fmt asks for (GS2_FORMAT_*), values as
+// they are now; w = A z with partial sums of w.z, and r = b - A x with partial
+// sums of r.r, each returning the number of partial sums (at most one per
+// 256 rows).
+//
+// Without flag the copy is kept per row-pointer and column array.  With it (a
+// device int that holds 0), per sizes, and the fill compares the pattern:
+// FILL_CHANGED: built for another pattern, to be built anew (fmt_req = -1);
+// FILL_UNSORTED: A's rows are not strictly sorted, which only the CSR arrays
+// or sliced ELL can hold.  Neither makes a product read out of bounds.
+int prepare_product(Product &W, const gs2_csr &A, int fmt, hipStream_t s, int *flag = nullptr);
+int product_dot(const Product &W, const double *z, double *w, const int *stop, double *part, hipStream_t s);
+int product_resid(const Product &W, const double *x, const double *b, double *r, double *part, hipStream_t s);
+
 // Building blocks of the copy (sella.hip); the Krylov solver picks among
-// them (krylov.hip: prepare_matrix).
+// them (krylov.hip: prepare_product).
 void sella_free(SellA &S);
 // lanes per row the mean row length suggests
 int sella_rule_lanes(const gs2_csr &A);
@@ -115,7 +141,7 @@ bool sella_b3_offsets(const gs2_csr &A, const Pattern &P, std::vector<int> &offs
 // fill with sella_fill_values)
 int sella_build_b3(SellA &S, const gs2_csr &A, int R, const std::vector<int> &offs, hipStream_t s);
 // copy A's values (and columns, for a new sliced-ELL structure) into S
-int sella_fill_values(SellA &S, const gs2_csr &A, bool with_col, hipStream_t s);
+int sella_fill_values(SellA &S, const gs2_csr &A, bool with_col, hipStream_t s, int *flag = nullptr);
 
 // ybuf[i] = (A z)[r0 + i] for the RB rows of the workgroup starting at r0
 // (0 past n), into LDS.  The workgroup's NW wavefronts take consecutive
