@@ -285,6 +285,11 @@ struct Handle {
     Perm PL, PU, PC;
     std::vector<int64_t> color_ptr;
     unsigned *tri_next = nullptr; // next chunk of the half sweeps in turn (3 counters)
+    // one-launch applies of small systems: two sets of ne exchanged vectors,
+    // and the applies each wavefront has done (small.hip; null: none)
+    int ne = 0;
+    void *ex = nullptr;
+    unsigned *ep = nullptr;
     GmresWork *gw = nullptr;
     CgWork *cw = nullptr;
     const int *stop = nullptr; // device flag: kernels return at once when set (GMRES)
@@ -336,6 +341,20 @@ inline size_t aligned(size_t b) { return (b + 255) / 256 * 256; }
 bool choice_get(const std::string &key, int *choice);
 void choice_put(const std::string &key, int choice);
 std::string shape_key(int64_t n, double avg, int maxlen, int prec);
+
+// small.hip: applies of at most SMALL_MAX_N rows in one launch, where their
+// passes exchange at most SMALL_MAX_EX vectors.  small_bytes: memory that takes (0
+// where it cannot be); small_init: on that memory; small_apply: false where it
+// does not fit after all (then nothing is launched).
+constexpr int64_t SMALL_MAX_N = 65536;
+constexpr int SMALL_MAX_EX = 8;
+// Longest row without its diagonal: a thread takes a row alone, four entries to
+// a trip.  60000 rows of 16 others, SGS2(1,1): 8.6 us in one launch, 13.3 pass
+// by pass (float32: 11.8, 14.0); of 24 others 11.5, 13.4 (float32: 21.0, 14.0).
+constexpr int SMALL_MAX_ROW = 16;
+size_t small_bytes(const Handle &h);
+void small_init(Handle &h, void *mem, hipStream_t s);
+bool small_apply(Handle &h, bool jr, int sweeps, double omega, const double *v, double *z, hipStream_t s);
 
 // sweep.hip
 int apply_gs2(Handle &h, const double *v, double *z, hipStream_t s);

@@ -341,7 +341,7 @@ struct Team {
                         Sums acc;
                         row_dot(T, acc, gin);
                         AT g = rh_own - w * acc.total();
-                        if (damp) g = (AT(1) - gamma) * g_own + gamma * g;
+                        if (damp) g = fma(gamma, g, (AT(1) - gamma) * g_own);
                         if (last) finish(fin, set, g, xc);
                         else put(gout, g);
                         g_own = g;

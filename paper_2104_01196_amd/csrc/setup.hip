@@ -1069,12 +1069,13 @@ static int build_levels(Handle &h, const gs2_csr &A, const int32_t *lcnt, hipStr
 }
 
 // The scaling vectors and, with work, the applies' temporaries.
-static int alloc_vectors(Handle &h, bool work)
+static int alloc_vectors(Handle &h, bool work, hipStream_t s)
 {
     const size_t n = (size_t)std::max<int64_t>(h.n, 1), d = aligned(sizeof(double) * n);
     const size_t vb = aligned(prec_bytes(h.precision) * n);
     const bool sv = h.precision != GS2_FP64, yh = h.blocks > 1;
-    GS2_TRY_HIP(hipMalloc(&h.vec, 2 * d + (work ? (5 + sv + yh) * vb : 0)));
+    const size_t small = work ? small_bytes(h) : 0;
+    GS2_TRY_HIP(hipMalloc(&h.vec, 2 * d + (work ? (5 + sv + yh) * vb : 0) + small));
     char *p = (char *)h.vec;
     h.sl = (double *)p;
     h.sr = (double *)(p + d);
@@ -1088,7 +1089,11 @@ static int alloc_vectors(Handle &h, bool work)
         h.sv = p;
         p += vb;
     }
-    if (yh) h.yh = p;
+    if (yh) {
+        h.yh = p;
+        p += vb;
+    }
+    if (small) small_init(h, p, s);
     return GS2_OK;
 }
 
@@ -1098,11 +1103,12 @@ int setup_handle(Handle &h, const gs2_csr &A, const gs2_options &o, hipStream_t 
     if (n == 0) return GS2_OK;
     SetupScratch sc;
     GS2_TRY(sc.alloc(n));
-    GS2_TRY(alloc_vectors(h, alloc_vecs));
+    GS2_TRY(alloc_vectors(h, alloc_vecs, s));
     GS2_TRY_HIP(hipMemsetAsync(sc.err, 0, sizeof(int), s));
     GS2_TRY(scan_pattern(A, sc.lcnt, sc.ucnt, h.sl, h.sr, sc.dev, sc.pat, s));
     GS2_TRY(flags_to_status(sc.pat.err));
 
+    if (sc.pat.maxlen > SMALL_MAX_ROW) h.ep = nullptr; // pass by pass
     // row-length statistics of L (U has the same count for symmetric patterns)
     const double avg = n ? (double)(A.nnz - n) / (2.0 * n) : 0.0;
     const int maxlen = sc.pat.maxlen;

@@ -170,7 +170,7 @@ __global__ __launch_bounds__(KT) void k_inner(const int *__restrict__ stop, int6
         AT g = r - w * a;
         if (damp) {
             const AT go = gv ? (AT)(v[row] * sl[row]) : gin[row];
-            g = (AT(1) - gamma) * go + gamma * g;
+            g = fma(gamma, g, (AT(1) - gamma) * go);
         }
         finish<AT>(dst, row, g, w, gout, xh, xh, z, sr);
     }
@@ -694,7 +694,7 @@ __global__ __launch_bounds__(DIA_THREADS) void k_dia_inner(const int *__restrict
         AT g = r - w * acc[k];
         if (damp) {
             const AT go = gv ? (AT)(v[row] * sl[row]) : gin[row];
-            g = (AT(1) - gamma) * go + gamma * g;
+            g = fma(gamma, g, (AT(1) - gamma) * go);
         }
         finish<AT>(dst, row, g, w, gout, xh, xh, z, sr);
     }
@@ -834,7 +834,7 @@ __global__ __launch_bounds__(DIA_THREADS) void k_b3_inner(const int *__restrict_
             AT g = r - w * acc[k][j];
             if (damp) {
                 const AT go = gv ? (AT)(v[row] * sl[row]) : gin[row];
-                g = (AT(1) - gamma) * go + gamma * g;
+                g = fma(gamma, g, (AT(1) - gamma) * go);
             }
             finish<AT>(dst, row, g, w, gout, xh, xh, z, sr);
         }
@@ -1464,14 +1464,16 @@ struct Launch {
 
 int apply_gs2(Handle &h, const double *v, double *z, hipStream_t s)
 {
-    int st = GS2_DISPATCH(h, gs2(h, v, z, s));
+    int st = GS2_OK;
+    if (!small_apply(h, false, h.sweeps, h.omega, v, z, s)) st = GS2_DISPATCH(h, gs2(h, v, z, s));
     GS2_TRY_HIP(hipGetLastError());
     return st;
 }
 
 int apply_jr(Handle &h, int sweeps, double omega, const double *v, double *z, hipStream_t s)
 {
-    int st = GS2_DISPATCH(h, jr(h, sweeps, omega, v, z, s));
+    int st = GS2_OK;
+    if (!small_apply(h, true, sweeps, omega, v, z, s)) st = GS2_DISPATCH(h, jr(h, sweeps, omega, v, z, s));
     GS2_TRY_HIP(hipGetLastError());
     return st;
 }
