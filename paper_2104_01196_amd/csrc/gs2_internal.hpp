@@ -131,6 +131,22 @@ __device__ __forceinline__ T wave_sum(T v)
     return group_sum<WAVE>(v);
 }
 
+// A NaN pattern that no result keeps: in vectors whose unknowns are their own
+// flags, the entries that are not there yet (exact sweeps, one-launch applies
+// and solves).
+template <typename AT>
+struct Bits;
+template <>
+struct Bits<double> {
+    typedef unsigned long long T;
+    static constexpr T not_ready = 0xfff8a5a5c3c30f0full;
+};
+template <>
+struct Bits<float> {
+    typedef unsigned int T;
+    static constexpr T not_ready = 0xffc5a5c3u;
+};
+
 // value type conversions used by the kernels
 template <typename T>
 __device__ __forceinline__ float to_f(T v)
@@ -341,6 +357,9 @@ inline size_t aligned(size_t b) { return (b + 255) / 256 * 256; }
 bool choice_get(const std::string &key, int *choice);
 void choice_put(const std::string &key, int choice);
 std::string shape_key(int64_t n, double avg, int maxlen, int prec);
+
+// small.hip: vectors that an apply's passes write for others to gather
+int exchanged(bool jr, int sweeps, int inner, int variant);
 
 // small.hip: applies of at most SMALL_MAX_N rows in one launch, where their
 // passes exchange at most SMALL_MAX_EX vectors.  small_bytes: memory that takes (0

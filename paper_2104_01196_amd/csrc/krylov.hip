@@ -111,13 +111,16 @@ void free_gmres_work(GmresWork *g)
     delete g;
 }
 
-static int alloc_work(GmresWork **out, int64_t n, int m)
+// ne: vectors exchanged within an apply of the handle (< 0: none, or too many
+// for a solve in one launch)
+static int alloc_work(GmresWork **out, int64_t n, int m, int ne)
 {
     GmresWork *g = new (std::nothrow) GmresWork;
     if (!g) return GS2_ERR_NOMEM;
     g->n = n;
     g->m = m;
     g->nb = (int)std::max<int64_t>(1, (n + RB - 1) / RB);
+    const int64_t nbs = n <= RES_MAX_N ? (n + res_rows(n) - 1) / res_rows(n) : g->nb; // most partials
     const size_t N = (size_t)std::max<int64_t>(n, 1);
     int st = GS2_OK;
     size_t total = 0;
@@ -131,12 +134,12 @@ static int alloc_work(GmresWork **out, int64_t n, int m)
         at(g->Z, sizeof(double) * N * m);
         at(g->w, sizeof(double) * N);
         at(g->w2, sizeof(double) * N);
-        at(g->part, sizeof(double) * (size_t)g->nb * (2 * MAXM + 3)); // delayed CGS2: 2j+3 per block
+        at(g->part, sizeof(double) * (size_t)nbs * (2 * MAXM + 3)); // delayed CGS2: 2j+3 per block
         at(g->st, sizeof(GState));
         at(g->pat, pattern_dev_bytes());
-        if (n <= RES_MAX_N) {
-            at(g->rex, sizeof(double) * 3 * N);
-            at(g->rpart, sizeof(double) * RES_MAX_GROUPS * (2 * RES_MAX_M + 4));
+        if (n <= RES_MAX_N && ne >= 0) {
+            at(g->rex, sizeof(double) * (3 + 2 * (size_t)(ne + 1)) * N);
+            at(g->rpart, sizeof(double) * RES_MAX_GROUPS * res_parts(RES_MAX_M));
             at(g->rbar, sizeof(unsigned) * 4);
         }
     };
@@ -199,13 +202,14 @@ __device__ __forceinline__ double norm_part(const double *rn, int c)
     return o;
 }
 
-template <bool TWO, int G = RL>
+template <bool TWO, int G = RL, int ROWS = RB>
 __device__ __forceinline__ void block_multidot(int64_t n, int64_t r0, const double *al, const double *bl,
                                                const double *__restrict__ V, int64_t ldv, int nk, bool with_norms,
                                                double *ra, double *rb, double *rn)
 {
     const int wv = threadIdx.x / WAVE, ln = threadIdx.x & (WAVE - 1);
-    const int last = (int)(n - 1 - r0 < RB - 1 ? n - 1 - r0 : RB - 1);
+    constexpr int RL = ROWS / WAVE;
+    const int last = (int)(n - 1 - r0 < ROWS - 1 ? n - 1 - r0 : ROWS - 1);
     if (with_norms) {
         constexpr int QR = RL / NWV;
         double aa = 0.0, ab = 0.0, bb = 0.0;
@@ -286,18 +290,18 @@ __global__ __launch_bounds__(KT) void k_spmv_dot(SellAView A, DiaAView D, int64_
 }
 
 // r = b - A x written to out, with ||r||^2 partials.
-template <int SEL>
+template <int SEL, int ROWS = RB>
 __global__ __launch_bounds__(KT) void k_true_resid(SellAView A, DiaAView D, int64_t n, const double *__restrict__ x,
                                                    const double *__restrict__ b, double *__restrict__ out,
                                                    double *__restrict__ part, int nb)
 {
-    __shared__ double wl[RB];
+    __shared__ double wl[ROWS];
     __shared__ double red[KT / WAVE];
-    const int64_t r0 = (int64_t)blockIdx.x * RB;
+    const int64_t r0 = (int64_t)blockIdx.x * ROWS;
     const int t = threadIdx.x;
-    mat_rows<SEL, KT / WAVE>(A, D, n, r0, x, wl);
+    mat_rows<SEL, KT / WAVE, ROWS>(A, D, n, r0, x, wl);
     double s = 0.0;
-    for (int i = t; i < RB; i += KT) {
+    for (int i = t; i < ROWS; i += KT) {
         const int64_t row = r0 + i;
         if (row < n) {
             const double r = b[row] - wl[i];
@@ -310,12 +314,13 @@ __global__ __launch_bounds__(KT) void k_true_resid(SellAView A, DiaAView D, int6
 }
 
 // ||b||^2 partials
+template <int ROWS = RB>
 __global__ __launch_bounds__(KT) void k_norm_part(int64_t n, const double *__restrict__ b, double *__restrict__ part, int nb)
 {
     __shared__ double red[4];
-    const int64_t r0 = (int64_t)blockIdx.x * RB;
+    const int64_t r0 = (int64_t)blockIdx.x * ROWS;
     double s = 0.0;
-    for (int u = 0; u < RB / KT; ++u) {
+    for (int u = 0; u < ROWS / KT; ++u) {
         const int64_t row = r0 + threadIdx.x + u * KT;
         if (row < n) s = fma(b[row], b[row], s);
     }
@@ -484,21 +489,21 @@ __global__ void k_scale_next(int64_t n, double *__restrict__ V, int64_t ldv, con
 // equal to the final column in exact arithmetic; when the cycle stops the
 // tentative column is committed as it stands.
 
-template <int SEL>
+template <int SEL, int ROWS = RB>
 __global__ __launch_bounds__(KT) void k_spmv_dot2(SellAView A, DiaAView D, int64_t n, const double *__restrict__ z,
                                                   double *__restrict__ w, const double *__restrict__ V, int64_t ldv,
                                                   const GState *__restrict__ st, double *__restrict__ part, int nb)
 {
-    __shared__ double wl[RB], ul[RB];
+    __shared__ double wl[ROWS], ul[ROWS];
     __shared__ double ra[MAXM + 2], rc[MAXM + 2], rn[3 * NWV];
     if (st->done) return;
     const int j = st->j;
-    const int64_t r0 = (int64_t)blockIdx.x * RB;
+    const int64_t r0 = (int64_t)blockIdx.x * ROWS;
     const int t = threadIdx.x;
-    mat_rows<SEL, KT / WAVE>(A, D, n, r0, z, wl);
+    mat_rows<SEL, KT / WAVE, ROWS>(A, D, n, r0, z, wl);
     const double zsc = st->zs[j];
     const double *__restrict__ u = V + (int64_t)j * ldv;
-    for (int i = t; i < RB; i += KT) {
+    for (int i = t; i < ROWS; i += KT) {
         const int64_t row = r0 + i;
         const double wv = zsc * wl[i];
         wl[i] = wv;
@@ -507,7 +512,7 @@ __global__ __launch_bounds__(KT) void k_spmv_dot2(SellAView A, DiaAView D, int64
     }
     __syncthreads();
     // a = Q^T u, c = Q^T w (Q = V[0..j)), then u.u, u.w, w.w
-    block_multidot<true>(n, r0, ul, wl, V, ldv, j, true, ra, rc, rn);
+    block_multidot<true, ROWS / WAVE, ROWS>(n, r0, ul, wl, V, ldv, j, true, ra, rc, rn);
     __syncthreads();
     for (int k = t; k < 2 * j + 3; k += KT)
         part[(int64_t)k * nb + blockIdx.x] = k < j ? ra[k] : k < 2 * j ? rc[k - j] : norm_part(rn, k - 2 * j);
@@ -720,6 +725,7 @@ __global__ __launch_bounds__(KT) void k_dot2(int64_t n, const double *__restrict
 // Pass 2 of step j: q_j = (u - Q a)/alpha over u's slot, w' = w - Q c - e q_j
 // into V[j+1], partial ||w'||^2.  Every workgroup derives alpha and e itself
 // (identical bits) and skips the pass when u has fallen into span(Q).
+template <int ROWS = RB>
 __global__ __launch_bounds__(KT) void k_dcgs_update(int64_t n, double *__restrict__ V, int64_t ldv,
                                                     const GState *__restrict__ st, const double *__restrict__ w,
                                                     double *__restrict__ part)
@@ -735,11 +741,11 @@ __global__ __launch_bounds__(KT) void k_dcgs_update(int64_t n, double *__restric
     double alpha, e, a2;
     if (!reorth_scalars(st, j, as, cs_, sc, &alpha, &e, &a2)) return; // the same in every workgroup
     const double ia = 1.0 / alpha, zsc = st->zs[j];
-    const int64_t r0 = (int64_t)blockIdx.x * RB;
+    const int64_t r0 = (int64_t)blockIdx.x * ROWS;
     double s = 0.0;
     double *__restrict__ u = V + (int64_t)j * ldv;
     double *__restrict__ wn = V + (int64_t)(j + 1) * ldv;
-    constexpr int NQ = RB / KT;
+    constexpr int NQ = ROWS / KT;
     // rows past n are clamped to n-1 for loads and skipped for stores
     int64_t rows[NQ];
     double aq[NQ], aw[NQ];
@@ -1043,6 +1049,20 @@ __global__ void k_copy_stop(int64_t n, const double *__restrict__ a, double *__r
         }                                                                    \
     } while (0)
 
+// the same for `rows` rows per workgroup, and for one lane per row and fewer
+// than RB rows per workgroup
+#define GS2_ROWS_DISPATCH(kern, grid, str, ...)                              \
+    do {                                                                     \
+        if (rows == 256) kern<256><<<grid, KT, 0, str>>>(__VA_ARGS__);       \
+        else if (rows == 512) kern<512><<<grid, KT, 0, str>>>(__VA_ARGS__);  \
+        else kern<RB><<<grid, KT, 0, str>>>(__VA_ARGS__);                    \
+    } while (0)
+#define GS2_SELL1_DISPATCH(kern, grid, str, ...)                             \
+    do {                                                                     \
+        if (rows == 256) kern<1, 256><<<grid, KT, 0, str>>>(__VA_ARGS__);    \
+        else kern<1, 512><<<grid, KT, 0, str>>>(__VA_ARGS__);                \
+    } while (0)
+
 static int precondition(int kind, gs2_handle *P, const double *v, double *z, int64_t n, const GState *st,
                         hipStream_t s)
 {
@@ -1290,7 +1310,7 @@ static int sum_lanes(const Handle &h) { return h.fmt == FMT_DIA ? 1 : h.L.K; }
 static bool resident_fits(const GmresWork *W, const gs2_handle *P, int m, int kind)
 {
     return P && W->rbar && m <= RES_MAX_M && P->h.orth == 0 && P->h.blocks == 1 && W->prod.A.sel == 1 &&
-           sum_lanes(P->h) <= RES_MAX_LANES &&
+           sum_lanes(P->h) <= res_lanes(W->n) &&
            P->h.spmv_fmt == GS2_FORMAT_AUTO && P->h.basis_req == 0 && !prof_on() &&
            (kind == GS2_PREC_NONE || kind == GS2_PREC_GS2 || kind == GS2_PREC_JR);
 }
@@ -1310,7 +1330,7 @@ static int resident_solve(GmresWork *W, const double *b, double *x, int m, doubl
     const size_t N = (size_t)h.n;
     ResArgs a{};
     a.n = (int)h.n;
-    a.G = W->nb;
+    a.G = (int)((h.n + res_rows(h.n) - 1) / res_rows(h.n));
     a.m = m;
     a.maxit = maxit;
     a.stag = h.stag_cycles == 0 ? 50 : h.stag_cycles;
@@ -1331,15 +1351,11 @@ static int resident_solve(GmresWork *W, const double *b, double *x, int m, doubl
     a.x = x;
     a.V = W->V;
     a.Z = W->Z;
-    a.se = W->rex;
+    a.xe = W->rex;
     a.ze = W->rex + N;
-    a.xe = W->rex + 2 * N;
+    a.ex = W->rex + 3 * N;
+    a.ne = exchanged(kind == GS2_PREC_JR, h.sweeps, h.inner, h.variant);
     a.part = W->rpart;
-    a.xh = h.xh;
-    a.xh2 = h.xh2;
-    a.rh = h.rh;
-    a.ga = h.ga;
-    a.gb = h.gb;
     a.bar = W->rbar;
     a.info = W->rinfo;
     GS2_TRY(resident_launch(h.precision, sum_lanes(h), a, s));
@@ -1364,11 +1380,12 @@ static int gmres_impl(const gs2_csr &A, const double *b, double *x, int m, doubl
         if (!P->h.gw || P->h.gw->n != n || P->h.gw->m < m) {
             if (P->h.gw) free_gmres_work(P->h.gw);
             P->h.gw = nullptr;
-            GS2_TRY(alloc_work(&P->h.gw, n, m));
+            const int ne = exchanged(false, P->h.sweeps, P->h.inner, P->h.variant);
+            GS2_TRY(alloc_work(&P->h.gw, n, m, ne <= RES_MAX_EX ? ne : -1));
         }
         W = P->h.gw;
     } else {
-        GS2_TRY(alloc_work(&own, n, m));
+        GS2_TRY(alloc_work(&own, n, m, -1));
         W = own;
     }
     struct Guard {
@@ -1376,8 +1393,6 @@ static int gmres_impl(const gs2_csr &A, const double *b, double *x, int m, doubl
         ~Guard() { if (g) free_gmres_work(g); }
     } guard{own};
 
-    const int nb = W->nb;
-    const unsigned gN = (unsigned)nb;
     const unsigned gE = (unsigned)((n + 255) / 256);
     W->prod.in = W->w;
     W->prod.out = W->w2;
@@ -1393,6 +1408,13 @@ static int gmres_impl(const gs2_csr &A, const double *b, double *x, int m, doubl
     const SellAView AS = view(W->prod.A);
     const DiaAView AD = dview(W->prod.A);
     const int K = W->prod.A.sel;
+    // orthogonalisation: 0 = delayed CGS2 (default), 1 = CGS2
+    const int orth = P ? P->h.orth : 0;
+    // rows per workgroup: those of the solve in one launch, where the system
+    // has its size and layout
+    const int rows = orth == 0 && K == 1 && n <= RES_MAX_N ? res_rows(n) : RB;
+    const int nb = (int)((n + rows - 1) / rows);
+    const unsigned gN = (unsigned)nb;
     GState *st = W->st;
     GHeader *hdr = W->hdr;
     if (P) P->h.stop = &st->done;
@@ -1411,7 +1433,7 @@ static int gmres_impl(const gs2_csr &A, const double *b, double *x, int m, doubl
     info->restarts = 0;
     info->converged = 0;
     info->relres = 0.0;
-    k_norm_part<<<gN, KT, 0, s>>>(n, b, W->part, nb);
+    GS2_ROWS_DISPATCH(k_norm_part, gN, s, n, b, W->part, nb);
     k_reduce<<<1, KT, 0, s>>>(W->part, nb, st, 8, 0, 1);
     GS2_TRY_HIP(hipGetLastError());
     GS2_TRY(read_hdr());
@@ -1423,8 +1445,6 @@ static int gmres_impl(const gs2_csr &A, const double *b, double *x, int m, doubl
         info->converged = 1;
         return GS2_OK;
     }
-    // orthogonalisation: 0 = delayed CGS2 (default), 1 = CGS2
-    const int orth = P ? P->h.orth : 0;
     // z_j is always a copy: the delayed variant rewrites v_j after z_j was formed
     double *Zb = W->Z;
     int total = 0, cycles = 0, status = GS2_OK;
@@ -1442,7 +1462,8 @@ static int gmres_impl(const gs2_csr &A, const double *b, double *x, int m, doubl
         prof_set_step(cycles, -1);
         {
             Prof pr(s, PK_TRUE_RESID, spmv_b + 8.0 * n);
-            GS2_SPMV_DISPATCH(K, k_true_resid, gN, AS, AD, n, x, b, W->V, W->part, nb);
+            if (rows < RB) GS2_SELL1_DISPATCH(k_true_resid, gN, s, AS, AD, n, x, b, W->V, W->part, nb);
+            else GS2_SPMV_DISPATCH(K, k_true_resid, gN, AS, AD, n, x, b, W->V, W->part, nb);
         }
         {
             Prof pr(s, PK_REDUCE, red_b);
@@ -1515,7 +1536,9 @@ static int gmres_impl(const gs2_csr &A, const double *b, double *x, int m, doubl
                     } else {
                         Prof pr(cs, PK_SPMV_DOT, spmv_b + vb);
                         hipStream_t s = cs;
-                        GS2_SPMV_DISPATCH(K, k_spmv_dot2, gN, AS, AD, n, zj, W->w, W->V, n, st, W->part, nb);
+                        if (rows < RB)
+                            GS2_SELL1_DISPATCH(k_spmv_dot2, gN, s, AS, AD, n, zj, W->w, W->V, n, st, W->part, nb);
+                        else GS2_SPMV_DISPATCH(K, k_spmv_dot2, gN, AS, AD, n, zj, W->w, W->V, n, st, W->part, nb);
                     }
                     {
                         Prof pr(cs, PK_REDUCE, red_b * (2 * j + 3));
@@ -1524,7 +1547,7 @@ static int gmres_impl(const gs2_csr &A, const double *b, double *x, int m, doubl
                     {
                         Prof pr(cs, PK_CGS, 8.0 * n * (j + 4));
                         if (!pairs)
-                            k_dcgs_update<<<gN, KT, 0, cs>>>(n, W->V, n, st, W->w, W->part);
+                            GS2_ROWS_DISPATCH(k_dcgs_update, gN, cs, n, W->V, n, st, W->w, W->part);
                         else if (j < W->upd_narrow)
                             k_dcgs_update_pairs<UPD_PAIRS, UPD_PAIRS>
                                 <<<(unsigned)nbu, KT, 0, cs>>>(n, W->V, n, st, W->w, W->part);

@@ -5,15 +5,22 @@
 // at 4 to 5 us each, whatever they do, and the launches of a cycle that are
 // left over once it has converged.  Here G workgroups stay for the whole
 // solve, each with its own contiguous rows, and meet at a barrier between
-// passes (0.8 us for up to 32 of them, 1.3 us for 64).  64 x 64 Poisson,
-// SGS2(1,1), GMRES(30), 92 steps: 3.17 ms launched, 2.1 ms here; 255 x 255
-// convection-diffusion, GS2(2,2), GMRES(20), 114 steps: 6.3 against 4.9 ms.
-// Bound by the instructions of 16 wavefronts on one compute unit (2.3 us for a
-// five-point product whose operands sit in LDS) and by the barriers.
+// cycles (0.8 us for up to 32 of them, 1.3 us for 64).  64 x 64 Poisson,
+// SGS2(1,1), GMRES(30), 92 steps: 3.17 ms launched, 1.26 ms here; 255 x 255
+// convection-diffusion, GS2(2,2), GMRES(20), 114 steps: 6.39 against 3.07 ms.
+// (With a barrier after every pass, 0.8 to 1.3 us and the stores' acknowledgement
+// before it, 1.99 and 4.88 ms.)  Bound by the chain of trips past the caches: one
+// for every pass of the preconditioner, for the product and for either
+// reduction of a step, about 0.8 us each, and by the serial work of a step
+// (3.5 us, on a wavefront of its own where 1024 threads leave room for one).
+//
+// Rows per workgroup: the fewest that 64 workgroups hold (64 partial sums are
+// one per lane).  64 x 64 Poisson with 1024 rows per workgroup and barriers took
+// 2.19 ms, with 256 and barriers 1.99.
 //
 // Method, order of every sum and therefore every bit are those of krylov.hip's
 // delayed reorthogonalisation launch by launch: a workgroup here owns the
-// KRB rows that a workgroup of the launches owns, forms its partial sums in
+// rows that a workgroup of the launches owns (res_rows), forms its partial sums in
 // the same order and adds the partials of all workgroups as k_reduce and
 // dcgs_finish_block do (at most 64 of them: one per lane).  Every workgroup
 // does so, repeats the scalar work on its own copy of the state
@@ -21,19 +28,30 @@
 //
 // Memory: what other workgroups read (the vectors that a pass gathers, partial
 // sums) is only ever stored and loaded at agent scope, past the caches that
-// XCDs do not share, with every wavefront's stores acknowledged before its
-// workgroup arrives at the barrier; what only its own workgroup reads (the
-// basis V, the preconditioned vectors Z) is only ever accessed plainly.  The
-// matrix is read plainly and never written.
+// XCDs do not share; what only its own workgroup reads (the basis V, the
+// preconditioned vectors Z) is only ever accessed plainly.  The matrix is read
+// plainly and never written.
+//
+// Within a cycle there is no barrier between workgroups: an entry of an
+// exchanged vector and a partial sum is its own flag (Bits::not_ready until it
+// is there) and readers poll, one trip instead of the four of store, arrival,
+// departure and load.  A step uses one of two turns of the exchanged vectors and
+// one of three turns of the partial sums.  A workgroup that has seen every
+// first-pass sum of step j knows that all are done with the vectors of step j
+// and the sums of step j - 1, and resets its own entries of these; it waits for
+// the resets to be acknowledged before it publishes its sums of step j + 1,
+// without which nobody reads that turn again.  A cycle starts with all of it
+// reset, then a barrier.
 //
 // Registers: 1024 threads leave 128 per thread.  Kept below that without
-// spills (eight loads in flight over a basis vector, not all sixteen): a
-// version that spilled vector registers beside spilled scalar ones gave wrong
+// spills (eight loads in flight over a basis vector, not all sixteen; two
+// entries of a row at a time): a version that spilled vector registers beside spilled scalar ones gave wrong
 // results in the float32 instantiation.
 //
-// Waits are bounded: past WAIT_TICKS of the wall clock the abort flag goes up,
-// every workgroup leaves and the caller solves by launches instead, from the
-// x it finds (x is written at the end only).
+// Waits are bounded: past WAIT_TICKS of the wall clock or WAIT_POLLS looks the
+// abort flag goes up, who has waited that long waits no more, every workgroup
+// leaves at the next barrier and the caller solves by launches instead, from
+// the x it finds (x is written at the end only).
 #include <algorithm>
 #include <cmath>
 
@@ -47,10 +65,13 @@ namespace gs2 {
 namespace {
 
 constexpr long long WAIT_TICKS = 200000000ll; // 2 s at 100 MHz
-constexpr int RT = RES_ROWS;    // a thread per row
-constexpr int NW = RT / WAVE;   // wavefronts per workgroup
+constexpr unsigned WAIT_POLLS = 1u << 21;      // trips to memory, half a microsecond or more each
 constexpr int QW = KT / WAVE;   // wavefronts of the launches whose sums are repeated here
-static_assert(RES_ROWS == KRB, "the launches' rows per workgroup");
+
+// Threads of a workgroup of RR rows: one per row and, where there is room for
+// it, a wavefront that closes a step while the others precondition.
+constexpr int threads_of(int rr) { return rr < 1024 ? rr + WAVE : rr; }
+constexpr int near_of(int rr) { return rr < 1024 ? 1 : rr; }
 
 __device__ __forceinline__ double ald(const double *p)
 {
@@ -71,12 +92,15 @@ __device__ __forceinline__ void ast(float *p, float v)
     __hip_atomic_store((unsigned *)p, __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+template <int RR>
 struct Shared {
     unsigned long long sw[GSTATE_SMALL_WORDS];
     double col[MAXM + 2], sc[2], red[QW], nrm[3 * QW];
     double step[3]; // alpha, e, alpha^2 of the step to be closed
-    double ul[RES_ROWS], wl[RES_ROWS];
-    double near[2][RES_ROWS]; // own rows of the vector gathered now, and of the next one
+    double ul[RR], wl[RR];
+    // own rows of the vector gathered now, and of the next one, for 1024 rows:
+    // read at agent scope every one of them was a trip past the caches
+    double near[2][near_of(RR)];
     int flag, most[3];
 };
 
@@ -92,43 +116,87 @@ struct Mat {
 
 // One workgroup's view of the solve.  KL: log2 of the lanes per row whose sums
 // the launches add (0 where they add a row's entries one after the other).
-template <typename VT, typename AT, int KL>
+template <typename VT, typename AT, int KL, int RR>
 struct Team {
+    static constexpr int NT = threads_of(RR), NW = NT / WAVE;
     const ResArgs &a;
-    Shared &sh;
+    Shared<RR> &sh;
     double *H; // m x m, in LDS
     int me, t, wv, ln;
     int r0, rows, row; // the workgroup's first row and row count, the thread's row
     bool own;          // the thread has one
     Mat mL, mU, mA;
-    double u_own = 0.0; // the raw tentative vector's entry
-    AT sv_own = AT(0);  // ... and S_l u, rounded
+    AT sv_own = AT(0); // S_l u, rounded (u itself, unscaled, in sh.ul)
     unsigned epoch = 0;
 
+    static constexpr bool NEAR = near_of(RR) == RR;
     int side = 0; // which of sh.near is gathered
+    bool late = false; // a wait has run out
+    int turn = 0; // of the exchanged vectors
 
     __device__ GState *st() const { return reinterpret_cast<GState *>(sh.sw); }
+
+    template <typename T>
+    __device__ static void astf(T *p, T v) // an entry that is its own flag
+    {
+        typename Bits<T>::T b = __builtin_bit_cast(typename Bits<T>::T, v);
+        if (b == Bits<T>::not_ready) b ^= 1;
+        ast(p, __builtin_bit_cast(T, b));
+    }
+    template <typename T>
+    __device__ static void reset(T *p)
+    {
+        ast(p, __builtin_bit_cast(T, Bits<T>::not_ready));
+    }
+    template <typename T>
+    __device__ static bool there(T v)
+    {
+        return __builtin_bit_cast(typename Bits<T>::T, v) != Bits<T>::not_ready;
+    }
+
+    // between two looks at entries that are not there yet; false: wait no more
+    __device__ bool wait(unsigned &polls)
+    {
+        if (late) return false;
+        if (++polls < WAIT_POLLS) return true;
+        late = true;
+        __hip_atomic_store(a.bar + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return false;
+    }
 
     // the thread's entry of the vector that the next pass gathers
     template <typename T>
     __device__ void put(T *vec, T v)
     {
-        ast(vec + row, v);
-        reinterpret_cast<T *>(sh.near[side ^ 1])[t] = v;
+        astf(vec + row, v);
+        if (NEAR) reinterpret_cast<T *>(sh.near[side ^ 1])[t] = v;
+    }
+    // what the workgroup's threads have put is gathered from here on
+    __device__ void flip()
+    {
+        side ^= 1;
+        if (NEAR) __syncthreads();
+        __asm__ volatile("" ::: "memory");
     }
 
-    // U entries of the vector put last: own rows from LDS (most of a mesh
-    // row's; read at agent scope every one of them was a trip past the
-    // caches), others from memory
+    // U entries of the vector put last: own rows from LDS where they are kept
+    // there (most of a mesh row's), others from memory as soon as they are there
     template <int U, typename T>
-    __device__ void gather(const T *vec, const int *c, T *x) const
+    __device__ void gather(const T *vec, const int *c, T *x)
     {
         const T *near = reinterpret_cast<const T *>(sh.near[side]);
+        unsigned polls = 0;
+        for (;;) {
+            bool ready = true;
 #pragma unroll
-        for (int q = 0; q < U; ++q) {
-            const unsigned i = (unsigned)(c[q] - r0);
-            if (i < (unsigned)rows) x[q] = near[i];
-            else x[q] = ald(vec + c[q]);
+            for (int q = 0; q < U; ++q) {
+                const unsigned i = (unsigned)(c[q] - r0);
+                if (NEAR && i < (unsigned)rows) x[q] = near[i];
+                else x[q] = ald(vec + c[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < U; ++q) ready = ready && (there(x[q]) || (NEAR && (unsigned)(c[q] - r0) < (unsigned)rows));
+            if (ready || !wait(polls)) return;
         }
     }
 
@@ -151,12 +219,10 @@ struct Team {
                 if ((++polls & 255u) == 0u) {
                     if (wall_clock64() - t0 > WAIT_TICKS)
                         __hip_atomic_store(a.bar + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (__hip_atomic_load(a.bar + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-                        sh.flag = 1;
-                        break;
-                    }
+                    if (__hip_atomic_load(a.bar + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
                 }
             }
+            if (__hip_atomic_load(a.bar + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) sh.flag = 1;
         }
         __syncthreads();
         __asm__ volatile("" ::: "memory");
@@ -196,19 +262,19 @@ struct Team {
         atomicMax(&sh.most[which], M.cnt);
         __syncthreads();
         const int most = __builtin_amdgcn_readfirstlane(sh.most[which]);
-        const int bytes = most * RT * (int)(sizeof(WT) + sizeof(int32_t));
+        const int bytes = most * RR * (int)(sizeof(WT) + sizeof(int32_t));
         if (used + bytes > size) return;
         WT *val = (WT *)(area + used);
-        int32_t *col = (int32_t *)(val + most * RT);
+        int32_t *col = (int32_t *)(val + most * RR);
         for (int k = 0; k < M.cnt; ++k) {
             const int p = M.at + (k >> M.lk) * M.step + (k & ((1 << M.lk) - 1));
-            val[k * RT + t] = ((const WT *)M.val)[p];
-            col[k * RT + t] = M.col[p];
+            val[k * RR + t] = ((const WT *)M.val)[p];
+            col[k * RR + t] = M.col[p];
         }
         M.val = val;
         M.col = col;
         M.lk = 0;
-        M.step = RT;
+        M.step = RR;
         M.at = t;
         used += bytes;
     }
@@ -234,9 +300,9 @@ struct Team {
     }
 
     // acc += the row's stored entries of T times vec at their columns
-    __device__ void row_dot(const Mat &T, Sums &acc, const AT *vec) const
+    __device__ void row_dot(const Mat &T, Sums &acc, const AT *vec)
     {
-        constexpr int U = 4;
+        constexpr int U = NEAR && KL < 2 ? 2 : 4; // what the registers hold
         each_entry<VT, U>(T, [&](const VT *v, const int *c, int left) {
             AT x[U];
             gather<U>(vec, c, x);
@@ -247,10 +313,10 @@ struct Team {
     }
 
     // (A x)[row] in float64
-    __device__ double a_row(const double *vec) const
+    __device__ double a_row(const double *vec)
     {
         double acc = 0.0;
-        constexpr int U = KL == 0 ? 8 : 4; // a 7-point row in one round trip, where the registers last
+        constexpr int U = !NEAR && KL == 0 ? 8 : 4; // a 7-point row in one round trip, where the registers last
         each_entry<double, U>(mA, [&](const double *v, const int *c, int left) {
             double x[U];
             gather<U>(vec, c, x);
@@ -261,35 +327,37 @@ struct Team {
         return acc;
     }
 
+    // the vectors of a turn: S_l u and the preconditioner's, z
+    __device__ AT *ex(int tn, int q) const { return (AT *)a.ex + (int64_t)(tn * (a.ne + 1) + q) * a.n; }
+    __device__ double *ze(int tn) const { return a.ze + (int64_t)tn * a.n; }
+
     // z_j into the plain column (read back by this thread) and the gathered vector
     __device__ void put_z(double *zcol, double z)
     {
         zcol[row] = z;
-        put(a.ze, z);
+        put(ze(turn), z);
     }
 
     // the next raw tentative vector: the thread's entry, and S_l u for the
     // preconditioner's gathers (rounded as the launches round it)
-    __device__ void put_u(double u)
+    __device__ void put_u(double u, int tn)
     {
-        u_own = u;
+        sh.ul[t] = u;
         if (a.kind == GS2_PREC_NONE) return;
         sv_own = (AT)(u * a.sl[row]);
-        put((AT *)a.se, sv_own);
+        put(ex(tn, 0), sv_own);
     }
 
     // z = Mhat^{-1} u on the raw tentative vector (Launch::gs2 and Launch::jr of
     // sweep.hip, pass by pass).  What a pass needs of the thread's own row it
-    // still holds; only other rows' entries are gathered.  Ends with the
-    // barrier that makes z readable.
-    __device__ bool precondition(double *zcol)
+    // still holds; only other rows' entries are gathered.
+    __device__ void precondition(double *zcol)
     {
         if (a.kind == GS2_PREC_NONE) {
-            if (own) put_z(zcol, u_own);
-            return meet();
+            if (own) put_z(zcol, sh.ul[t]);
+            flip();
+            return;
         }
-        AT *xc = (AT *)a.xh, *xo = (AT *)a.xh2, *const rh = (AT *)a.rh;
-        AT *const g0 = (AT *)a.ga, *const g1 = (AT *)a.gb, *const se = (AT *)a.se;
         const bool jr = a.kind == GS2_PREC_JR;
         const int inner = jr ? 0 : a.inner, compact = jr ? 0 : a.compact;
         const int per = !jr && a.variant == GS2_SYMMETRIC ? 2 : 1, Hh = a.sweeps * per;
@@ -298,80 +366,90 @@ struct Team {
         const AT cdiag = compact ? (AT)(1.0 - 1.0 / a.omega) : AT(1);
         bool xzero = true;
         AT x_own = AT(0);
+        AT *src = ex(turn, 0); // the vector gathered
+        int used = 0;
+        // the row's entry of the next one
+        auto next = [&](AT v) {
+            ++used;
+            if (own) put(ex(turn, used), v);
+            src = ex(turn, used);
+            flip();
+        };
         // x <- w g or x + w g, or the output
-        auto finish = [&](bool fin, bool set, AT g, AT *xout) {
-            const AT x = set ? w * g : x_own + w * g;
-            if (fin) put_z(zcol, a.sr[row] * (double)x);
-            else put(xout, x);
+        auto finish = [&](bool fin, bool set, AT g) {
+            const AT x = set ? w * g : fma(w, g, x_own);
             x_own = x;
+            if (!fin) {
+                next(x);
+                return;
+            }
+            if (own) put_z(zcol, a.sr[row] * (double)x);
+            flip();
         };
         for (int tt = 0; tt < Hh; ++tt) {
             const bool lower = jr || a.variant == GS2_FORWARD || (a.variant == GS2_SYMMETRIC && tt % 2 == 0);
             const Mat &T = lower ? mL : mU, &O = lower ? mU : mL;
             const bool fin = tt == Hh - 1, set = xzero || compact;
-            auto residual = [&]() {
+            AT r = sv_own;
+            if (!xzero) {
                 Sums acc;
-                if (!compact) row_dot(T, acc, xc);
-                row_dot(O, acc, xc);
-                return fma(-cdiag, x_own, sv_own) - acc.total();
-            };
+                if (!compact) row_dot(T, acc, src);
+                row_dot(O, acc, src);
+                r = fma(-cdiag, x_own, sv_own) - acc.total();
+            }
             if (inner == 0) {
-                if (own) finish(fin, set, xzero ? sv_own : residual(), xzero ? xc : xo);
-                if (!xzero) {
-                    AT *tmp = xc;
-                    xc = xo;
-                    xo = tmp;
-                }
-                if (!meet()) return false;
+                finish(fin, set, r);
             } else {
-                AT rh_own = sv_own;
-                if (!xzero) {
-                    if (own) {
-                        rh_own = residual();
-                        put(rh, rh_own);
-                    }
-                    if (!meet()) return false;
-                }
-                const AT *gin = xzero ? se : rh;
-                AT g_own = rh_own;
+                if (!xzero) next(r);
+                AT g = r;
                 for (int j = 1; j <= inner; ++j) {
-                    const bool last = j == inner;
-                    AT *gout = (j & 1) ? g0 : g1;
-                    if (own) {
-                        Sums acc;
-                        row_dot(T, acc, gin);
-                        AT g = rh_own - w * acc.total();
-                        if (damp) g = fma(gamma, g, (AT(1) - gamma) * g_own);
-                        if (last) finish(fin, set, g, xc);
-                        else put(gout, g);
-                        g_own = g;
-                    }
-                    if (!meet()) return false;
-                    gin = gout;
+                    Sums acc;
+                    row_dot(T, acc, src);
+                    const AT old = g;
+                    g = fma(-w, acc.total(), r);
+                    if (damp) g = fma(gamma, g, (AT(1) - gamma) * old);
+                    if (j == inner) finish(fin, set, g);
+                    else next(g);
                 }
             }
             xzero = false;
         }
-        return true;
     }
 
-    // sum of the workgroups' partials part[q * G ..), one per lane (one
-    // wavefront; every lane gets it)
-    __device__ double total(const double *part, int q) const
+    // sums of the workgroups' partials part[q * G ..), one per lane, for q = q0,
+    // q0 + dq, .. (one wavefront; every lane gets them), PF polled at a time
+    template <int PF>
+    __device__ void totals(const double *part, int q0, int dq, int last, double *o)
     {
-        return wave_sum(ln < a.G ? ald(part + q * a.G + ln) : 0.0);
+        unsigned polls = 0;
+        for (;;) {
+            bool ready = true;
+#pragma unroll
+            for (int p = 0; p < PF; ++p) o[p] = ln < a.G ? ald(part + min(q0 + p * dq, last) * a.G + ln) : 0.0;
+#pragma unroll
+            for (int p = 0; p < PF; ++p) ready = ready && there(o[p]);
+            if (ready || !wait(polls)) break;
+        }
+#pragma unroll
+        for (int p = 0; p < PF; ++p) o[p] = wave_sum(o[p]);
+    }
+    __device__ double total(const double *part)
+    {
+        double o[1];
+        totals<1>(part, 0, 0, 0, o);
+        return o[0];
     }
 
     // the workgroup's sum of squares of one value per row (0 without a row):
     // a thread of KT adds its rows t, t + KT, ..., then block_sum; to part[me]
     __device__ void publish_squares(double v, double *part)
     {
-        sh.wl[t] = v;
+        if (NT == RR || t < RR) sh.wl[t] = v;
         __syncthreads();
         if (t < KT) {
             double s = 0.0;
 #pragma unroll
-            for (int u = 0; u < RES_ROWS / KT; ++u) s = fma(sh.wl[t + u * KT], sh.wl[t + u * KT], s);
+            for (int u = 0; u < RR / KT; ++u) s = fma(sh.wl[t + u * KT], sh.wl[t + u * KT], s);
             s = wave_sum(s);
             if (ln == 0) sh.red[wv] = s;
         }
@@ -379,7 +457,7 @@ struct Team {
         if (t == 0) {
             double s = 0.0;
             for (int k = 0; k < QW; ++k) s += sh.red[k];
-            ast(part + me, s);
+            astf(part + me, s);
         }
     }
 
@@ -387,7 +465,7 @@ struct Team {
     __device__ double agree(const double *part)
     {
         if (wv == 0) {
-            const double s = total(part, 0);
+            const double s = total(part);
             if (ln == 0) sh.sc[0] = s;
         }
         __syncthreads();
@@ -399,12 +477,16 @@ struct Team {
     __device__ bool solve(ResInfo &info);
 };
 
-template <typename VT, typename AT, int KL>
-__device__ bool Team<VT, AT, KL>::solve(ResInfo &info)
+template <typename VT, typename AT, int KL, int RR>
+__device__ bool Team<VT, AT, KL, RR>::solve(ResInfo &info)
 {
     GState *ls = st();
     const int n = a.n, m = a.m;
-    double *partN = a.part, *partQ = a.part + a.G; // norms; the first pass's sums
+    // a norm between barriers; a step's norm and first-pass sums, three turns
+    double *const partB = a.part;
+    const int turn_size = a.G * (2 * m + 4);
+    auto partN = [&](int j) { return a.part + a.G + (j % 3) * turn_size; };
+    auto partQ = [&](int j) { return partN(j) + a.G; };
     info = ResInfo{0, 0, GS2_OK, 0, 0.0};
     // the rows into LDS, the triangles first: they are read most often
     {
@@ -422,11 +504,10 @@ __device__ bool Team<VT, AT, KL>::solve(ResInfo &info)
         }
         keep<double>(mA, 2, area, used, size);
     }
-    double xv = own ? a.x[row] : 0.0;
-    if (own) put(a.xe, xv);
-    publish_squares(own ? a.b[row] : 0.0, partN);
+    if (own) put(a.xe, a.x[row]);
+    publish_squares(own ? a.b[row] : 0.0, partB);
     if (!meet()) return false;
-    const double bnorm = sqrt(agree(partN));
+    const double bnorm = sqrt(agree(partB));
     if (!isfinite(bnorm)) {
         info.status = GS2_ERR_NONFINITE;
         return true;
@@ -442,9 +523,9 @@ __device__ bool Team<VT, AT, KL>::solve(ResInfo &info)
         // true residual
         const double r = own ? a.b[row] - a_row(a.xe) : 0.0;
         if (!meet()) return false; // the norms read last are no longer needed
-        publish_squares(r, partN);
+        publish_squares(r, partB);
         if (!meet()) return false;
-        const double beta = sqrt(agree(partN));
+        const double beta = sqrt(agree(partB));
         if (cycles > 0) {
             info.iterations += ls->kk;
             if (ls->status != GS2_OK) {
@@ -477,9 +558,9 @@ __device__ bool Team<VT, AT, KL>::solve(ResInfo &info)
         const int steps = min(m, a.maxit - info.iterations);
         // a new cycle: state, and the normalised residual as the first vector
         __syncthreads();
-        for (int k = t; k < GSTATE_SMALL_WORDS; k += RT) sh.sw[k] = 0ull;
+        for (int k = t; k < GSTATE_SMALL_WORDS; k += NT) sh.sw[k] = 0ull;
         __syncthreads();
-        for (int k = t; k < MAXM + 2; k += RT) ls->zs[k] = 1.0;
+        for (int k = t; k < MAXM + 2; k += NT) ls->zs[k] = 1.0;
         if (t == 0) {
             ls->status = GS2_OK;
             ls->maxsteps = steps;
@@ -488,8 +569,15 @@ __device__ bool Team<VT, AT, KL>::solve(ResInfo &info)
             ls->beta = beta;
             ls->g[0] = beta;
         }
-        if (own) put_u(r * (1.0 / beta));
+        if (own)
+            for (int tn = 0; tn < 2; ++tn) {
+                for (int q = 0; q <= a.ne; ++q) reset(ex(tn, q) + row);
+                reset(ze(tn) + row);
+            }
+        for (int k = t; k < 3 * (2 * m + 4); k += NT) reset(a.part + a.G + k * a.G + me);
         if (!meet()) return false;
+        if (own) put_u(r * (1.0 / beta), 0);
+        flip();
         bool ok = true;
         for (int j = 0;; ++j) {
             // the serial work that closes step j - 1, on one wavefront; unless
@@ -499,27 +587,34 @@ __device__ bool Team<VT, AT, KL>::solve(ResInfo &info)
             if (j > 0) {
                 if (wv == NW - 1)
                     dcgs_finish_wave(ls, H, m, sh.col, ok, sh.step[0], sh.step[1], sh.step[2],
-                                     ok ? total(partN, 0) : 0.0);
+                                     ok ? total(partN(j - 1)) : 0.0);
                 if (j == steps || !ok) {
                     __syncthreads();
                     break;
                 }
             }
-            if (!precondition(a.Z + (int64_t)j * n)) return false;
+            turn = j & 1;
+            if (NW * WAVE == RR || wv != NW - 1) precondition(a.Z + (int64_t)j * n);
+            __syncthreads();
             if (ls->done) break;
             // w = A z_j and u, scaled
             const double zsc = ls->zs[j];
-            sh.wl[t] = own ? zsc * a_row(a.ze) : 0.0;
-            sh.ul[t] = own ? zsc * u_own : 0.0;
+            const double ws = own ? zsc * a_row(ze(turn)) : 0.0;
+            if (NT == RR || t < RR) {
+                sh.wl[t] = ws;
+                sh.ul[t] = own ? zsc * sh.ul[t] : 0.0;
+            }
+            __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory"); // the resets, before anything is published
             __syncthreads();
+            double *const pq = partQ(j);
             // a = Q^T u, c = Q^T w, a column per wavefront in turn; the first
             // QW of them start with u.u, u.w, w.w (as block_multidot)
             if (wv < QW) {
                 double aa = 0.0, ab = 0.0, bb = 0.0;
 #pragma unroll
-                for (int q = 0; q < RES_ROWS / KT; ++q) {
-                    const double x = sh.ul[ln + (wv * (RES_ROWS / KT) + q) * WAVE];
-                    const double y = sh.wl[ln + (wv * (RES_ROWS / KT) + q) * WAVE];
+                for (int q = 0; q < RR / KT; ++q) {
+                    const double x = sh.ul[ln + (wv * (RR / KT) + q) * WAVE];
+                    const double y = sh.wl[ln + (wv * (RR / KT) + q) * WAVE];
                     aa = fma(x, x, aa);
                     ab = fma(x, y, ab);
                     bb = fma(y, y, bb);
@@ -536,9 +631,9 @@ __device__ bool Team<VT, AT, KL>::solve(ResInfo &info)
             for (int k = NW - 1 - wv; k < j; k += NW) {
                 const double *__restrict__ vk = a.V + (int64_t)k * n + r0;
                 double sa = 0.0, sb = 0.0;
-                constexpr int U = KL == 0 ? 8 : 4; // loads in flight
+                constexpr int U = std::min(RR / WAVE, 8); // loads in flight
 #pragma unroll 1
-                for (int q0 = 0; q0 < RES_ROWS / WAVE; q0 += U) {
+                for (int q0 = 0; q0 < RR / WAVE; q0 += U) {
                     double x[U];
 #pragma unroll
                     for (int q = 0; q < U; ++q) x[q] = vk[min(ln + (q0 + q) * WAVE, rows - 1)];
@@ -551,26 +646,24 @@ __device__ bool Team<VT, AT, KL>::solve(ResInfo &info)
                 sa = wave_sum(sa);
                 sb = wave_sum(sb);
                 if (ln == 0) {
-                    ast(partQ + k * a.G + me, sa);
-                    ast(partQ + (j + k) * a.G + me, sb);
+                    astf(pq + k * a.G + me, sa);
+                    astf(pq + (j + k) * a.G + me, sb);
                 }
             }
             __syncthreads();
             if (t < 3) {
                 double o = 0.0;
                 for (int q = 0; q < QW; ++q) o += sh.nrm[3 * q + t];
-                ast(partQ + (2 * j + t) * a.G + me, o);
+                astf(pq + (2 * j + t) * a.G + me, o);
             }
-            if (!meet()) return false;
-            for (int q0 = wv; q0 < 2 * j + 3; q0 += 4 * NW) { // four loads in flight
-                double o[4];
+            constexpr int PF = RR < 512 ? 8 : 4; // loads in flight
+            for (int q0 = wv; q0 < 2 * j + 3; q0 += PF * NW) {
+                double o[PF];
+                totals<PF>(pq, q0, NW, 2 * j + 2, o);
 #pragma unroll
-                for (int p = 0; p < 4; ++p)
-                    o[p] = ln < a.G ? ald(partQ + min(q0 + p * NW, 2 * j + 2) * a.G + ln) : 0.0;
-#pragma unroll
-                for (int p = 0; p < 4; ++p) {
+                for (int p = 0; p < PF; ++p) {
                     const int q = q0 + p * NW;
-                    const double v = wave_sum(o[p]);
+                    const double v = o[p];
                     if (ln == 0 && q < 2 * j + 3) {
                         if (q < j) ls->hA[q] = v;
                         else if (q < 2 * j) ls->hB[q - j] = v;
@@ -581,6 +674,12 @@ __device__ bool Team<VT, AT, KL>::solve(ResInfo &info)
                 }
             }
             __syncthreads();
+            // nobody needs the vectors of this step and the sums of the last one any more
+            if (own) {
+                for (int q = 0; q <= a.ne; ++q) reset(ex(turn, q) + row);
+                reset(ze(turn) + row);
+            }
+            for (int k = t; k < 2 * m + 4; k += NT) reset(partN(j + 2) + k * a.G + me);
             double alpha, e, a2;
             ok = reorth_scalars(ls, j, ls->hA, ls->hB, sh.sc, &alpha, &e, &a2);
             if (wv == NW - 1 && ln == 0) {
@@ -594,7 +693,7 @@ __device__ bool Team<VT, AT, KL>::solve(ResInfo &info)
             if (own) {
                 double aq = sh.ul[t], aw = sh.wl[t]; // rounded products, as the launches read them
                 const double *__restrict__ vr = a.V + row;
-                constexpr int U = KL == 0 ? 8 : 4; // loads in flight
+                constexpr int U = RR < 1024 ? 16 : 4; // loads in flight
                 for (int k = 0; k < j; k += U) {
                     double x[U];
 #pragma unroll
@@ -609,10 +708,10 @@ __device__ bool Team<VT, AT, KL>::solve(ResInfo &info)
                 const double qv = aq * (1.0 / alpha);
                 wp = aw - e * qv;
                 a.V[(int64_t)j * n + row] = qv;
-                put_u(wp);
+                put_u(wp, turn ^ 1);
             }
-            publish_squares(wp, partN);
-            if (!meet()) return false;
+            flip();
+            publish_squares(wp, partN(j));
         }
         __syncthreads();
         // y = R^{-1} g (as k_backsolve), x += Z y
@@ -628,24 +727,25 @@ __device__ bool Team<VT, AT, KL>::solve(ResInfo &info)
         }
         __syncthreads();
         if (own) {
+            double xv = ald(a.xe + row);
 #pragma unroll 8
             for (int k = 0; k < kk; ++k) xv += (ls->y[k] * ls->zs[k]) * a.Z[(int64_t)k * n + row];
             put(a.xe, xv);
         }
         if (!meet()) return false;
     }
-    if (own) a.x[row] = xv;
+    if (own) a.x[row] = ald(a.xe + row);
     return true;
 }
 
-template <typename VT, typename AT, int KL>
-__global__ __launch_bounds__(RT) void k_resident(ResArgs a)
+template <typename VT, typename AT, int KL, int RR>
+__global__ __launch_bounds__(threads_of(RR)) void k_resident(ResArgs a)
 {
     extern __shared__ double hl[];
-    __shared__ Shared sh;
-    const int t = threadIdx.x, r0 = (int)blockIdx.x * RES_ROWS;
-    Team<VT, AT, KL> T{a, sh, hl, (int)blockIdx.x, t, t / WAVE, t & (WAVE - 1), r0, min(RES_ROWS, a.n - r0), r0 + t,
-                       r0 + t < a.n, Mat{}, Mat{}, Mat{}};
+    __shared__ Shared<RR> sh;
+    const int t = threadIdx.x, r0 = (int)blockIdx.x * RR, rows = min(RR, a.n - r0);
+    Team<VT, AT, KL, RR> T{a, sh, hl, (int)blockIdx.x, t, __builtin_amdgcn_readfirstlane(t / WAVE), t & (WAVE - 1), r0, rows, r0 + t,
+                           t < rows, Mat{}, Mat{}, Mat{}};
     ResInfo info;
     const bool done = T.solve(info);
     if (t == 0) {
@@ -662,18 +762,30 @@ __global__ __launch_bounds__(RT) void k_resident(ResArgs a)
     }
 }
 
-template <typename VT, typename AT, int KL>
-int launch_lanes(ResArgs a, hipStream_t s)
+template <typename VT, typename AT, int KL, int RR>
+int launch_rows(ResArgs a, hipStream_t s)
 {
     // the Hessenberg matrix and as much of the rows as fits
     int dev = 0, most = 0;
     GS2_TRY_HIP(hipGetDevice(&dev));
     GS2_TRY_HIP(hipDeviceGetAttribute(&most, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-    a.lds = std::max((int)sizeof(double) * a.m * a.m, (most - (int)sizeof(Shared)) / 256 * 256);
-    GS2_TRY_HIP(hipFuncSetAttribute((const void *)k_resident<VT, AT, KL>, hipFuncAttributeMaxDynamicSharedMemorySize, a.lds));
-    k_resident<VT, AT, KL><<<(unsigned)a.G, RT, (size_t)a.lds, s>>>(a);
+    a.lds = std::max((int)sizeof(double) * a.m * a.m, (most - (int)sizeof(Shared<RR>)) / 256 * 256);
+    GS2_TRY_HIP(hipFuncSetAttribute((const void *)k_resident<VT, AT, KL, RR>, hipFuncAttributeMaxDynamicSharedMemorySize, a.lds));
+    k_resident<VT, AT, KL, RR><<<(unsigned)a.G, threads_of(RR), (size_t)a.lds, s>>>(a);
     GS2_TRY_HIP(hipGetLastError());
     return GS2_OK;
+}
+
+template <typename VT, typename AT, int KL>
+int launch_lanes(const ResArgs &a, hipStream_t s)
+{
+    switch (res_rows(a.n)) {
+    case 256: return launch_rows<VT, AT, KL, 256>(a, s);
+    case 512: return launch_rows<VT, AT, KL, 512>(a, s);
+    default:
+        if constexpr (KL < 2) return launch_rows<VT, AT, KL, 1024>(a, s);
+        return GS2_ERR_ARG; // res_lanes
+    }
 }
 
 template <typename VT, typename AT>

@@ -291,11 +291,11 @@ __device__ __forceinline__ void b3_rows(const DiaAView A, int64_t n, int64_t r0,
 
 // The product in the layout sel encodes (> 0 sliced ELL, K lanes per row;
 // -9..-1 the diagonal copy, -sel rows per lane; <= -10 the 3-row block copy).
-template <int SEL, int NW>
+template <int SEL, int NW, int ROWS = KRB>
 __device__ __forceinline__ void mat_rows(const SellAView A, const DiaAView D, int64_t n, int64_t r0,
                                          const double *__restrict__ z, double *ybuf)
 {
-    if constexpr (SEL > 0) sella_rows<SEL, KRB, NW>(A, n, r0, z, ybuf);
+    if constexpr (SEL > 0) sella_rows<SEL, ROWS, NW>(A, n, r0, z, ybuf);
     else if constexpr (SEL <= -10) b3_rows<NW>(D, n, r0, z, ybuf);
     else dia_rows<-SEL, NW>(D, n, r0, z, ybuf);
 }

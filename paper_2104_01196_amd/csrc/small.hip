@@ -42,19 +42,6 @@ namespace {
 constexpr long long SMALL_WAIT_TICKS = 200000000ll; // 2 s at 100 MHz
 constexpr int SMALL_LANES = 4; // most lanes per row whose sums are repeated
 
-template <typename AT>
-struct Word;
-template <>
-struct Word<double> {
-    typedef unsigned long long T;
-    static constexpr T not_ready = 0xfff8a5a5c3c30f0full;
-};
-template <>
-struct Word<float> {
-    typedef unsigned int T;
-    static constexpr T not_ready = 0xffc5a5c3u;
-};
-
 struct SmallArgs {
     const int *stop;
     int n, ne;
@@ -69,8 +56,8 @@ struct SmallArgs {
 
 template <typename VT, typename AT, int KL>
 struct SmallRow {
-    using BT = typename Word<AT>::T;
-    static constexpr BT NR = Word<AT>::not_ready;
+    using BT = typename Bits<AT>::T;
+    static constexpr BT NR = Bits<AT>::not_ready;
     static constexpr int U = 4; // entries of a row taken at a time
     static_assert(U % (1 << KL) == 0, "an entry's lane follows from its place among the U");
 
@@ -290,15 +277,14 @@ ResSell small_view(const Sell &T)
     return ResSell{T.slice_ptr, T.col, T.val, lk};
 }
 
-// vectors exchanged between the passes
+} // namespace
+
 int exchanged(bool jr, int sweeps, int inner, int variant)
 {
     const int64_t halves = (int64_t)sweeps * (!jr && variant == GS2_SYMMETRIC ? 2 : 1);
     const int64_t passes = jr || inner == 0 ? halves : halves * inner + halves - 1;
-    return (int)std::min<int64_t>(passes - 1, SMALL_MAX_EX + 1);
+    return (int)std::min<int64_t>(passes - 1, 1 << 20);
 }
-
-} // namespace
 
 size_t small_bytes(const Handle &h)
 {
@@ -316,8 +302,8 @@ void small_init(Handle &h, void *mem, hipStream_t s)
     h.ep = (unsigned *)((char *)mem + small_bytes(h) - aligned(4 * (size_t)nw));
     const unsigned g = (unsigned)((std::max<int64_t>(m, nw) + 255) / 256);
     if (h.precision == GS2_FP64)
-        k_small_reset<<<g, 256, 0, s>>>(m, (Word<double>::T *)mem, Word<double>::not_ready, nw, h.ep);
-    else k_small_reset<<<g, 256, 0, s>>>(m, (Word<float>::T *)mem, Word<float>::not_ready, nw, h.ep);
+        k_small_reset<<<g, 256, 0, s>>>(m, (Bits<double>::T *)mem, Bits<double>::not_ready, nw, h.ep);
+    else k_small_reset<<<g, 256, 0, s>>>(m, (Bits<float>::T *)mem, Bits<float>::not_ready, nw, h.ep);
 }
 
 bool small_apply(Handle &h, bool jr, int sweeps, double omega, const double *v, double *z, hipStream_t s)

@@ -281,19 +281,6 @@ __global__ void k_fill_zero(const int *__restrict__ stop, int64_t n, AT *__restr
 // it, row update) against 8 us for a launch per level.  96^3 Laplacian, 286
 // levels per half sweep, symmetric sweep: 4.57 ms with a launch per level,
 // 0.82 ms here.
-template <typename AT>
-struct Bits;
-template <>
-struct Bits<double> {
-    typedef unsigned long long T;
-    static constexpr T not_ready = 0xfff8a5a5c3c30f0full;
-};
-template <>
-struct Bits<float> {
-    typedef unsigned int T;
-    static constexpr T not_ready = 0xffc5a5c3u;
-};
-
 constexpr int TRI_TB = 256;
 constexpr long long TRI_WAIT_TICKS = 200000000ll; // 2 s at 100 MHz
 

@@ -19,9 +19,13 @@ DEV = "cuda"
 MATS = {
     "one_row": lambda: laplace1d(1),
     "chain_65": lambda: laplace1d(65),
-    "laplace3d_10": lambda: laplace3d(10),      # 1000 rows: one workgroup, a ragged wavefront
-    "poisson2d_32": lambda: poisson2d(32),      # 1024: exactly one workgroup
-    "poisson2d_33": lambda: poisson2d(33),      # 1089: a second one with 65 rows
+    "laplace3d_10": lambda: laplace3d(10),      # 1000 rows: a ragged wavefront
+    "chain_257": lambda: laplace1d(257),        # a second workgroup with one row
+    "poisson2d_32": lambda: poisson2d(32),      # 1024
+    "poisson2d_33": lambda: poisson2d(33),      # 1089
+    "poisson2d_128": lambda: poisson2d(128),    # 16384: the most rows at 256 per workgroup
+    "chain_16385": lambda: laplace1d(16385),    # at 512
+    "chain_32769": lambda: laplace1d(32769),    # at 1024, a last workgroup of one row
     "vardiff3d_23": lambda: vardiff3d(23, seed=4),
     "convdiff_101": lambda: convdiff2d(101, 30.0, 1.0),
     "random_3000": lambda: random_sparse(3000, seed=3, avg_offdiag=6, long_rows=3, long_len=60, neg_diag_rows=40),
