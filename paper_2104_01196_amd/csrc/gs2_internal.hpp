@@ -247,12 +247,17 @@ struct Dia {
 // col >= 0 marks a main entry, ~col another one, PERM_PAD the end.  In the
 // orders by level a main entry's col is the position of its row in the same
 // order: neighbours in a level tend to need neighbours in the one before it.
+// The order by color, whose entries are all alike, holds 16-bit offsets instead
+// of columns where col - row - off_min fits (PERM_PAD16 the end).
 constexpr int32_t PERM_PAD = INT32_MIN;
+constexpr uint16_t PERM_PAD16 = 0xffff;
 struct Perm {
     int64_t nchunks = 0;
     int32_t *rows = nullptr; // 64 nchunks row indices, -1 for none
     int64_t *ptr = nullptr;  // nchunks + 1
     int32_t *col = nullptr;
+    uint16_t *off = nullptr; // in place of col
+    int off_min = 0;
     void *val = nullptr;
 };
 

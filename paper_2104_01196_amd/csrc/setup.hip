@@ -883,7 +883,7 @@ static int read_err(int *err, hipStream_t s)
 
 void free_perm(Perm &P)
 {
-    for (void *p : {(void *)P.rows, (void *)P.ptr, (void *)P.col, P.val})
+    for (void *p : {(void *)P.rows, (void *)P.ptr, (void *)P.col, (void *)P.off, P.val})
         if (p) (void)hipFree(p);
     P = Perm{};
 }
@@ -912,7 +912,8 @@ __global__ __launch_bounds__(256) void k_perm_fill(int64_t nchunks, const int32_
                                                    const int32_t *__restrict__ lcnt, int lower,
                                                    const int32_t *__restrict__ place,
                                                    const double *__restrict__ sl, const double *__restrict__ sr,
-                                                   int32_t *__restrict__ col, VT *__restrict__ val)
+                                                   int32_t *__restrict__ col, uint16_t *__restrict__ off, int off_min,
+                                                   VT *__restrict__ val)
 {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t c = g / WAVE;
@@ -927,22 +928,26 @@ __global__ __launch_bounds__(256) void k_perm_fill(int64_t nchunks, const int32_
     for (int t = 0; t < steps; ++t) {
         const int64_t pos = beg + (int64_t)t * WAVE + g % WAVE;
         if (t >= tot) {
-            col[pos] = PERM_PAD;
+            if (off) off[pos] = PERM_PAD16;
+            else col[pos] = PERM_PAD;
             val[pos] = VT(0);
             continue;
         }
         const bool low = lower ? t < mc : t >= mc;
         const int k = b + (low ? (lower ? t : t - mc) : lc + 1 + (lower ? t - mc : t));
         const int j = ci[k];
-        col[pos] = t >= mc ? ~j : place ? place[j] : j;
+        if (off) off[pos] = (uint16_t)(j - i - off_min);
+        else col[pos] = t >= mc ? ~j : place ? place[j] : j;
         val[pos] = convert_scaled<VT>((srow * va[k]) * sr[j], &ovf);
     }
 }
 
 // The rows in the given order (-1: no row), 64 per chunk, with their entries;
-// by_place: the main entries name positions of this order instead of rows.
+// by_place: the main entries name positions of this order instead of rows;
+// span: the pattern's smallest and largest col - row, for 16-bit offsets where
+// they fit (null: columns).
 static int build_perm(Handle &h, Perm &P, std::vector<int32_t> &order, int lower, bool by_place, const gs2_csr &A,
-                      const int32_t *lcnt, hipStream_t s)
+                      const int32_t *lcnt, const Pattern *span, hipStream_t s)
 {
     struct Tmp {
         int32_t *place = nullptr;
@@ -973,18 +978,23 @@ static int build_perm(Handle &h, Perm &P, std::vector<int32_t> &order, int lower
     GS2_TRY_HIP(hipMemcpyAsync(&total, P.ptr + P.nchunks, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     GS2_TRY_HIP(hipStreamSynchronize(s)); // `order` may go
     const size_t vb = h.precision == GS2_FP64 ? 8 : h.precision == GS2_FP32 ? 4 : 2;
-    GS2_TRY_HIP(hipMalloc(&P.col, sizeof(int32_t) * std::max<int64_t>(total, WAVE)));
+    if (span && (int64_t)span->hi - span->lo < PERM_PAD16) {
+        P.off_min = span->lo;
+        GS2_TRY_HIP(hipMalloc(&P.off, sizeof(uint16_t) * std::max<int64_t>(total, WAVE)));
+    } else {
+        GS2_TRY_HIP(hipMalloc(&P.col, sizeof(int32_t) * std::max<int64_t>(total, WAVE)));
+    }
     GS2_TRY_HIP(hipMalloc(&P.val, vb * std::max<int64_t>(total, WAVE)));
     const unsigned g = (unsigned)((P.nchunks * WAVE + 255) / 256);
     if (h.precision == GS2_FP64)
         k_perm_fill<double><<<g, 256, 0, s>>>(P.nchunks, P.rows, P.ptr, A.rowptr, A.colind, A.val, lcnt, lower,
-                                              tmp.place, h.sl, h.sr, P.col, (double *)P.val);
+                                              tmp.place, h.sl, h.sr, P.col, P.off, P.off_min, (double *)P.val);
     else if (h.precision == GS2_FP32)
         k_perm_fill<float><<<g, 256, 0, s>>>(P.nchunks, P.rows, P.ptr, A.rowptr, A.colind, A.val, lcnt, lower,
-                                             tmp.place, h.sl, h.sr, P.col, (float *)P.val);
+                                             tmp.place, h.sl, h.sr, P.col, P.off, P.off_min, (float *)P.val);
     else
         k_perm_fill<_Float16><<<g, 256, 0, s>>>(P.nchunks, P.rows, P.ptr, A.rowptr, A.colind, A.val, lcnt, lower,
-                                                tmp.place, h.sl, h.sr, P.col, (_Float16 *)P.val);
+                                                tmp.place, h.sl, h.sr, P.col, P.off, P.off_min, (_Float16 *)P.val);
     GS2_TRY_HIP(hipGetLastError());
     GS2_TRY_HIP(hipStreamSynchronize(s)); // tmp goes with this scope
     return GS2_OK;
@@ -996,7 +1006,7 @@ static int build_perm(Handle &h, Perm &P, std::vector<int32_t> &order, int lower
 // nonzero).  Rows are then grouped color by color, each color from a chunk
 // of its own.
 static int build_colors(Handle &h, const gs2_csr &A, const int32_t *lcnt, const std::vector<int32_t> &rp,
-                        const std::vector<int32_t> &ci, hipStream_t s)
+                        const std::vector<int32_t> &ci, const Pattern &span, hipStream_t s)
 {
     const int64_t n = h.n;
     // transpose pattern (column -> rows), to see couplings a_ji from earlier rows j
@@ -1027,7 +1037,7 @@ static int build_colors(Handle &h, const gs2_csr &A, const int32_t *lcnt, const 
     }
     std::vector<int32_t> rows(ptr[ncol] * WAVE, -1);
     for (int64_t i = 0; i < n; ++i) rows[pos[color[i]]++] = (int32_t)i;
-    GS2_TRY(build_perm(h, h.PC, rows, 1, false, A, lcnt, s));
+    GS2_TRY(build_perm(h, h.PC, rows, 1, false, A, lcnt, &span, s));
     h.ncolors = ncol;
     h.color_ptr = std::move(ptr);
     return GS2_OK;
@@ -1036,7 +1046,7 @@ static int build_colors(Handle &h, const gs2_csr &A, const int32_t *lcnt, const 
 // Level sets of the DAGs of L (ascending) and U (descending), computed on the
 // host from a copy of the pattern: level_i = 1 + max level over the
 // triangle's entries of row i.  Rows are then grouped level by level.
-static int build_levels(Handle &h, const gs2_csr &A, const int32_t *lcnt, hipStream_t s)
+static int build_levels(Handle &h, const gs2_csr &A, const int32_t *lcnt, const Pattern &span, hipStream_t s)
 {
     const int64_t n = A.n;
     std::vector<int32_t> rp(n + 1), ci(A.nnz);
@@ -1062,10 +1072,10 @@ static int build_levels(Handle &h, const gs2_csr &A, const int32_t *lcnt, hipStr
         for (int l = 0; l < nlev; ++l) pos[l + 1] += pos[l];
         std::vector<int32_t> rows(n);
         for (int64_t i = 0; i < n; ++i) rows[pos[lev[i]]++] = (int32_t)i;
-        GS2_TRY(build_perm(h, lower ? h.PL : h.PU, rows, lower, true, A, lcnt, s));
+        GS2_TRY(build_perm(h, lower ? h.PL : h.PU, rows, lower, true, A, lcnt, nullptr, s));
         (lower ? h.nlev_l : h.nlev_u) = nlev;
     }
-    return build_colors(h, A, lcnt, rp, ci, s);
+    return build_colors(h, A, lcnt, rp, ci, span, s);
 }
 
 // The scaling vectors and, with work, the applies' temporaries.
@@ -1141,7 +1151,7 @@ int setup_handle(Handle &h, const gs2_csr &A, const gs2_options &o, hipStream_t 
     GS2_TRY(choose_format(h, A, o, sc, flush, s, can_time, shape));
     if (h.blocks > 1) GS2_TRY(build_parts(h, PART_E, PART_E, K, A, sc, s));
     GS2_TRY(read_err(sc.err, s));
-    if (o.build_levels) GS2_TRY(build_levels(h, A, sc.lcnt, s));
+    if (o.build_levels) GS2_TRY(build_levels(h, A, sc.lcnt, sc.pat, s));
     GS2_TRY_HIP(hipStreamSynchronize(s));
     return GS2_OK;
 }

@@ -396,14 +396,16 @@ __global__ void k_tri_begin(const int *__restrict__ stop, int64_t n, AT *__restr
 // so they update in place from the current iterate,
 //   x_i = (1 - w) x_i + w (S_l v_i - sum_{j != i} ah_ij x_j)   (scaled space).
 // xzero: the whole iterate is still zero and is not gathered; z: the row's
-// last update, written out as S_r x as well.  Bandwidth-bound; with the rows
-// picked out of the natural-order triangles each pass moved the lines of
-// every color (151 x 140 x 133, float32, two sweeps of two colors: 171 us,
-// 122 us by color).
-template <typename VT, typename AT>
+// last update, written out as S_r x as well.  r: S_l v, formed once per apply
+// (k_color_begin).  Bandwidth-bound.  Two sweeps of two colors on 151 x 140 x
+// 133 points in float32: 171 us with the rows picked out of the natural-order
+// triangles, where each pass moved the lines of every color, 122 by color, and
+// 114 with 16-bit offsets and without v and s_l (16 bytes of a row, of whose
+// lines a color uses a part) in every pass.
+template <typename VT, typename AT, bool OFF>
 __global__ __launch_bounds__(256) void k_color(const int *__restrict__ stop, int64_t c0, int64_t c1, Perm P, int xzero,
-                                               AT *x, const double *__restrict__ v, const double *__restrict__ sl,
-                                               AT w, double *__restrict__ z, const double *__restrict__ sr)
+                                               AT *x, const AT *__restrict__ r, AT w, double *__restrict__ z,
+                                               const double *__restrict__ sr)
 {
     if (stop && *stop) return;
     const int lane = threadIdx.x & (WAVE - 1);
@@ -413,6 +415,7 @@ __global__ __launch_bounds__(256) void k_color(const int *__restrict__ stop, int
     const int64_t beg = P.ptr[ch];
     const int steps = xzero ? 0 : (int)((P.ptr[ch + 1] - beg) / WAVE);
     const VT *__restrict__ val = (const VT *)P.val;
+    const AT ri = i < 0 ? AT(0) : r[i], xi = i < 0 ? AT(0) : x[i];
     AT acc = AT(0);
     constexpr int U = 6;
     for (int t = 0; t < steps; t += U) {
@@ -422,17 +425,35 @@ __global__ __launch_bounds__(256) void k_color(const int *__restrict__ stop, int
         for (int q = 0; q < U; ++q) {
             const bool in = t + q < steps;
             const int64_t p = beg + (int64_t)(in ? t + q : 0) * WAVE + lane;
-            cc[q] = in ? P.col[p] : PERM_PAD;
+            if constexpr (OFF) {
+                const uint16_t o = in ? P.off[p] : PERM_PAD16;
+                cc[q] = o != PERM_PAD16 ? i + P.off_min + (int)o : -1;
+            } else {
+                const int c = in ? P.col[p] : PERM_PAD;
+                cc[q] = c == PERM_PAD ? -1 : c < 0 ? ~c : c;
+            }
             a[q] = in ? (AT)val[p] : AT(0);
         }
 #pragma unroll
         for (int q = 0; q < U; ++q)
-            if (cc[q] != PERM_PAD) acc += a[q] * x[cc[q] < 0 ? ~cc[q] : cc[q]];
+            if (cc[q] >= 0) acc += a[q] * x[cc[q]];
     }
     if (i < 0) return;
-    const AT xn = (AT(1) - w) * x[i] + w * ((AT)(v[i] * sl[i]) - acc);
+    const AT xn = (AT(1) - w) * xi + w * (ri - acc);
     x[i] = xn;
     if (z) z[i] = sr[i] * (double)xn;
+}
+
+// what a multicolor apply starts from: x = 0, r = S_l v
+template <typename AT>
+__global__ void k_color_begin(const int *__restrict__ stop, int64_t n, const double *__restrict__ v,
+                              const double *__restrict__ sl, AT *__restrict__ x, AT *__restrict__ r)
+{
+    if (stop && *stop) return;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    x[i] = AT(0);
+    r[i] = (AT)(v[i] * sl[i]);
 }
 
 // ------------------------------------------------ diagonal-interleaved passes
@@ -1345,7 +1366,8 @@ struct Launch {
     {
         AT *x = (AT *)h.xh;
         const int per = variant == GS2_SYMMETRIC ? 2 : 1, H = h.sweeps * per;
-        k_fill_zero<AT><<<grid_rows(h.n), TB, 0, s>>>(h.stop, h.n, x);
+        AT *const r = (AT *)h.rh;
+        k_color_begin<AT><<<grid_rows(h.n), TB, 0, s>>>(h.stop, h.n, v, h.sl, x, r);
         for (int t = 0; t < H; ++t) {
             const bool fwd = variant == GS2_FORWARD || (variant == GS2_SYMMETRIC && t % 2 == 0);
             for (int q = 0; q < h.ncolors; ++q) {
@@ -1353,8 +1375,12 @@ struct Launch {
                 const int64_t c0 = h.color_ptr[c], c1 = h.color_ptr[c + 1];
                 const int xzero = t == 0 && q == 0;
                 Prof pr(s, PK_TRI, (double)(c1 - c0) * WAVE * (16.0 + 2 * sizeof(AT)));
-                k_color<VT, AT><<<(unsigned)((c1 - c0 + TB / WAVE - 1) / (TB / WAVE)), TB, 0, s>>>(
-                    h.stop, c0, c1, h.PC, xzero, x, v, h.sl, (AT)omega, t == H - 1 ? z : nullptr, h.sr);
+                const unsigned g = (unsigned)((c1 - c0 + TB / WAVE - 1) / (TB / WAVE));
+                double *const out = t == H - 1 ? z : nullptr;
+                if (h.PC.off)
+                    k_color<VT, AT, true><<<g, TB, 0, s>>>(h.stop, c0, c1, h.PC, xzero, x, r, (AT)omega, out, h.sr);
+                else
+                    k_color<VT, AT, false><<<g, TB, 0, s>>>(h.stop, c0, c1, h.PC, xzero, x, r, (AT)omega, out, h.sr);
             }
         }
         return GS2_OK;

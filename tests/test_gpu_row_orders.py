@@ -17,6 +17,18 @@ from gen import laplace1d, poisson2d, random_sparse  # noqa: E402
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
 
+
+def ring(n):
+    """A chain whose last row is coupled to the first: columns up to n - 1 rows
+    away, so that 16-bit offsets hold them up to n = 32768 only."""
+    from gen import CSR
+
+    i = np.arange(n)
+    cols = np.sort(np.stack([(i - 1) % n, i, (i + 1) % n], 1), 1)
+    val = np.where(cols == i[:, None], 4.0, -1.0)
+    return CSR(n, np.arange(0, 3 * n + 1, 3).astype(np.int32), cols.ravel().astype(np.int32), val.ravel())
+
+
 MATS = {
     "one_row": (lambda: laplace1d(1), [g.FP64]),
     "chain_63": (lambda: laplace1d(63), [g.FP64]),
@@ -26,6 +38,8 @@ MATS = {
     "plane_23": (lambda: poisson2d(23), [g.FP64, g.FP32, g.FP16_SCALED]),
     "ragged_515": (lambda: random_sparse(515, seed=31, avg_offdiag=5, long_rows=3, long_len=90, diag_only_rows=20),
                    [g.FP64]),
+    "ring_32768": (lambda: ring(32768), [g.FP64, g.FP32]),
+    "ring_32769": (lambda: ring(32769), [g.FP64, g.FP32]),
 }
 
 
