@@ -39,7 +39,9 @@ namespace gs2 {
 
 namespace {
 
-constexpr long long SMALL_WAIT_TICKS = 200000000ll; // 2 s at 100 MHz
+// Looks before a wait is given up, half a microsecond or more each (counted, not
+// timed: a process that shares the device may be set aside for any time).
+constexpr unsigned SMALL_WAIT_POLLS = 1u << 22;
 constexpr int SMALL_LANES = 4; // most lanes per row whose sums are repeated
 
 struct SmallArgs {
@@ -130,7 +132,6 @@ struct SmallRow {
             return;
         }
         BT b[U];
-        long long t0 = 0;
         unsigned polls = 0;
         for (;;) {
             bool ready = true;
@@ -139,12 +140,7 @@ struct SmallRow {
                 b[q] = __hip_atomic_load(src + c[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
             for (int q = 0; q < U; ++q) ready = ready && b[q] != NR;
-            if (ready) break;
-            if ((++polls & 255u) == 0u) {
-                const long long now = wall_clock64();
-                if (t0 == 0) t0 = now;
-                else if (now - t0 > SMALL_WAIT_TICKS) break;
-            }
+            if (ready || ++polls > SMALL_WAIT_POLLS) break;
         }
 #pragma unroll
         for (int q = 0; q < U; ++q) x[q] = __builtin_bit_cast(AT, b[q]);

@@ -274,15 +274,16 @@ __global__ void k_fill_zero(const int *__restrict__ stop, int64_t n, AT *__restr
 // sweep.  A row only waits on chunks handed out before its own, so a wavefront that waits always
 // waits on running ones, however few are resident; rows of one wavefront may
 // depend on each other, so the store sits inside the polling loop, which all
-// lanes leave together.  The wait is bounded all the same (TRI_WAIT_TICKS of
-// the wall clock; the pattern then passes on as NaN).
+// lanes leave together.  The wait is bounded all the same (TRI_WAIT_POLLS looks,
+// counted and not timed, as a process that shares the device may be set aside;
+// the pattern then passes on as NaN).
 //
 // What bounds it is the chain of levels: 1.4 us each (store, load that sees
 // it, row update) against 8 us for a launch per level.  96^3 Laplacian, 286
 // levels per half sweep, symmetric sweep: 4.57 ms with a launch per level,
 // 0.82 ms here.
 constexpr int TRI_TB = 256;
-constexpr long long TRI_WAIT_TICKS = 200000000ll; // 2 s at 100 MHz
+constexpr unsigned TRI_WAIT_POLLS = 1u << 22; // looks, half a microsecond or more each
 
 template <typename VT, typename AT>
 __global__ __launch_bounds__(TRI_TB) void k_tri_sweep(const int *__restrict__ stop, int64_t n, Perm P,
@@ -337,7 +338,7 @@ __global__ __launch_bounds__(TRI_TB) void k_tri_sweep(const int *__restrict__ st
         load(cur, 0);
         load(nxt, U);
         bool open = i >= 0;
-        const long long t0 = wall_clock64();
+        unsigned polls = 0;
         while (__any(open)) {
             bool ready = open;
             if (open) {
@@ -375,7 +376,7 @@ __global__ __launch_bounds__(TRI_TB) void k_tri_sweep(const int *__restrict__ st
             }
             if (!__any(ready)) {
                 __builtin_amdgcn_s_sleep(1);
-                late = late || wall_clock64() - t0 > TRI_WAIT_TICKS;
+                late = late || ++polls > TRI_WAIT_POLLS;
             }
         }
     }
