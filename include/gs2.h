@@ -128,7 +128,7 @@ typedef struct gs2_options {
                            /* default 50, also without a handle; < 0 = never)*/
     int spmv_format;      /* gmres_solve with this handle: layout of the     */
                           /* solver's copy of A for w = A z: GS2_FORMAT_AUTO */
-                          /* (0: timed once per pattern on >= 65536 rows --  */
+                          /* (0: timed once per shape on >= 65536 rows --    */
                           /* sliced ELL at two lane counts, diagonal copy at */
                           /* 1 and 2 rows per lane when A qualifies --, else */
                           /* or, for n = 3 x nodes with <= 32 node offsets  */
@@ -140,7 +140,7 @@ typedef struct gs2_options {
                           /* qualify                                         */
     int basis_loads;      /* gmres_solve with this handle: loads in flight   */
                           /* of the delayed passes over the Krylov basis:    */
-                          /* 0 = timed once per workspace (bases of 2^20     */
+                          /* 0 = timed once per size class (bases of 2^20    */
                           /* rows and more, else wide), 1 = wide groups at   */
                           /* every step, 2 = narrow groups from the          */
                           /* crossover steps (even row counts; wide where    */
@@ -248,7 +248,9 @@ int mtgs_apply(gs2_handle *h, int variant, double damping, const double *v, doub
  * per restart cycle and before returning.  With a handle, a restart cycle is
  * captured once into a HIP graph (keyed by A, b, x, handle, kind, restart,
  * step count, rtol) and replayed (see gs2_graphs; not while gs2_profile is
- * on).  Returns GS2_OK,
+ * on); a system of at most 65536 rows with one lane per row of A, no
+ * preconditioner, GS2 or JR and restart <= 64 is solved in one launch instead,
+ * with the same bits (not while gs2_profile is on).  Returns GS2_OK,
  * GS2_NOT_CONVERGED (maxit reached), GS2_BREAKDOWN_EXACT, GS2_STAGNATED (the
  * true residual at the end of a restart cycle has not halved for the
  * handle's stagnation_cycles cycles, 50 by default), or an error; `info`
