@@ -401,7 +401,7 @@ __global__ void k_tri_begin(const int *__restrict__ stop, int64_t n, AT *__restr
 // (k_color_begin).  Bandwidth-bound.  Two sweeps of two colors on 151 x 140 x
 // 133 points in float32: 171 us with the rows picked out of the natural-order
 // triangles, where each pass moved the lines of every color, 122 by color, and
-// 114 with 16-bit offsets and without v and s_l (16 bytes of a row, of whose
+// 108 with 16-bit offsets and without v and s_l (16 bytes of a row, of whose
 // lines a color uses a part) in every pass.
 template <typename VT, typename AT, bool OFF>
 __global__ __launch_bounds__(256) void k_color(const int *__restrict__ stop, int64_t c0, int64_t c1, Perm P, int xzero,
@@ -435,9 +435,12 @@ __global__ __launch_bounds__(256) void k_color(const int *__restrict__ stop, int
             }
             a[q] = in ? (AT)val[p] : AT(0);
         }
+        AT g[U]; // all gathers issued before the first sum (one by one: 114 us)
+#pragma unroll
+        for (int q = 0; q < U; ++q) g[q] = x[max(cc[q], 0)];
 #pragma unroll
         for (int q = 0; q < U; ++q)
-            if (cc[q] >= 0) acc += a[q] * x[cc[q]];
+            if (cc[q] >= 0) acc += a[q] * g[q];
     }
     if (i < 0) return;
     const AT xn = (AT(1) - w) * xi + w * (ri - acc);
