@@ -312,7 +312,7 @@ static int cg_impl(const gs2_csr &A, const double *b, double *x, double rtol, in
     // With a handle, which lives on, the products run on a copy of A in the
     // layout that suits it (as gmres_solve's): 20 against 46 us per
     // product on a 120^3 7-point matrix.  On the CSR arrays where there is no
-    // handle, no memory for a copy, or rows that are not strictly sorted.
+    // handle, no memory for a copy, or rows that are no longer strictly sorted.
     bool copied = P != nullptr;
     auto copy = [&]() -> int {
         const int e = prepare_product(W->prod, A, P->h.spmv_fmt, s, &st->flag);

@@ -340,7 +340,8 @@ int64_t scan_tmp(int64_t m);
 // and largest col - row, the distinct col - row (0 among them if a diagonal
 // entry exists) and, for n a multiple of 3, the distinct node offsets
 // c/3 - r/3 below and above the diagonal; all ascending.  many_d / many_b:
-// more than two triangles of DIA_MAX could hold, lists not complete.
+// more than two triangles of DIA_MAX could hold, lists not complete; nor are
+// they where err is set (an entry whose column does not increase is left out).
 struct Pattern {
     int err = 0, maxlen = 0, lo = 0, hi = 0;
     int64_t nl = 0, nu = 0;

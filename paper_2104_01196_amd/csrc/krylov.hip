@@ -1210,7 +1210,8 @@ static int build_layout(SellA &S, const gs2_csr &A, int sel, const std::vector<i
 // SPMV_TUNE_MIN_ROWS rows, once per shape in the process (as the sweep
 // schedules); GS2_FORMAT_SELL / _DIA / _BLOCK3 force a layout
 // (the diagonal one at two rows per lane, the block one at two nodes per
-// lane, falling back to sliced ELL when A does not qualify).
+// lane, falling back to sliced ELL when A does not qualify).  Rows that are
+// not strictly sorted never qualify.
 int prepare_product(Product &W, const gs2_csr &A, int fmt, hipStream_t s, int *flag)
 {
     SellA &S = W.A;
@@ -1222,8 +1223,11 @@ int prepare_product(Product &W, const gs2_csr &A, int fmt, hipStream_t s, int *f
     std::vector<int> offs;
     Pattern pat;
     if (fmt != GS2_FORMAT_SELL) GS2_TRY(scan_pattern(A, nullptr, nullptr, nullptr, nullptr, W.pat, pat, s));
-    const bool dia_ok = fmt != GS2_FORMAT_SELL && fmt != GS2_FORMAT_BLOCK3 && sella_dia_offsets(A, pat, offs);
-    const bool b3_ok = !dia_ok && fmt != GS2_FORMAT_SELL && fmt != GS2_FORMAT_DIA && sella_b3_offsets(A, pat, offs);
+    // where columns do not increase the scan's offset lists are not complete,
+    // and a column may come twice: only sliced ELL holds every entry
+    const bool sorted = fmt != GS2_FORMAT_SELL && !pat.err;
+    const bool dia_ok = sorted && fmt != GS2_FORMAT_BLOCK3 && sella_dia_offsets(A, pat, offs);
+    const bool b3_ok = sorted && !dia_ok && fmt != GS2_FORMAT_DIA && sella_b3_offsets(A, pat, offs);
     const int K0 = sella_rule_lanes(A);
     int sel = K0, tuned = 0;
     const std::string key = "A_" + shape_key(A.n, (double)A.nnz / (double)A.n, pat.maxlen, GS2_FP64) + "_d" +
