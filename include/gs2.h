@@ -316,6 +316,14 @@ int gs2_inner_residuals(gs2_handle *h, const double *r, int inner, double *out, 
 #define GS2_NOALLOC_SCRATCH_DOUBLES 524288
 int gs2_inner_residuals_noalloc(gs2_handle *h, const double *r, int inner, double *out, void *stream);
 
+/*
+ * Longest wait between the wavefronts of a one-launch apply on this handle (systems
+ * of at most 65536 rows), in looks at memory; < 0 = the default.  A wavefront
+ * that has waited that long forms what it waits for itself, so the result does
+ * not depend on it.  For tests.  Errors: GS2_ERR_ARG.
+ */
+int gs2_wait_looks(gs2_handle *h, int looks);
+
 /* Free a handle (NULL is ignored).  Synchronises the device. */
 void gs2_destroy(gs2_handle *h);
 

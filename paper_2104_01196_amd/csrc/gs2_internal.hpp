@@ -311,6 +311,7 @@ struct Handle {
     int ne = 0;
     void *ex = nullptr;
     unsigned *ep = nullptr;
+    int wait_looks = -1; // looks before a wait between wavefronts ends (< 0: the default)
     GmresWork *gw = nullptr;
     CgWork *cw = nullptr;
     const int *stop = nullptr; // device flag: kernels return at once when set (GMRES)

@@ -16,10 +16,15 @@
 // turn is counted per wavefront on the device, so that an apply replayed from
 // a graph takes its turn too.
 //
-// The wavefronts wait for each other, so all of an apply have to run at once:
-// SMALL_MAX_N rows are SMALL_MAX_N / 64 wavefronts of at most 128 registers, of
-// which the chip holds 4096; other kernels only delay that.  The waits are
-// bounded all the same (the pattern then passes on as NaN).
+// The wavefronts wait for each other, and nothing makes all of an apply run at
+// once: other kernels may hold the compute units that the rest of it needs, for
+// seconds or, where they are such applies too, until this one is done.  So a
+// wavefront waits for SMALL_WAIT_POLLS looks only.  It then forms what it waits for
+// itself, vector by vector and every entry that is not there yet (complete()), and
+// starts over with its own rows, which find all they need.  An entry's bits do not
+// depend on who forms it, and formed twice it is stored twice alike; a wavefront
+// that gets to run only now finds the entries there.  One wavefront alone could do
+// the whole apply.
 //
 // Sums, roundings and therefore every bit are those of the passes launched one
 // by one (sweep.hip: Launch::gs2 and Launch::jr), for which fused operations
@@ -28,8 +33,9 @@
 // Enqueued one after the other, SGS2(1,1) in float64 (a call, in us): 11.6
 // pass by pass and 6.5 in one launch on 64 x 64 points, 11.9 and 6.8 on 256 x
 // 256; GS2(2,2) in float32 19.6 and 7.4, 19.2 and 8.5.  What is left is the
-// host's time to enqueue one launch.  More rows would gain too, but wavefronts
-// that wait for each other have to fit next to those of other streams.
+// host's time to enqueue one launch, which the way out of a wait leaves as it was
+// (64 x 64 points, 7.0 us a call with it and without).  More rows would gain too, but
+// wavefronts that wait for each other should fit next to those of other streams.
 #include <algorithm>
 
 #include "gs2_internal.hpp"
@@ -39,9 +45,12 @@ namespace gs2 {
 
 namespace {
 
-// Looks before a wait is given up, half a microsecond or more each (counted, not
-// timed: a process that shares the device may be set aside for any time).
-constexpr unsigned SMALL_WAIT_POLLS = 1u << 22;
+// Looks before a wavefront goes on by itself, half a microsecond or more each
+// (counted, not timed: a process that shares the device may be set aside for any
+// time): 16 ms, about what forming all vectors of the most rows takes it.
+constexpr unsigned SMALL_WAIT_POLLS = 1u << 15;
+// In complete() every entry waited for is stored already; a bound all the same.
+constexpr unsigned SMALL_STORED_POLLS = 1u << 22;
 constexpr int SMALL_LANES = 4; // most lanes per row whose sums are repeated
 
 struct SmallArgs {
@@ -54,6 +63,7 @@ struct SmallArgs {
     double *z;
     void *ex;     // two sets of ne vectors
     unsigned *ep; // applies done, per wavefront
+    unsigned looks; // before a wait ends
 };
 
 template <typename VT, typename AT, int KL>
@@ -66,6 +76,8 @@ struct SmallRow {
     const SmallArgs &a;
     int row;
     bool own;
+    unsigned looks;
+    bool late = false; // a wait has ended without what it waited for
 
     // a triangle's row: entry k at p = at + (k >> lk) 64 + (k mod 2^lk), the
     // first U of them held (the last one repeated where there are fewer)
@@ -124,7 +136,7 @@ struct SmallRow {
     };
 
     // an exchanged vector (its entries once they are there), or S_l v
-    __device__ void gather(const BT *src, const int *c, AT *x) const
+    __device__ void gather(const BT *src, const int *c, AT *x)
     {
         if (!src) {
 #pragma unroll
@@ -140,13 +152,14 @@ struct SmallRow {
                 b[q] = __hip_atomic_load(src + c[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
             for (int q = 0; q < U; ++q) ready = ready && b[q] != NR;
-            if (ready || ++polls > SMALL_WAIT_POLLS) break;
+            if (ready || late) break;
+            late = ++polls > looks;
         }
 #pragma unroll
         for (int q = 0; q < U; ++q) x[q] = __builtin_bit_cast(AT, b[q]);
     }
 
-    __device__ void dot(const Row &R, Sums &acc, const BT *src) const
+    __device__ void dot(const Row &R, Sums &acc, const BT *src)
     {
         for (int e = 0; e < R.cnt; e += U) {
             int c[U];
@@ -168,15 +181,61 @@ struct SmallRow {
         }
     }
 
-    __device__ void run()
+    // what the passes form of a row: the residual S_l v - ... of a half sweep after
+    // the first, and the next inner iterate (T: the triangle that the half sweep
+    // solves with, O: the other one)
+    __device__ AT residual(const Row &T, const Row &O, const BT *src, AT sv, AT x_own)
     {
-        const unsigned turn = a.ep[blockIdx.x];
-        BT *set = (BT *)a.ex + (size_t)(turn & 1u) * a.ne * a.n;
-        BT *other = (BT *)a.ex + (size_t)(~turn & 1u) * a.ne * a.n;
+        const bool compact = !a.jr && a.compact;
+        const AT cdiag = compact ? (AT)(1.0 - 1.0 / a.omega) : AT(1);
+        Sums acc;
+        if (!compact) dot(T, acc, src);
+        dot(O, acc, src);
+        return fma(-cdiag, x_own, sv) - acc.total();
+    }
+    __device__ AT relax(const Row &T, const BT *src, AT r, AT old)
+    {
+        const AT w = (AT)a.omega, gamma = (AT)a.gamma;
+        Sums acc;
+        dot(T, acc, src);
+        AT g = fma(-w, acc.total(), r);
+        if (a.gamma != 1.0) g = fma(gamma, g, (AT(1) - gamma) * old);
+        return g;
+    }
+    // x <- w g (fresh: x is zero or replaced) or x + w g
+    __device__ AT updated(bool fresh, AT x_own, AT g) const
+    {
+        const AT w = (AT)a.omega;
+        return fresh ? w * g : fma(w, g, x_own);
+    }
+    __device__ AT scaled_v() const { return own ? (AT)(a.v[row] * a.sl[row]) : AT(0); }
+    __device__ void store(BT *vec, AT x) const
+    {
+        BT b = __builtin_bit_cast(BT, x);
+        if (b == NR) b ^= BT(1);
+        if (own) __hip_atomic_store(vec + row, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ BT fetched(const BT *vec) const
+    {
+        return own ? __hip_atomic_load(vec + row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : BT(0);
+    }
+
+    // half sweeps, and whether one solves with the lower triangle
+    __device__ static int halves(const SmallArgs &a) { return a.sweeps * (!a.jr && a.variant == GS2_SYMMETRIC ? 2 : 1); }
+    __device__ static bool lower_half(const SmallArgs &a, int t)
+    {
+        return a.jr || a.variant == GS2_FORWARD || (a.variant == GS2_SYMMETRIC && t % 2 == 0);
+    }
+
+    // the row through all passes; false (in every lane) once a wait has ended
+    __device__ bool run(BT *set, BT *other, unsigned limit)
+    {
+        looks = limit;
+        late = false;
         Row rL, rU;
         load(rL, a.L);
         load(rU, a.U);
-        const AT sv = own ? (AT)(a.v[row] * a.sl[row]) : AT(0);
+        const AT sv = scaled_v();
         const double sr = own ? a.sr[row] : 0.0;
         if (own)
             for (int q = 0; q < a.ne; ++q) other[(size_t)q * a.n + row] = NR;
@@ -184,69 +243,115 @@ struct SmallRow {
         // the row's entry of the next exchanged vector, gathered from then on
         const BT *src = nullptr;
         auto put = [&](AT x) {
-            BT b = __builtin_bit_cast(BT, x);
-            if (b == NR) b ^= BT(1);
-            if (own) __hip_atomic_store(set + row, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            store(set, x);
             src = set;
             set += a.n;
             __asm__ volatile("" ::: "memory");
         };
-        const int inner = a.jr ? 0 : a.inner, compact = a.jr ? 0 : a.compact;
-        const int per = !a.jr && a.variant == GS2_SYMMETRIC ? 2 : 1, halves = a.sweeps * per;
-        const AT w = (AT)a.omega, gamma = (AT)a.gamma;
-        const bool damp = !a.jr && a.gamma != 1.0;
-        const AT cdiag = compact ? (AT)(1.0 - 1.0 / a.omega) : AT(1);
-        bool xzero = true;
+        const int inner = a.jr ? 0 : a.inner, H = halves(a);
         AT x_own = AT(0);
-        // x <- w g or x + w g; the last one goes out
         auto finish = [&](bool fin, bool fresh, AT g) {
-            x_own = fresh ? w * g : fma(w, g, x_own);
+            x_own = updated(fresh, x_own, g);
             if (!fin) put(x_own);
             else if (own) a.z[row] = sr * (double)x_own;
         };
-        for (int t = 0; t < halves; ++t) {
-            const bool lower = a.jr || a.variant == GS2_FORWARD || (a.variant == GS2_SYMMETRIC && t % 2 == 0);
-            const bool fin = t == halves - 1, fresh = xzero || compact;
+        for (int t = 0; t < H; ++t) {
+            const bool lower = lower_half(a, t), fin = t == H - 1, fresh = t == 0 || (!a.jr && a.compact);
             AT r = sv;
-            if (!xzero) {
-                Sums acc;
-                if (!compact) {
-                    if (lower) dot(rL, acc, src);
-                    else dot(rU, acc, src);
-                }
-                if (lower) dot(rU, acc, src);
-                else dot(rL, acc, src);
-                r = fma(-cdiag, x_own, sv) - acc.total();
+            if (t > 0) {
+                r = lower ? residual(rL, rU, src, sv, x_own) : residual(rU, rL, src, sv, x_own);
+                if (__any(late)) return false;
             }
             if (inner == 0) {
                 finish(fin, fresh, r);
-            } else {
-                if (!xzero) put(r);
-                else src = nullptr; // S_l v
-                AT g = r;
-                for (int j = 1; j <= inner; ++j) {
-                    Sums acc;
-                    if (lower) dot(rL, acc, src);
-                    else dot(rU, acc, src);
-                    const AT old = g;
-                    g = fma(-w, acc.total(), r);
-                    if (damp) g = fma(gamma, g, (AT(1) - gamma) * old);
-                    if (j == inner) finish(fin, fresh, g);
-                    else put(g);
-                }
+                continue;
             }
-            xzero = false;
+            if (t > 0) put(r);
+            else src = nullptr; // S_l v
+            AT g = r;
+            for (int j = 1; j <= inner; ++j) {
+                g = lower ? relax(rL, src, r, g) : relax(rU, src, r, g);
+                if (__any(late)) return false;
+                if (j == inner) finish(fin, fresh, g);
+                else put(g);
+            }
         }
-        if ((threadIdx.x & (WAVE - 1)) == 0) a.ep[blockIdx.x] = turn + 1u;
+        return true;
+    }
+
+    // Every entry of the apply's exchanged vectors that is not there yet, one vector
+    // after the other (each needs all of the one before it and, of its own row, the
+    // half sweep's residual and the iterate before it).  The wavefront starts with its
+    // own rows, as others that do the same start with theirs.
+    __device__ static void complete(const SmallArgs &a, BT *set)
+    {
+        const int inner = a.jr ? 0 : a.inner, H = halves(a), nc = (a.n + WAVE - 1) / WAVE;
+        const BT *x = nullptr, *r = nullptr, *src = nullptr; // iterate, residual, the vector before
+        for (int t = 0; t < H; ++t) {
+            const bool lower = lower_half(a, t), fresh = t == 0 || (!a.jr && a.compact);
+            r = nullptr;
+            // pass 0: the residual (itself, or the iterate it gives); j > 0: inner pass j
+            for (int pass = t == 0 && inner > 0 ? 1 : 0; pass <= inner; ++pass) {
+                const bool last = pass == inner;
+                if (last && t == H - 1) return; // the output
+                for (int k = 0; k < nc; ++k) {
+                    const int c = ((int)blockIdx.x + k) % nc, row = c * WAVE + (int)(threadIdx.x & (WAVE - 1));
+                    SmallRow w{a, row, row < a.n, SMALL_STORED_POLLS};
+                    if (!__any(w.own && w.fetched(set) == NR)) continue;
+                    Row T, O;
+                    w.load(T, lower ? a.L : a.U);
+                    w.load(O, lower ? a.U : a.L);
+                    const AT sv = w.scaled_v();
+                    const AT xo = x ? __builtin_bit_cast(AT, w.fetched(x)) : AT(0);
+                    AT g;
+                    if (pass == 0) {
+                        g = t == 0 ? sv : w.residual(T, O, src, sv, xo);
+                    } else {
+                        const AT rr = r ? __builtin_bit_cast(AT, w.fetched(r)) : sv;
+                        g = w.relax(T, src, rr, pass == 1 ? rr : __builtin_bit_cast(AT, w.fetched(src)));
+                    }
+                    w.store(set, last ? w.updated(fresh, xo, g) : g);
+                }
+                src = set;
+                if (last) x = set;
+                else if (pass == 0) r = set;
+                set += a.n;
+            }
+        }
     }
 };
+
+// The kernel's arguments, read again where the call stands: the way that is hardly
+// ever taken then keeps nothing in scalar registers, which spilled, on the other.
+__device__ __forceinline__ SmallArgs arguments()
+{
+    static_assert(sizeof(SmallArgs) % 4 == 0, "whole words");
+    auto p = (const __attribute__((address_space(4))) unsigned *)__builtin_amdgcn_kernarg_segment_ptr();
+    __asm__ volatile("" : "+s"(p));
+    unsigned w[sizeof(SmallArgs) / 4];
+#pragma unroll
+    for (unsigned k = 0; k < sizeof(SmallArgs) / 4; ++k) w[k] = p[k];
+    SmallArgs a;
+    __builtin_memcpy(&a, w, sizeof a);
+    return a;
+}
 
 template <typename VT, typename AT, int KL>
 __global__ __launch_bounds__(WAVE, 4) void k_small_apply(SmallArgs a)
 {
     if (a.stop && *a.stop) return;
+    using R = SmallRow<VT, AT, KL>;
+    using BT = typename R::BT;
     const int row = (int)(blockIdx.x * WAVE + threadIdx.x);
-    SmallRow<VT, AT, KL>{a, row, row < a.n}.run();
+    const unsigned turn = a.ep[blockIdx.x];
+    BT *set = (BT *)a.ex + (size_t)(turn & 1u) * a.ne * a.n;
+    BT *other = (BT *)a.ex + (size_t)(~turn & 1u) * a.ne * a.n;
+    if (!R{a, row, row < a.n}.run(set, other, a.looks)) {
+        R::complete(arguments(), set);
+        const SmallArgs b = arguments();
+        (void)R{b, row, row < b.n}.run(set, other, SMALL_STORED_POLLS);
+    }
+    if (threadIdx.x == 0) a.ep[blockIdx.x] = turn + 1u;
 }
 
 template <typename BT>
@@ -326,6 +431,7 @@ bool small_apply(Handle &h, bool jr, int sweeps, double omega, const double *v, 
     a.z = z;
     a.ex = h.ex;
     a.ep = h.ep;
+    a.looks = h.wait_looks < 0 ? SMALL_WAIT_POLLS : (unsigned)h.wait_looks;
     if (h.precision == GS2_FP64) launch<double, double>(lanes, a, s);
     else if (h.precision == GS2_FP32) launch<float, float>(lanes, a, s);
     else launch<_Float16, float>(lanes, a, s);
@@ -333,3 +439,10 @@ bool small_apply(Handle &h, bool jr, int sweeps, double omega, const double *v, 
 }
 
 } // namespace gs2
+
+extern "C" int gs2_wait_looks(gs2_handle *H, int looks)
+{
+    if (!H) return GS2_ERR_ARG;
+    H->h.wait_looks = looks;
+    return GS2_OK;
+}

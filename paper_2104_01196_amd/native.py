@@ -90,6 +90,7 @@ def lib():
         L.gs2_gmres_basis_schedule.argtypes = [vp, ip, ip, ip]
         L.gs2_inner_residuals.argtypes = [vp, vp, i, C.POINTER(C.c_double), vp]
         L.gs2_inner_residuals_noalloc.argtypes = [vp, vp, i, vp, vp]
+        L.gs2_wait_looks.argtypes = [vp, i]
         L.gs2_profile.argtypes = [i]
         L.gs2_graphs.argtypes = [i]
         L.gs2_profile_kernel_count.argtypes = []
@@ -331,6 +332,13 @@ def gs2_inner_residuals_noalloc(h: Handle, r, inner: int, out, stream=None):
                                            _ptr(out, torch.float64, inner + 1, "out"), _stream(stream))
     if st != OK:
         raise Gs2Error(st, "gs2_inner_residuals_noalloc")
+
+
+def gs2_wait_looks(h: Handle, looks: int):
+    """Longest wait within one-launch applies on this handle, in looks (< 0: the default)."""
+    st = lib().gs2_wait_looks(h.ptr, looks)
+    if st != OK:
+        raise Gs2Error(st, "gs2_wait_looks")
 
 
 def gs2_profile(enable: bool):
