@@ -112,8 +112,9 @@ void free_gmres_work(GmresWork *g)
 }
 
 // ne: vectors exchanged within an apply of the handle (< 0: none, or too many
-// for a solve in one launch)
-static int alloc_work(GmresWork **out, int64_t n, int m, int ne)
+// for a solve in one launch).  The barrier words are cleared on s, the stream of
+// the solve that follows: the null stream has no order with a non-blocking one.
+static int alloc_work(GmresWork **out, int64_t n, int m, int ne, hipStream_t s)
 {
     GmresWork *g = new (std::nothrow) GmresWork;
     if (!g) return GS2_ERR_NOMEM;
@@ -147,7 +148,7 @@ static int alloc_work(GmresWork **out, int64_t n, int m, int ne)
     if (hipMalloc(&g->mem, total) != hipSuccess) st = GS2_ERR_NOMEM;
     else place(g->mem);
     if (st == GS2_OK && g->rbar &&
-        (hipMemset(g->rbar, 0, sizeof(unsigned) * 4) != hipSuccess ||
+        (hipMemsetAsync(g->rbar, 0, sizeof(unsigned) * 4, s) != hipSuccess ||
          hipHostMalloc((void **)&g->rinfo, sizeof(ResInfo), hipHostMallocDefault) != hipSuccess))
         st = GS2_ERR_NOMEM;
     if (st == GS2_OK && hipHostMalloc((void **)&g->hdr, sizeof(GHeader), hipHostMallocDefault) != hipSuccess)
@@ -1385,11 +1386,11 @@ static int gmres_impl(const gs2_csr &A, const double *b, double *x, int m, doubl
             if (P->h.gw) free_gmres_work(P->h.gw);
             P->h.gw = nullptr;
             const int ne = exchanged(false, P->h.sweeps, P->h.inner, P->h.variant);
-            GS2_TRY(alloc_work(&P->h.gw, n, m, ne <= RES_MAX_EX ? ne : -1));
+            GS2_TRY(alloc_work(&P->h.gw, n, m, ne <= RES_MAX_EX ? ne : -1, s));
         }
         W = P->h.gw;
     } else {
-        GS2_TRY(alloc_work(&own, n, m, -1));
+        GS2_TRY(alloc_work(&own, n, m, -1, s));
         W = own;
     }
     struct Guard {
