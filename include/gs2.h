@@ -250,7 +250,8 @@ int mtgs_apply(gs2_handle *h, int variant, double damping, const double *v, doub
  * step count, rtol) and replayed (see gs2_graphs; not while gs2_profile is
  * on); a system of at most 65536 rows with one lane per row of A, no
  * preconditioner, GS2 or JR and restart <= 64 is solved in one launch instead,
- * with the same bits (not while gs2_profile is on).  Returns GS2_OK,
+ * with the same bits (not while gs2_profile is on, and not for some solves
+ * after one whose workgroups could not meet in two seconds).  Returns GS2_OK,
  * GS2_NOT_CONVERGED (maxit reached), GS2_BREAKDOWN_EXACT, GS2_STAGNATED (the
  * true residual at the end of a restart cycle has not halved for the
  * handle's stagnation_cycles cycles, 50 by default), or an error; `info`
@@ -317,12 +318,24 @@ int gs2_inner_residuals(gs2_handle *h, const double *r, int inner, double *out, 
 int gs2_inner_residuals_noalloc(gs2_handle *h, const double *r, int inner, double *out, void *stream);
 
 /*
- * Longest wait between the wavefronts of a one-launch apply on this handle (systems
- * of at most 65536 rows), in looks at memory; < 0 = the default.  A wavefront
- * that has waited that long forms what it waits for itself, so the result does
- * not depend on it.  For tests.  Errors: GS2_ERR_ARG.
+ * Longest wait between the wavefronts of a one-launch apply or solve on this handle
+ * (systems of at most 65536 rows), in looks at memory; < 0 = the default.  A
+ * wavefront of an apply that has waited that long forms what it waits for itself; a
+ * solve is given up and repeated launch by launch, as the next 8, 64, ... solves
+ * with the handle then are.  Results do not depend on it.  For tests.  Errors:
+ * GS2_ERR_ARG.
  */
 int gs2_wait_looks(gs2_handle *h, int looks);
+
+/*
+ * How calls on this handle ran, for tests: last_solve 0 (no gmres_solve yet), 1
+ * (the last one launch by launch) or 2 (in one launch); paired: the last one's
+ * second basis pass, where it was launched with the default orthogonalisation,
+ * loads pairs of rows; given_up: solves tried in one launch and given up;
+ * applies: applies enqueued as one launch, within solvers too.  Any pointer but h
+ * may be NULL.
+ */
+int gs2_paths(const gs2_handle *h, int *last_solve, int *paired, int64_t *given_up, int64_t *applies);
 
 /* Free a handle (NULL is ignored).  Synchronises the device. */
 void gs2_destroy(gs2_handle *h);

@@ -312,6 +312,12 @@ struct Handle {
     void *ex = nullptr;
     unsigned *ep = nullptr;
     int wait_looks = -1; // looks before a wait between wavefronts ends (< 0: the default)
+    // one-launch solves whose waits ended, in a row, and solves from then on that are
+    // launched without trying
+    int given_up_row = 0, launch_next = 0;
+    // gs2_paths
+    int last_solve = 0, paired = 0;
+    int64_t given_up = 0, one_launch_applies = 0;
     GmresWork *gw = nullptr;
     CgWork *cw = nullptr;
     const int *stop = nullptr; // device flag: kernels return at once when set (GMRES)

@@ -1362,6 +1362,7 @@ static int resident_solve(GmresWork *W, const double *b, double *x, int m, doubl
     a.ne = exchanged(kind == GS2_PREC_JR, h.sweeps, h.inner, h.variant);
     a.part = W->rpart;
     a.bar = W->rbar;
+    a.looks = h.wait_looks < 0 ? RES_WAIT_POLLS : (unsigned)h.wait_looks;
     a.info = W->rinfo;
     GS2_TRY(resident_launch(h.precision, sum_lanes(h), a, s));
     GS2_TRY_HIP(hipStreamSynchronize(s));
@@ -1406,10 +1407,26 @@ static int gmres_impl(const gs2_csr &A, const double *b, double *x, int m, doubl
     GS2_TRY(prepare_product(W->prod, A, P ? P->h.spmv_fmt : GS2_FORMAT_AUTO, s));
     GS2_TRY(tune_basis(W, P ? P->h.basis_req : 0, s));
     if (resident_fits(W, P, m, kind)) {
-        bool given_up = false;
-        const int st = resident_solve(W, b, x, m, rtol, maxit, kind, P, info, s, &given_up);
-        if (!given_up) return st;
+        // What keeps its workgroups from meeting (other work on the card) may last: each
+        // solve given up costs seconds, so after k of them in a row the next 8^k
+        // are launched at once.
+        Handle &h = P->h;
+        if (h.launch_next > 0) {
+            --h.launch_next;
+        } else {
+            bool given_up = false;
+            const int st = resident_solve(W, b, x, m, rtol, maxit, kind, P, info, s, &given_up);
+            if (!given_up) {
+                if (st >= 0 || st == GS2_ERR_NONFINITE) h.given_up_row = 0;
+                h.last_solve = 2;
+                return st;
+            }
+            ++h.given_up;
+            h.given_up_row = std::min(h.given_up_row + 1, 6);
+            h.launch_next = 1 << 3 * h.given_up_row;
+        }
     }
+    if (P) P->h.last_solve = 1;
     const SellAView AS = view(W->prod.A);
     const DiaAView AD = dview(W->prod.A);
     const int K = W->prod.A.sel;
@@ -1506,6 +1523,7 @@ static int gmres_impl(const gs2_csr &A, const double *b, double *x, int m, doubl
         // 16-byte aligned; below the size solved in one launch it keeps that
         // launch's order of summation
         const bool pairs = n % 2 == 0 && n > RES_MAX_N;
+        if (P) P->h.paired = orth == 0 && pairs;
         const int nbu = pairs ? (int)((n + 2 * UPD_PAIRS * KT - 1) / (2 * UPD_PAIRS * KT)) : nb;
         auto enqueue_cycle = [&](hipStream_t cs) -> int {
             k_cycle_init<<<1, 64, 0, cs>>>(st, steps, rtol);

@@ -48,10 +48,10 @@
 // entries of a row at a time): a version that spilled vector registers beside spilled scalar ones gave wrong
 // results in the float32 instantiation.
 //
-// Waits are bounded: past WAIT_TICKS of the wall clock or WAIT_POLLS looks the
+// Waits are bounded: past WAIT_TICKS of the wall clock or ResArgs::looks the
 // abort flag goes up, who has waited that long waits no more, every workgroup
 // leaves at the next barrier and the caller solves by launches instead, from
-// the x it finds (x is written at the end only).
+// the x it finds (x is written after a barrier past which nothing is waited for).
 #include <algorithm>
 #include <cmath>
 
@@ -65,7 +65,6 @@ namespace gs2 {
 namespace {
 
 constexpr long long WAIT_TICKS = 200000000ll; // 2 s at 100 MHz
-constexpr unsigned WAIT_POLLS = 1u << 21;      // trips to memory, half a microsecond or more each
 constexpr int QW = KT / WAVE;   // wavefronts of the launches whose sums are repeated here
 
 // Threads of a workgroup of RR rows: one per row and, where there is room for
@@ -102,6 +101,7 @@ struct Shared {
     // read at agent scope every one of them was a trip past the caches
     double near[2][near_of(RR)];
     int flag, most[3];
+    unsigned looks; // ResArgs::looks (in a scalar register the polls were 1 % slower)
 };
 
 // A stored matrix and a thread's row of it: entry k at col[p], val[p] with
@@ -158,7 +158,7 @@ struct Team {
     __device__ bool wait(unsigned &polls)
     {
         if (late) return false;
-        if (++polls < WAIT_POLLS) return true;
+        if (++polls < sh.looks) return true;
         late = true;
         __hip_atomic_store(a.bar + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return false;
@@ -207,7 +207,11 @@ struct Team {
         side ^= 1;
         __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (a.G == 1) return true;
+        if (a.G == 1) { // a wait may have run out all the same
+            if (t == 0) sh.flag = (int)__hip_atomic_load(a.bar + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            return sh.flag == 0;
+        }
         ++epoch;
         if (t == 0) {
             sh.flag = 0;
@@ -497,6 +501,7 @@ __device__ bool Team<VT, AT, KL, RR>::solve(ResInfo &info)
         mU = row_of(a.U);
         mA = row_of(a.A);
         if (t < 3) sh.most[t] = 0;
+        if (t == 0) sh.looks = a.looks;
         __syncthreads();
         if (a.kind != GS2_PREC_NONE) {
             keep<VT>(mL, 0, area, used, size);

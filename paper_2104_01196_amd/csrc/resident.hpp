@@ -10,6 +10,7 @@ constexpr int RES_MAX_ROWS = 1024;  // rows per workgroup, at most
 constexpr int RES_MAX_EX = 32;      // most vectors exchanged within a preconditioner apply
 constexpr int64_t RES_MAX_N = (int64_t)RES_MAX_GROUPS * RES_MAX_ROWS;
 constexpr int RES_MAX_M = 64;       // longest restart (its Hessenberg matrix sits in LDS)
+constexpr unsigned RES_WAIT_POLLS = 1u << 21; // trips to memory before a wait ends, half a microsecond or more each
 constexpr int RES_GIVEN_UP = 1000;  // ResInfo::status of a solve whose wait ran out
 
 // Rows per workgroup of a small system, here and where it is solved launch by
@@ -54,6 +55,7 @@ struct ResArgs {
     int ne;
     double *part;
     unsigned *bar; // arrivals, abort, departures: zero between solves
+    unsigned looks; // before a wait ends
     ResInfo *info;
 };
 

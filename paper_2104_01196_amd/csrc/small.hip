@@ -435,6 +435,7 @@ bool small_apply(Handle &h, bool jr, int sweeps, double omega, const double *v, 
     if (h.precision == GS2_FP64) launch<double, double>(lanes, a, s);
     else if (h.precision == GS2_FP32) launch<float, float>(lanes, a, s);
     else launch<_Float16, float>(lanes, a, s);
+    ++h.one_launch_applies;
     return true;
 }
 
@@ -444,5 +445,15 @@ extern "C" int gs2_wait_looks(gs2_handle *H, int looks)
 {
     if (!H) return GS2_ERR_ARG;
     H->h.wait_looks = looks;
+    return GS2_OK;
+}
+
+extern "C" int gs2_paths(const gs2_handle *H, int *last_solve, int *paired, int64_t *given_up, int64_t *applies)
+{
+    if (!H) return GS2_ERR_ARG;
+    if (last_solve) *last_solve = H->h.last_solve;
+    if (paired) *paired = H->h.paired;
+    if (given_up) *given_up = H->h.given_up;
+    if (applies) *applies = H->h.one_launch_applies;
     return GS2_OK;
 }

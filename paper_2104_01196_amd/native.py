@@ -91,6 +91,7 @@ def lib():
         L.gs2_inner_residuals.argtypes = [vp, vp, i, C.POINTER(C.c_double), vp]
         L.gs2_inner_residuals_noalloc.argtypes = [vp, vp, i, vp, vp]
         L.gs2_wait_looks.argtypes = [vp, i]
+        L.gs2_paths.argtypes = [vp, ip, ip, i64p, i64p]
         L.gs2_profile.argtypes = [i]
         L.gs2_graphs.argtypes = [i]
         L.gs2_profile_kernel_count.argtypes = []
@@ -335,10 +336,19 @@ def gs2_inner_residuals_noalloc(h: Handle, r, inner: int, out, stream=None):
 
 
 def gs2_wait_looks(h: Handle, looks: int):
-    """Longest wait within one-launch applies on this handle, in looks (< 0: the default)."""
+    """Longest wait within one-launch applies and solves on this handle, in looks (< 0: the default)."""
     st = lib().gs2_wait_looks(h.ptr, looks)
     if st != OK:
         raise Gs2Error(st, "gs2_wait_looks")
+
+
+def gs2_paths(h: Handle) -> dict:
+    """How calls on this handle ran: last_solve 0 none, 1 launched, 2 in one launch; see include/gs2.h."""
+    v = [C.c_int(), C.c_int(), C.c_int64(), C.c_int64()]
+    st = lib().gs2_paths(h.ptr, *[C.byref(x) for x in v])
+    if st != OK:
+        raise Gs2Error(st, "gs2_paths")
+    return {k: x.value for k, x in zip(["last_solve", "paired", "given_up", "applies"], v)}
 
 
 def gs2_profile(enable: bool):
