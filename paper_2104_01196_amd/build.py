@@ -6,6 +6,7 @@ Object files go to paper_2104_01196_amd/_build/, the library next to this file.
 from __future__ import annotations
 
 import os
+import re
 import shutil
 import subprocess
 import sys
@@ -30,6 +31,30 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I", os.path.join(ROOT, "include"),
 ]
+
+
+# Kernels that must not spill vector registers or use scratch memory: an
+# instantiation of k_resident that spilled 55 vector registers beside 139 scalar
+# ones gave wrong results, the same ones every time, and the same source without
+# spills right ones.  (Scalar registers alone go to lanes of vector registers.)
+NO_SPILLS = {"resident.hip": "k_resident", "small.hip": "k_small_apply"}
+
+
+def check_spills(remarks: str, kernel: str) -> int:
+    """Instantiations of `kernel` in the compiler's resource remarks; raises if one spills."""
+    seen = 0
+    for block in remarks.split("Function Name: ")[1:]:
+        name = block.split()[0]
+        if kernel not in name:
+            continue
+        seen += 1
+        for what in ("VGPRs Spill", r"ScratchSize \[bytes/lane\]"):
+            m = re.search(what + r": (\d+)", block)
+            if m is None or int(m.group(1)) != 0:
+                raise RuntimeError(f"{name}: {m.group(0) if m else 'no ' + what} (must be 0)")
+    if not seen:
+        raise RuntimeError(f"no resource remarks for {kernel}")
+    return seen
 
 
 def _hipcc() -> str:
@@ -58,10 +83,14 @@ def _runtime_dir() -> str:
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
     cmd = [_hipcc(), *HIPCC_FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+    if src in NO_SPILLS:
+        cmd.append("-Rpass-analysis=kernel-resource-usage")
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         sys.stderr.write(r.stdout + r.stderr)
         raise RuntimeError(f"hipcc failed on {src}")
+    if src in NO_SPILLS:
+        check_spills(r.stderr, NO_SPILLS[src])
     errs = [ln for ln in r.stderr.splitlines() if "warning" in ln and "packed-fp32-ops" not in ln
             and "recognized feature" not in ln]
     if errs:

@@ -43,10 +43,12 @@
 // without which nobody reads that turn again.  A cycle starts with all of it
 // reset, then a barrier.
 //
-// Registers: 1024 threads leave 128 per thread.  Kept below that without
-// spills (eight loads in flight over a basis vector, not all sixteen; two
-// entries of a row at a time): a version that spilled vector registers beside spilled scalar ones gave wrong
-// results in the float32 instantiation.
+// Registers: 1024 threads leave 128 per thread.  Kept below that without spills
+// of vector registers (eight loads in flight over a basis vector, not all sixteen;
+// two entries of a row at a time).  The build fails on such a spill here: a version
+// that spilled 55 of them beside 139 scalar ones gave wrong results in the float32
+// instantiation, the same ones in every run, and the cause was not found (scalar
+// registers alone, which go to lanes of vector registers, do no harm).
 //
 // Waits are bounded: past WAIT_TICKS of the wall clock or ResArgs::looks the
 // abort flag goes up, who has waited that long waits no more, every workgroup
