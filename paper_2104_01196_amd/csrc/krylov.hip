@@ -726,10 +726,11 @@ __global__ __launch_bounds__(KT) void k_dot2(int64_t n, const double *__restrict
 // Pass 2 of step j: q_j = (u - Q a)/alpha over u's slot, w' = w - Q c - e q_j
 // into V[j+1], partial ||w'||^2.  Every workgroup derives alpha and e itself
 // (identical bits) and skips the pass when u has fallen into span(Q).
-template <int ROWS = RB>
-__global__ __launch_bounds__(KT) void k_dcgs_update(int64_t n, double *__restrict__ V, int64_t ldv,
-                                                    const GState *__restrict__ st, const double *__restrict__ w,
-                                                    double *__restrict__ part)
+// NARROW: one load in flight per thread; the updates run in the same order.
+template <int ROWS, bool NARROW>
+__device__ __forceinline__ void dcgs_update(int64_t n, double *__restrict__ V, int64_t ldv,
+                                            const GState *__restrict__ st, const double *__restrict__ w,
+                                            double *__restrict__ part)
 {
     __shared__ double as[MAXM + 2], cs_[MAXM + 2], red[KT / WAVE], sc[2];
     if (st->done) return;
@@ -757,15 +758,17 @@ __global__ __launch_bounds__(KT) void k_dcgs_update(int64_t n, double *__restric
         aq[q] = zsc * u[rows[q]];
         aw[q] = w[rows[q]];
     }
-#pragma unroll 2
+#pragma unroll NARROW ? 1 : 2
     for (int k = 0; k < j; ++k) {
         const double *__restrict__ vk = V + (int64_t)k * ldv;
         const double a = as[k], c = cs_[k];
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-            const double x = __builtin_nontemporal_load(&vk[rows[q]]);
+            double x = __builtin_nontemporal_load(&vk[rows[q]]);
+            if constexpr (NARROW) asm volatile("" : "+v"(x)::"memory");
             aq[q] -= a * x;
             aw[q] -= c * x;
+            if constexpr (NARROW) asm volatile("" : "+v"(aq[q]), "+v"(aw[q]));
         }
     }
 #pragma unroll
@@ -780,6 +783,21 @@ __global__ __launch_bounds__(KT) void k_dcgs_update(int64_t n, double *__restric
     }
     s = block_sum(s, red);
     if (t == 0) part[blockIdx.x] = s;
+}
+
+template <int ROWS = RB>
+__global__ __launch_bounds__(KT) void k_dcgs_update(int64_t n, double *__restrict__ V, int64_t ldv,
+                                                    const GState *__restrict__ st, const double *__restrict__ w,
+                                                    double *__restrict__ part)
+{
+    dcgs_update<ROWS, false>(n, V, ldv, st, w, part);
+}
+template <int ROWS = RB>
+__global__ __launch_bounds__(KT) void k_dcgs_update_narrow(int64_t n, double *__restrict__ V, int64_t ldv,
+                                                           const GState *__restrict__ st,
+                                                           const double *__restrict__ w, double *__restrict__ part)
+{
+    dcgs_update<ROWS, true>(n, V, ldv, st, w, part);
 }
 
 // The same pass with 16-byte loads for an even n (every column then starts
@@ -1519,9 +1537,12 @@ static int gmres_impl(const gs2_csr &A, const double *b, double *x, int m, doubl
         // a GS2 or JR pass: it needs only step j's partial sums and the state,
         // and the pass needs neither.  The last step's runs alone.
         const bool fuse_fin = orth == 0 && P && (kind == GS2_PREC_GS2 || kind == GS2_PREC_JR);
-        // the second basis pass loads pairs of rows when every column is
-        // 16-byte aligned; below the size solved in one launch it keeps that
-        // launch's order of summation
+        // The second basis pass loads pairs of rows when every column is 16-byte
+        // aligned, on more rows than are solved in one launch.  Fewer leave its 2048-row
+        // workgroups too few (a whole step, in us: 5616-row elasticity 207 paired and 175
+        // not, 52728 rows 340 and 334; GMRES(80) on the 7-point Laplacian, 4096 rows 42
+        // and 38, 64000 rows 109 and 97; multicolor on 40000 rows 84 and 73), and the
+        // other form adds in the order of the one launch.
         const bool pairs = n % 2 == 0 && n > RES_MAX_N;
         if (P) P->h.paired = orth == 0 && pairs;
         const int nbu = pairs ? (int)((n + 2 * UPD_PAIRS * KT - 1) / (2 * UPD_PAIRS * KT)) : nb;
@@ -1569,8 +1590,10 @@ static int gmres_impl(const gs2_csr &A, const double *b, double *x, int m, doubl
                     }
                     {
                         Prof pr(cs, PK_CGS, 8.0 * n * (j + 4));
-                        if (!pairs)
+                        if (!pairs && j < W->upd_narrow)
                             GS2_ROWS_DISPATCH(k_dcgs_update, gN, cs, n, W->V, n, st, W->w, W->part);
+                        else if (!pairs) // asked for
+                            GS2_ROWS_DISPATCH(k_dcgs_update_narrow, gN, cs, n, W->V, n, st, W->w, W->part);
                         else if (j < W->upd_narrow)
                             k_dcgs_update_pairs<UPD_PAIRS, UPD_PAIRS>
                                 <<<(unsigned)nbu, KT, 0, cs>>>(n, W->V, n, st, W->w, W->part);
