@@ -250,8 +250,8 @@ int mtgs_apply(gs2_handle *h, int variant, double damping, const double *v, doub
  * step count, rtol) and replayed (see gs2_graphs; not while gs2_profile is
  * on); a system of at most 65536 rows with one lane per row of A, no
  * preconditioner, GS2 or JR and restart <= 64 is solved in one launch instead,
- * with the same bits (not while gs2_profile is on, and not for some solves
- * after one whose workgroups could not meet in two seconds).  Returns GS2_OK,
+ * with the same bits (not while gs2_profile is on or gs2_graphs off, and not for
+ * some solves after one whose workgroups could not meet in two seconds).  Returns GS2_OK,
  * GS2_NOT_CONVERGED (maxit reached), GS2_BREAKDOWN_EXACT, GS2_STAGNATED (the
  * true residual at the end of a restart cycle has not halved for the
  * handle's stagnation_cycles cycles, 50 by default), or an error; `info`
@@ -262,8 +262,9 @@ int gmres_solve(const gs2_csr *A, const double *b, double *x, int restart, doubl
 
 /*
  * Process-wide switch for the graph replay of GMRES restart cycles: enable
- * != 0 (the default) captures and replays, 0 launches every kernel one by
- * one.  Both give bitwise identical results.  Returns the previous setting.
+ * != 0 (the default) captures and replays (or solves small systems in one
+ * launch), 0 launches every kernel one by one.  Both give bitwise identical
+ * results.  Returns the previous setting.
  */
 int gs2_graphs(int enable);
 

@@ -1329,12 +1329,13 @@ static int sum_lanes(const Handle &h) { return h.fmt == FMT_DIA ? 1 : h.L.K; }
 // Whether a solve runs in one launch (resident.hip): small, unpreconditioned
 // or preconditioned by GS2 or JR on one block, default orthogonalisation, rows
 // short enough for a thread each, no choice of the launches' schedules asked
-// for and no per-kernel timing.  Either way gives the same bits.
+// for, no per-kernel timing and kernels not asked for one by one (gs2_graphs).
+// Either way gives the same bits.
 static bool resident_fits(const GmresWork *W, const gs2_handle *P, int m, int kind)
 {
     return P && W->rbar && m <= RES_MAX_M && P->h.orth == 0 && P->h.blocks == 1 && W->prod.A.sel == 1 &&
            sum_lanes(P->h) <= res_lanes(W->n) &&
-           P->h.spmv_fmt == GS2_FORMAT_AUTO && P->h.basis_req == 0 && !prof_on() &&
+           P->h.spmv_fmt == GS2_FORMAT_AUTO && P->h.basis_req == 0 && !prof_on() && g_graphs.load() &&
            (kind == GS2_PREC_NONE || kind == GS2_PREC_GS2 || kind == GS2_PREC_JR);
 }
 
