@@ -128,7 +128,7 @@ typedef struct gs2_options {
                            /* default 50, also without a handle; < 0 = never)*/
     int spmv_format;      /* gmres_solve with this handle: layout of the     */
                           /* solver's copy of A for w = A z: GS2_FORMAT_AUTO */
-                          /* (0: timed once per shape on >= 65536 rows --    */
+                          /* (0: timed once per shape on > 65536 rows --     */
                           /* sliced ELL at two lane counts, diagonal copy at */
                           /* 1 and 2 rows per lane when A qualifies --, else */
                           /* or, for n = 3 x nodes with <= 32 node offsets  */

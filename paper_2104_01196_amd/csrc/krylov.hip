@@ -1097,8 +1097,10 @@ static int precondition(int kind, gs2_handle *P, const double *v, double *z, int
 }
 
 // Below this many rows the product's layout is not timed (sliced ELL at the
-// rule's lanes per row, unless forced): launch overhead would dominate.
-constexpr int64_t SPMV_TUNE_MIN_ROWS = 65536;
+// rule's lanes per row, unless forced): launch overhead would dominate, and
+// solves in one launch multiply by sliced ELL only, so whether the largest of
+// them runs in one must not depend on a timing.
+constexpr int64_t SPMV_TUNE_MIN_ROWS = RES_MAX_N + 1;
 
 // Loads in flight of the two delayed basis passes (all groups of one width:
 // block_multidot's and k_dcgs_update_pairs' G), decided once per size bucket
