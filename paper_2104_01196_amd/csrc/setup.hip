@@ -298,25 +298,43 @@ __device__ __forceinline__ Range row_range(const Rows &A, int part, int64_t i)
 
 // Stored entries of each slice of a part: 64 * ceil(longest row / K), one
 // lane per row.  The extra element at index nslices is zero so that an
-// exclusive scan yields the end.  Adds the part's entries to *total, if given
-// (one workgroup after the other: only where the pattern scan's count does
-// not hold, with several blocks).
+// exclusive scan yields the end.  With st, adds up the part's entries and their
+// smallest and largest col - row (one wavefront after the other: only where what
+// the pattern scan found does not hold, with several blocks).
+struct PartStats {
+    unsigned long long total;
+    int lo, hi; // 0 among them, as padding
+};
 __global__ __launch_bounds__(256) void k_slice_len(Rows A, int part, int64_t nslices, int K, int64_t *__restrict__ len,
-                                                   unsigned long long *total)
+                                                   PartStats *st)
 {
     const int C = WAVE / K;
     const int64_t row = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    int c = 0;
+    int c = 0, lo = 0, hi = 0;
     if (row < A.n) {
         const Range r = row_range(A, part, row);
         c = r.c1 + r.c2;
+        if (st && c > 0) {
+            const int64_t b = A.rp[row];
+            lo = min(0, A.ci[b + (r.c1 ? r.o1 : r.o2)] - (int)row);
+            hi = max(0, A.ci[b + (r.c2 ? r.o2 + r.c2 : r.o1 + r.c1) - 1] - (int)row);
+        }
     }
     int m = c;
     for (int o = 1; o < C; o <<= 1) m = max(m, __shfl_xor(m, o));
-    if (total) {
+    if (st) {
         int sum = c;
-        for (int o = 1; o < WAVE; o <<= 1) sum += __shfl_xor(sum, o);
-        if (threadIdx.x % WAVE == 0 && sum) atomicAdd(total, (unsigned long long)sum);
+        for (int o = 1; o < WAVE; o <<= 1) {
+            sum += __shfl_xor(sum, o);
+            lo = min(lo, __shfl_xor(lo, o));
+            hi = max(hi, __shfl_xor(hi, o));
+        }
+        if (threadIdx.x % WAVE == 0 && sum) {
+            atomicAdd(&st->total, (unsigned long long)sum);
+            // a plain read first: after a few wavefronts the extremes stand
+            if (lo < st->lo) atomicMin(&st->lo, lo);
+            if (hi > st->hi) atomicMax(&st->hi, hi);
+        }
     }
     if (row % C == 0 && row / C <= nslices) len[row / C] = row / C == nslices ? 0 : (int64_t)WAVE * ((m + K - 1) / K);
 }
@@ -645,11 +663,12 @@ static int build_parts(Handle &h, int first, int last, int K, const gs2_csr &A, 
     const int64_t C = WAVE / K, ns = (n + C - 1) / C, tmp = scan_tmp(ns + 1);
     for (int q = first; q <= last; ++q) free_sell(*part[q]);
     Sell &own = *part[first];
-    // per part: pointers, lengths, scan totals, entry count
-    const int64_t per = 2 * (ns + 1) + tmp + 1;
+    // per part: pointers, lengths, scan totals, counts
+    const int64_t per = 2 * (ns + 1) + tmp + (int64_t)(sizeof(PartStats) / sizeof(int64_t));
     GS2_TRY_HIP(hipMalloc(&own.mem[0], sizeof(int64_t) * per * np));
     int64_t *base = (int64_t *)own.mem[0];
-    int64_t ends[3][2];
+    int64_t ends[3];
+    PartStats stats[3];
     for (int q = 0; q < np; ++q) {
         Sell &S = *part[first + q];
         S.n = n;
@@ -658,25 +677,26 @@ static int build_parts(Handle &h, int first, int last, int K, const gs2_csr &A, 
         S.nslices = ns;
         S.val_bytes = vb;
         S.slice_ptr = base + q * per;
-        int64_t *len = S.slice_ptr + ns + 1, *tot = len + ns + 1 + tmp;
+        int64_t *len = S.slice_ptr + ns + 1;
+        PartStats *dev = (PartStats *)(len + ns + 1 + tmp);
         const bool count = h.blocks > 1;
-        if (count) GS2_TRY_HIP(hipMemsetAsync(tot, 0, sizeof(int64_t), s));
-        k_slice_len<<<(unsigned)((ns * C + 1 + 255) / 256), 256, 0, s>>>(R, first + q, ns, K, len,
-                                                                       count ? (unsigned long long *)tot : nullptr);
+        if (count) GS2_TRY_HIP(hipMemsetAsync(dev, 0, sizeof(PartStats), s));
+        k_slice_len<<<(unsigned)((ns * C + 1 + 255) / 256), 256, 0, s>>>(R, first + q, ns, K, len, count ? dev : nullptr);
         GS2_TRY(exclusive_scan_i64(len, S.slice_ptr, ns + 1, len + ns + 1, s));
-        GS2_TRY_HIP(hipMemcpyAsync(&ends[q][0], S.slice_ptr + ns, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        ends[q][1] = first + q == PART_L ? sc.pat.nl : sc.pat.nu;
-        if (count) GS2_TRY_HIP(hipMemcpyAsync(&ends[q][1], tot, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+        GS2_TRY_HIP(hipMemcpyAsync(&ends[q], S.slice_ptr + ns, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+        const bool low = first + q == PART_L;
+        stats[q] = PartStats{(unsigned long long)(low ? sc.pat.nl : sc.pat.nu), low ? sc.pat.lo : 0, low ? 0 : sc.pat.hi};
+        if (count) GS2_TRY_HIP(hipMemcpyAsync(&stats[q], dev, sizeof(PartStats), hipMemcpyDeviceToHost, s));
     }
     GS2_TRY_HIP(hipStreamSynchronize(s));
     size_t bytes = 0, at[3][3];
     for (int q = 0; q < np; ++q) {
         Sell &S = *part[first + q];
-        S.padded = ends[q][0];
-        S.nnz = ends[q][1];
-        // padding sits at offset 0, and past the last row up to 63 below it
-        const int64_t lo = std::min<int64_t>(first + q == PART_U ? 0 : sc.pat.lo, 1 - WAVE);
-        const int64_t hi = first + q == PART_L ? 0 : sc.pat.hi;
+        S.padded = ends[q];
+        S.nnz = (int64_t)stats[q].total;
+        // padding sits at offset 0, and past the last row as far below it as the
+        // last slice goes on
+        const int64_t lo = std::min<int64_t>(stats[q].lo, n - ns * C), hi = stats[q].hi;
         const bool narrow = S.nnz > 0 && hi - lo <= 65535;
         S.off_min = narrow ? (int)lo : 0;
         const size_t cnt = (size_t)std::max<int64_t>(S.padded, WAVE);

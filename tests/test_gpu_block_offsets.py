@@ -39,18 +39,25 @@ def matrix(bs, near, far):
     return SimpleNamespace(n=n, rowptr=rp.astype(np.int32), colind=c.astype(np.int32), val=v)
 
 
-# blocks whose own span fits 16 bits and ones whose own span does not; near = 65535 - 63: the widest that fits
-# beside the padding of rows past the last one
-@pytest.mark.parametrize("bs,near", [(40_000, 300), (90_001, 300), (90_001, 65_472), (90_001, 65_600)])
+def stored(A):
+    h = g.gs2_setup(g.DeviceCSR.from_host(A), 1, 1, 0.9, g.FORWARD, blocks=BLOCKS, autotune=False)
+    return h, g.gs2_handle_query(h)["bytes_stored"]
+
+
+# 180002 rows leave 30 past the last one in a slice of 64, whose padding lies up to 30 below the diagonal: 65505 is the
+# widest coupling that fits beside it
+@pytest.mark.parametrize("bs,near", [(40_000, 300), (90_001, 300), (90_001, 65_505), (90_001, 65_506)])
 def test_stored_bytes_and_values(bs, near):
-    byts = []
-    for far in (0, bs):
-        A = matrix(bs, near, far)
-        h = g.gs2_setup(g.DeviceCSR.from_host(A), 1, 1, 0.9, g.FORWARD, blocks=BLOCKS, autotune=False)
-        byts.append(g.gs2_handle_query(h)["bytes_stored"])
-    assert byts[0] == byts[1]
+    (_, want), (h, got) = stored(matrix(bs, near, 0)), stored(matrix(bs, near, bs))
+    assert got == want
+    A = matrix(bs, near, bs)
     v = np.random.default_rng(1).standard_normal(A.n)
     z = torch.empty(A.n, dtype=torch.float64, device=DEV)
     g.gs2_apply(h, torch.as_tensor(v, device=DEV), z)
     want = oracle.gs2_block_sweep(A, v, np.zeros(A.n), BLOCKS, g.FORWARD, 1, 1, 1, 0.9)
     assert np.abs(z.cpu().numpy() - want).max() <= 1e-12 * np.abs(want).max()
+
+
+def test_widest():
+    """The offsets are held beside the columns: at the limit there are more bytes than past it."""
+    assert stored(matrix(90_001, 65_505, 90_001))[1] > stored(matrix(90_001, 65_506, 90_001))[1]
