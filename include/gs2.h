@@ -140,7 +140,7 @@ typedef struct gs2_options {
                           /* qualify                                         */
     int basis_loads;      /* gmres_solve with this handle: loads in flight   */
                           /* of the delayed passes over the Krylov basis:    */
-                          /* 0 = timed once per size class (bases of 2^20    */
+                          /* 0 = timed once per size (bases of 2^20          */
                           /* rows and more, else wide), 1 = wide groups at   */
                           /* every step, 2 = narrow groups from the          */
                           /* crossover steps (even row counts; wide where    */
@@ -333,10 +333,11 @@ int gs2_wait_looks(gs2_handle *h, int looks);
  * (the last one launch by launch) or 2 (in one launch); paired: the last one's
  * second basis pass, where it was launched with the default orthogonalisation,
  * loads pairs of rows; given_up: solves tried in one launch and given up;
- * applies: applies enqueued as one launch, within solvers too.  Any pointer but h
- * may be NULL.
+ * applies: applies enqueued as one launch, within solvers too; timings: schedules
+ * that gmres_solve timed with this handle (layout of A, basis passes), which it
+ * does once per size in the process.  Any pointer but h may be NULL.
  */
-int gs2_paths(const gs2_handle *h, int *last_solve, int *paired, int64_t *given_up, int64_t *applies);
+int gs2_paths(const gs2_handle *h, int *last_solve, int *paired, int64_t *given_up, int64_t *applies, int *timings);
 
 /* Free a handle (NULL is ignored).  Synchronises the device. */
 void gs2_destroy(gs2_handle *h);

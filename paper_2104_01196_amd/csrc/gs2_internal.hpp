@@ -366,10 +366,12 @@ int scan_pattern(const gs2_csr &A, int32_t *lcnt, int32_t *ucnt, double *sl, dou
 inline size_t aligned(size_t b) { return (b + 255) / 256 * 256; }
 
 // Schedules chosen by timing, process-wide and keyed by the shape of the
-// problem (get: false when there is none yet).
+// problem (shape_key: its class; size_key: its sizes; get: false when there is none
+// yet).
 bool choice_get(const std::string &key, int *choice);
 void choice_put(const std::string &key, int choice);
 std::string shape_key(int64_t n, double avg, int maxlen, int prec);
+std::string size_key(int64_t n, int64_t m, int maxlen);
 
 // small.hip: vectors that an apply's passes write for others to gather
 int exchanged(bool jr, int sweeps, int inner, int variant);
@@ -401,6 +403,7 @@ int noalloc_scratch(double **ptr);
 
 // krylov.hip, cg.hip
 void free_gmres_work(GmresWork *w);
+int timings(const GmresWork *w); // schedules its solves have timed
 void free_cg_work(CgWork *w);
 
 inline size_t prec_bytes(int precision) { return precision == GS2_FP64 ? 8 : 4; }

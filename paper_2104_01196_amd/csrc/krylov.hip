@@ -71,8 +71,8 @@ struct GmresWork {
     CycleKey key;
     Product prod;    // the solver's copy of the system matrix
     // Arnoldi steps from which the delayed passes keep fewer loads in flight
-    // (INT_MAX: never), timed once per workspace (tune_basis); basis_tuned 1
-    // decided there, 2 forced by the handle's request
+    // (INT_MAX: never), timed once per size and restart in the process (tune_basis);
+    // basis_tuned 1 decided there, 2 forced by the handle's request
     int upd_narrow = INT_MAX, dot_narrow = INT_MAX, basis_tuned = 0;
 };
 
@@ -1103,9 +1103,9 @@ static int precondition(int kind, gs2_handle *P, const double *v, double *z, int
 constexpr int64_t SPMV_TUNE_MIN_ROWS = RES_MAX_N + 1;
 
 // Loads in flight of the two delayed basis passes (all groups of one width:
-// block_multidot's and k_dcgs_update_pairs' G), decided once per size bucket
-// and restart in the process by timing both widths of each pass at step min(m - 1, 24) on the zeroed
-// basis (best of three batches of three launches after a warm-up batch; a
+// block_multidot's and k_dcgs_update_pairs' G), decided once per size and
+// restart in the process by timing both widths of each pass at step
+// min(m - 1, 24) on the zeroed basis (best of three batches of three launches after a warm-up batch; a
 // narrow variant must win by 3 %).  The narrow width then runs from the
 // crossover step.  Small bases (fewer than BASIS_TUNE_MIN_ROWS rows, or a
 // restart below 16) keep the wide groups.  The probe's writes (two columns,
@@ -1124,7 +1124,7 @@ static int tune_basis(GmresWork *W, int req, hipStream_t s)
         W->basis_tuned = req != 0 ? 2 : 1;
         return GS2_OK;
     }
-    const std::string key = "V_" + shape_key(n, W->m, 0, GS2_FP64);
+    const std::string key = "V_" + size_key(n, W->m, 0);
     int known = 0;
     if (choice_get(key, &known)) {
         if (known & 1) W->dot_narrow = DOT_NARROW_FROM;
@@ -1168,6 +1168,7 @@ static int tune_basis(GmresWork *W, int req, hipStream_t s)
     if (dn < 0.97f * dw) W->dot_narrow = DOT_NARROW_FROM;
     if (un < 0.97f * uw) W->upd_narrow = UPD_NARROW_FROM;
     choice_put(key, (dn < 0.97f * dw ? 1 : 0) | (un < 0.97f * uw ? 2 : 0));
+    ++W->prod.timings;
     W->basis_tuned = 1;
     return GS2_OK;
 }
@@ -1228,8 +1229,8 @@ static int build_layout(SellA &S, const gs2_csr &A, int sel, const std::vector<i
 // 16-byte value loads) or, failing that, the 3-row block copy at one and
 // two nodes per lane.  fmt GS2_FORMAT_AUTO times them (one product each;
 // a later candidate must win by 3 %) on matrices of at least
-// SPMV_TUNE_MIN_ROWS rows, once per shape in the process (as the sweep
-// schedules); GS2_FORMAT_SELL / _DIA / _BLOCK3 force a layout
+// SPMV_TUNE_MIN_ROWS rows, once per shape in the process (sizes, longest row
+// and number of offsets); GS2_FORMAT_SELL / _DIA / _BLOCK3 force a layout
 // (the diagonal one at two rows per lane, the block one at two nodes per
 // lane, falling back to sliced ELL when A does not qualify).  Rows that are
 // not strictly sorted never qualify.
@@ -1251,7 +1252,7 @@ int prepare_product(Product &W, const gs2_csr &A, int fmt, hipStream_t s, int *f
     const bool b3_ok = sorted && !dia_ok && fmt != GS2_FORMAT_DIA && sella_b3_offsets(A, pat, offs);
     const int K0 = sella_rule_lanes(A);
     int sel = K0, tuned = 0;
-    const std::string key = "A_" + shape_key(A.n, (double)A.nnz / (double)A.n, pat.maxlen, GS2_FP64) + "_d" +
+    const std::string key = "A_" + size_key(A.n, A.nnz, pat.maxlen) + "_d" +
                             std::to_string(dia_ok || b3_ok ? offs.size() : 0) + (b3_ok ? "b" : "");
     if (fmt == GS2_FORMAT_DIA && dia_ok) {
         sel = -2;
@@ -1286,6 +1287,7 @@ int prepare_product(Product &W, const gs2_csr &A, int fmt, hipStream_t s, int *f
         }
         tuned = 1;
         choice_put(key, sel);
+        ++W.timings;
     }
     if (S.sel != sel || !(S.val || S.dval)) GS2_TRY(build_layout(S, A, sel, offs, flag, s));
     S.tuned = tuned;
@@ -1677,6 +1679,8 @@ static int gmres_impl(const gs2_csr &A, const double *b, double *x, int m, doubl
     info->iterations = total;
     return status;
 }
+
+int timings(const GmresWork *W) { return W ? W->prod.timings : 0; }
 
 } // namespace gs2
 

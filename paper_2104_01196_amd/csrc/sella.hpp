@@ -103,6 +103,7 @@ constexpr int FILL_CHANGED = 1, FILL_UNSORTED = 2;
 struct Product {
     SellA A;
     int fmt_req = -1; // the layout request it was built for
+    int timings = 0;  // choices timed for it
     double *in = nullptr, *out = nullptr, *part = nullptr;
     PatternDev *pat = nullptr;
 };

@@ -587,8 +587,12 @@ int choose_lanes(double avg_len, int max_len)
     return 16;
 }
 
-// Timed choices, process-wide, keyed by the size bucket, rounded mean row
-// length, longest-row bucket, precision and what else the choice depends on.
+// Timed choices, process-wide.  The sweep schedules are keyed by the size bucket,
+// rounded mean row length, longest-row bucket, precision and what else they depend
+// on; the solver's (layout of A, basis passes) by the exact sizes, as nothing shows
+// that a timing holds for twice the rows.  Past CHOICES_MOST of them the table starts
+// anew.
+constexpr size_t CHOICES_MOST = 4096;
 static std::mutex g_choice_mu;
 static std::map<std::string, int> g_choices;
 
@@ -604,6 +608,7 @@ bool choice_get(const std::string &key, int *choice)
 void choice_put(const std::string &key, int choice)
 {
     std::lock_guard<std::mutex> lk(g_choice_mu);
+    if (g_choices.size() >= CHOICES_MOST) g_choices.clear();
     g_choices[key] = choice;
 }
 
@@ -616,6 +621,11 @@ std::string shape_key(int64_t n, double avg, int maxlen, int prec)
     char buf[96];
     std::snprintf(buf, sizeof buf, "n%d_a%d_m%d_p%d", nb, (int)std::lround(avg), mb, prec);
     return buf;
+}
+
+std::string size_key(int64_t n, int64_t m, int maxlen)
+{
+    return "n" + std::to_string(n) + "_" + std::to_string(m) + "_m" + std::to_string(maxlen);
 }
 
 // Device scratch of one setup, in one allocation.

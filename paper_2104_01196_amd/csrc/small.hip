@@ -448,12 +448,14 @@ extern "C" int gs2_wait_looks(gs2_handle *H, int looks)
     return GS2_OK;
 }
 
-extern "C" int gs2_paths(const gs2_handle *H, int *last_solve, int *paired, int64_t *given_up, int64_t *applies)
+extern "C" int gs2_paths(const gs2_handle *H, int *last_solve, int *paired, int64_t *given_up, int64_t *applies,
+                         int *timings)
 {
     if (!H) return GS2_ERR_ARG;
     if (last_solve) *last_solve = H->h.last_solve;
     if (paired) *paired = H->h.paired;
     if (given_up) *given_up = H->h.given_up;
     if (applies) *applies = H->h.one_launch_applies;
+    if (timings) *timings = gs2::timings(H->h.gw);
     return GS2_OK;
 }

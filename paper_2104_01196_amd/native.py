@@ -91,7 +91,7 @@ def lib():
         L.gs2_inner_residuals.argtypes = [vp, vp, i, C.POINTER(C.c_double), vp]
         L.gs2_inner_residuals_noalloc.argtypes = [vp, vp, i, vp, vp]
         L.gs2_wait_looks.argtypes = [vp, i]
-        L.gs2_paths.argtypes = [vp, ip, ip, i64p, i64p]
+        L.gs2_paths.argtypes = [vp, ip, ip, i64p, i64p, ip]
         L.gs2_profile.argtypes = [i]
         L.gs2_graphs.argtypes = [i]
         L.gs2_profile_kernel_count.argtypes = []
@@ -344,11 +344,11 @@ def gs2_wait_looks(h: Handle, looks: int):
 
 def gs2_paths(h: Handle) -> dict:
     """How calls on this handle ran: last_solve 0 none, 1 launched, 2 in one launch; see include/gs2.h."""
-    v = [C.c_int(), C.c_int(), C.c_int64(), C.c_int64()]
+    v = [C.c_int(), C.c_int(), C.c_int64(), C.c_int64(), C.c_int()]
     st = lib().gs2_paths(h.ptr, *[C.byref(x) for x in v])
     if st != OK:
         raise Gs2Error(st, "gs2_paths")
-    return {k: x.value for k, x in zip(["last_solve", "paired", "given_up", "applies"], v)}
+    return {k: x.value for k, x in zip(["last_solve", "paired", "given_up", "applies", "timings"], v)}
 
 
 def gs2_profile(enable: bool):
