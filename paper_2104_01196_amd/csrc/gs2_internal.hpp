@@ -304,7 +304,7 @@ struct Handle {
     // by color (color q's rows in chunks color_ptr[q] .. color_ptr[q + 1))
     int nlev_l = 0, nlev_u = 0, ncolors = 0;
     Perm PL, PU, PC;
-    std::vector<int64_t> color_ptr;
+    std::vector<int64_t> color_ptr, color_rows, color_nnz; // the last two: rows, and off-diagonal entries
     unsigned *tri_next = nullptr; // next chunk of the half sweeps in turn (3 counters)
     // one-launch applies of small systems: two sets of ne exchanged vectors,
     // and the applies each wavefront has done (small.hip; null: none)

@@ -1059,8 +1059,11 @@ static int build_colors(Handle &h, const gs2_csr &A, const int32_t *lcnt, const 
         color[i] = c;
         ncol = std::max(ncol, c + 1);
     }
-    std::vector<int64_t> cnt(ncol, 0), ptr(ncol + 1, 0), pos(ncol);
-    for (int64_t i = 0; i < n; ++i) cnt[color[i]]++;
+    std::vector<int64_t> cnt(ncol, 0), nnz(ncol, 0), ptr(ncol + 1, 0), pos(ncol);
+    for (int64_t i = 0; i < n; ++i) {
+        cnt[color[i]]++;
+        nnz[color[i]] += rp[i + 1] - rp[i] - 1;
+    }
     for (int c = 0; c < ncol; ++c) {
         pos[c] = ptr[c] * WAVE;
         ptr[c + 1] = ptr[c] + (cnt[c] + WAVE - 1) / WAVE;
@@ -1070,6 +1073,8 @@ static int build_colors(Handle &h, const gs2_csr &A, const int32_t *lcnt, const 
     GS2_TRY(build_perm(h, h.PC, rows, 1, false, A, lcnt, &span, s));
     h.ncolors = ncol;
     h.color_ptr = std::move(ptr);
+    h.color_rows = std::move(cnt);
+    h.color_nnz = std::move(nnz);
     return GS2_OK;
 }
 

@@ -1354,7 +1354,7 @@ struct Launch {
             const bool fwd = variant == GS2_FORWARD || (variant == GS2_SYMMETRIC && t % 2 == 0);
             const Perm &P = fwd ? h.PL : h.PU;
             const bool last = t == H - 1;
-            Prof pr(s, PK_TRI, (double)(h.L.nnz + (t ? h.U.nnz : 0)) * (sizeof(VT) + 4) +
+            Prof pr(s, PK_TRI, (double)((fwd || t ? h.L.nnz : 0) + (!fwd || t ? h.U.nnz : 0)) * (sizeof(VT) + 4) +
                                    (double)h.n * (16.0 + 2 * sizeof(AT) + (last ? 16.0 : sizeof(AT))));
             k_tri_sweep<VT, AT><<<tri_grid(P.nchunks, fwd ? h.nlev_l : h.nlev_u), TRI_TB, 0, s>>>(
                 h.stop, h.n, P, t ? byrow[(t + 1) % 2] : nullptr, last ? nullptr : byrow[t % 2], bypos[t % 2],
@@ -1378,9 +1378,11 @@ struct Launch {
                 const int c = fwd ? q : h.ncolors - 1 - q;
                 const int64_t c0 = h.color_ptr[c], c1 = h.color_ptr[c + 1];
                 const int xzero = t == 0 && q == 0;
-                Prof pr(s, PK_TRI, (double)(c1 - c0) * WAVE * (16.0 + 2 * sizeof(AT)));
                 const unsigned g = (unsigned)((c1 - c0 + TB / WAVE - 1) / (TB / WAVE));
                 double *const out = t == H - 1 ? z : nullptr;
+                Prof pr(s, PK_TRI,
+                        (xzero ? 0.0 : (double)h.color_nnz[c] * (sizeof(VT) + (h.PC.off ? 2 : 4))) +
+                            (double)h.color_rows[c] * (4.0 + 3 * sizeof(AT) + (out ? 16.0 : 0.0)));
                 if (h.PC.off)
                     k_color<VT, AT, true><<<g, TB, 0, s>>>(h.stop, c0, c1, h.PC, xzero, x, r, (AT)omega, out, h.sr);
                 else
