@@ -1048,6 +1048,7 @@ static int build_colors(Handle &h, const gs2_csr &A, const int32_t *lcnt, const 
     for (int64_t i = 0; i < n; ++i)
         for (int32_t k = rp[i]; k < rp[i + 1]; ++k) tc[fill[ci[k]]++] = (int32_t)i;
     std::vector<int32_t> color(n), seen(n + 2, -1);
+    std::vector<int64_t> cnt, nnz;
     int ncol = 0;
     for (int64_t i = 0; i < n; ++i) {
         for (int32_t k = rp[i]; k < rp[i + 1]; ++k)
@@ -1057,13 +1058,15 @@ static int build_colors(Handle &h, const gs2_csr &A, const int32_t *lcnt, const 
         int c = 0;
         while (seen[c] == i) ++c;
         color[i] = c;
-        ncol = std::max(ncol, c + 1);
+        if (c == ncol) {
+            ++ncol;
+            cnt.push_back(0);
+            nnz.push_back(0);
+        }
+        cnt[c]++;
+        nnz[c] += rp[i + 1] - rp[i] - 1;
     }
-    std::vector<int64_t> cnt(ncol, 0), nnz(ncol, 0), ptr(ncol + 1, 0), pos(ncol);
-    for (int64_t i = 0; i < n; ++i) {
-        cnt[color[i]]++;
-        nnz[color[i]] += rp[i + 1] - rp[i] - 1;
-    }
+    std::vector<int64_t> ptr(ncol + 1, 0), pos(ncol);
     for (int c = 0; c < ncol; ++c) {
         pos[c] = ptr[c] * WAVE;
         ptr[c + 1] = ptr[c] + (cnt[c] + WAVE - 1) / WAVE;

@@ -47,8 +47,10 @@ namespace {
 
 // Looks before a wavefront goes on by itself, half a microsecond or more each
 // (counted, not timed: a process that shares the device may be set aside for any
-// time): 16 ms, about what forming all vectors of the most rows takes it.
-constexpr unsigned SMALL_WAIT_POLLS = 1u << 15;
+// time): 2 ms, some times what forming the vectors takes where all wavefronts do it at
+// once.  With no look allowed an apply (SGS2(1,1) and (1,2), us) takes 41 and 79 on
+// 64 x 64 points, 485 and 768 on 256 x 256.
+constexpr unsigned SMALL_WAIT_POLLS = 1u << 12;
 // In complete() every entry waited for is stored already; a bound all the same.
 constexpr unsigned SMALL_STORED_POLLS = 1u << 22;
 constexpr int SMALL_LANES = 4; // most lanes per row whose sums are repeated
