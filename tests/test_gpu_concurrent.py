@@ -26,15 +26,14 @@ def test_streams_and_threads():
         jobs.append((dA, h, v))
 
     def work(job, stream):
+        # everything on the job's own stream: a fill left to the default stream, which
+        # nothing orders with it, could land in the middle of the solve
         dA, h, v = job
-        z, x = torch.empty_like(v), torch.zeros_like(v)
         with torch.cuda.stream(stream):
-            z.zero_()
-            x.zero_()
+            z, x = torch.full_like(v, float("nan")), torch.zeros_like(v)
             g.gs2_apply(h, v, z, stream=stream)
             info = g.gmres_solve(dA, v, x, 20, 1e-12, 45, g.PREC_GS2, h, stream=stream)
-        stream.synchronize()
-        return z, x, info["iterations"]
+            return z.cpu().numpy(), x.cpu().numpy(), info["iterations"]
 
     torch.cuda.synchronize()
     want = [work(j, torch.cuda.Stream()) for j in jobs]
@@ -44,8 +43,9 @@ def test_streams_and_threads():
         s = torch.cuda.Stream()
         for rep in range(8):
             z, x, its = work(jobs[k], s)
-            if not (torch.equal(z, want[k][0]) and torch.equal(x, want[k][1]) and its == want[k][2]):
-                wrong.append((k, rep))
+            dz, dx = (z != want[k][0]).sum(), (x != want[k][1]).sum()
+            if dz or dx or its != want[k][2]:
+                wrong.append((k, rep, int(dz), int(dx), its, float(np.nanmax(np.abs(x)))))
 
     threads = [threading.Thread(target=run, args=(k,)) for k in range(len(jobs))]
     for t in threads:
