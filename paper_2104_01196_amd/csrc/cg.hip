@@ -315,7 +315,7 @@ static int cg_impl(const gs2_csr &A, const double *b, double *x, double rtol, in
     // handle, no memory for a copy, or rows that are no longer strictly sorted.
     bool copied = P != nullptr;
     auto copy = [&]() -> int {
-        const int e = prepare_product(W->prod, A, P->h.spmv_fmt, s, &st->flag);
+        const int e = prepare_product(W->prod, A, P->h.spmv_fmt, s, &st->flag, false);
         if (e != GS2_ERR_NOMEM) return e;
         (void)hipGetLastError();
         copied = false;

@@ -1233,8 +1233,13 @@ static int build_layout(SellA &S, const gs2_csr &A, int sel, const std::vector<i
 // and number of offsets); GS2_FORMAT_SELL / _DIA / _BLOCK3 force a layout
 // (the diagonal one at two rows per lane, the block one at two nodes per
 // lane, falling back to sliced ELL when A does not qualify).  Rows that are
-// not strictly sorted never qualify.
-int prepare_product(Product &W, const gs2_csr &A, int fmt, hipStream_t s, int *flag)
+// not strictly sorted never qualify.  Without `time` (conjugate gradients, which
+// may be few steps) an automatic choice not yet known is not timed: the diagonal
+// copy at two rows per lane, else the block copy at one node per lane, else sliced
+// ELL at the rule's lanes.  40 steps of CG with the rule and with the timed choice,
+// ms: 120^3 Laplacian 4.95 and 4.93, 160^3 10.76 and 10.76, 700^2 plane 2.12 and
+// 2.13; the timing took 5 to 17 ms of a first solve.
+int prepare_product(Product &W, const gs2_csr &A, int fmt, hipStream_t s, int *flag, bool time)
 {
     SellA &S = W.A;
     if ((flag || (S.rp == A.rowptr && S.ci == A.colind)) && S.n == A.n && S.nnz == A.nnz && (S.val || S.dval) &&
@@ -1260,6 +1265,8 @@ int prepare_product(Product &W, const gs2_csr &A, int fmt, hipStream_t s, int *f
         sel = -12;
     } else if (fmt == GS2_FORMAT_AUTO && A.n >= SPMV_TUNE_MIN_ROWS && choice_get(key, &sel)) {
         tuned = 1;
+    } else if (fmt == GS2_FORMAT_AUTO && A.n >= SPMV_TUNE_MIN_ROWS && !time) {
+        sel = dia_ok ? -2 : b3_ok ? -11 : K0;
     } else if (fmt == GS2_FORMAT_AUTO && A.n >= SPMV_TUNE_MIN_ROWS) {
         std::vector<int> cands{K0};
         if (K0 < WAVE) cands.push_back(2 * K0);

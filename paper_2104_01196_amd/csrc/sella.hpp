@@ -118,7 +118,7 @@ struct Product {
 // FILL_CHANGED: built for another pattern, to be built anew (fmt_req = -1);
 // FILL_UNSORTED: A's rows are not strictly sorted, which only the CSR arrays
 // or sliced ELL can hold.  Neither makes a product read out of bounds.
-int prepare_product(Product &W, const gs2_csr &A, int fmt, hipStream_t s, int *flag = nullptr);
+int prepare_product(Product &W, const gs2_csr &A, int fmt, hipStream_t s, int *flag = nullptr, bool time = true);
 int product_dot(const Product &W, const double *z, double *w, const int *stop, double *part, hipStream_t s);
 int product_resid(const Product &W, const double *x, const double *b, double *r, double *part, hipStream_t s);
 

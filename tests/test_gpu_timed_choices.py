@@ -25,3 +25,16 @@ def test_timed_per_size(sizes, each):
                 g.gmres_solve(A, b, torch.zeros_like(b), 16, 1e-8, 5, g.PREC_GS2, h)
                 assert g.gs2_paths(h)["timings"] == timings
             assert g.gs2_gmres_schedule(h)["tuned"] == 1
+
+
+def test_conjugate_gradients_time_nothing():
+    """A solve by conjugate gradients takes a layout by rule where none is known: gmres_solve then still
+    times the size, and the layout it found serves later solves."""
+    n = 70_011
+    A = g.DeviceCSR.from_host(laplace1d(n))
+    b = torch.as_tensor(np.random.default_rng(1).standard_normal(n), device=DEV)
+    h = g.gs2_setup(A, variant=g.SYMMETRIC)
+    g.cg_solve(A, b, torch.zeros_like(b), 1e-8, 5, g.PREC_GS2, h)
+    g.gmres_solve(A, b, torch.zeros_like(b), 16, 1e-8, 5, g.PREC_GS2, h)
+    assert g.gs2_paths(h)["timings"] == 1
+    g.cg_solve(A, b, torch.zeros_like(b), 1e-8, 5, g.PREC_GS2, g.gs2_setup(A, variant=g.SYMMETRIC))
