@@ -662,8 +662,8 @@ __global__ __launch_bounds__(KT) void k_b3_spmv(DiaAView A, int64_t n, const dou
 }
 
 // w = A z on sliced ELL with the workgroup's sum of w.z in part[blockIdx.x].
-template <int SEL>
-__global__ __launch_bounds__(KT) void k_sell_spmv_dot(SellAView A, DiaAView D, int64_t n, const double *__restrict__ z,
+template <int K, bool NT>
+__global__ __launch_bounds__(KT) void k_sell_spmv_dot(SellAView A, int64_t n, const double *__restrict__ z,
                                                       double *__restrict__ w, const int *__restrict__ stop,
                                                       double *__restrict__ part)
 {
@@ -671,7 +671,7 @@ __global__ __launch_bounds__(KT) void k_sell_spmv_dot(SellAView A, DiaAView D, i
     __shared__ double red[KT / WAVE];
     if (stop && *stop) return;
     const int64_t r0 = (int64_t)blockIdx.x * RB;
-    mat_rows<SEL, KT / WAVE>(A, D, n, r0, z, wl);
+    sella_rows<K, RB, KT / WAVE, NT>(A, n, r0, z, wl);
     double s = 0.0;
     for (int i = threadIdx.x; i < RB; i += KT)
         if (r0 + i < n) {
@@ -1304,7 +1304,19 @@ int prepare_product(Product &W, const gs2_csr &A, int fmt, hipStream_t s, int *f
     return GS2_OK;
 }
 
-int product_dot(const Product &W, const double *z, double *w, const int *stop, double *part, hipStream_t s)
+// In conjugate gradients nothing as large as a Krylov basis runs between two
+// products, so a sliced-ELL copy stays in the last-level cache (256 MB) if it is let and
+// all that an iteration reads fits there.  An iteration in us, with the copy cached and
+// streamed past: 300,000 rows of 7 random entries 54.5 and 64.2 (60 on the CSR
+// arrays), of 15 77 and 94 (89), 150,000 rows of 31 104 and 122 (123).  40 iterations
+// in ms, with the copy, the triangles and six vectors in MB: 400,000 rows of 15, 212
+// MB 6.23 and 6.87 (6.67), 500,000, 265 MB 7.93 and 7.50; 7-point Laplacian 108^3, 217 MB
+// 4.26 and 4.52, 112^3, 240 MB 5.02 and 4.83, 120^3 without triangles, 227 MB 3.39 and
+// 3.64.
+constexpr double CG_CACHED_BYTES = 230e6;
+
+int product_dot(const Product &W, const double *z, double *w, const int *stop, double *part, double beside,
+                hipStream_t s)
 {
     const int64_t n = W.A.n;
     const SellAView AS = view(W.A);
@@ -1320,7 +1332,21 @@ int product_dot(const Product &W, const double *z, double *w, const int *stop, d
     else if (K == -1) k_dia_spmv<1, 0, true><<<gD, KT, 0, s>>>(AD, n, z, w, nullptr, stop, part);
     else {
         const unsigned g = (unsigned)((n + RB - 1) / RB);
-        GS2_SPMV_DISPATCH(K, k_sell_spmv_dot, g, AS, AD, n, z, w, stop, part);
+        const bool nt = 12.0 * (double)W.A.padded + beside > CG_CACHED_BYTES;
+        auto go = [&](auto k) {
+            constexpr int KL = decltype(k)::value;
+            if (nt) k_sell_spmv_dot<KL, true><<<g, KT, 0, s>>>(AS, n, z, w, stop, part);
+            else k_sell_spmv_dot<KL, false><<<g, KT, 0, s>>>(AS, n, z, w, stop, part);
+        };
+        switch (K) {
+        case 1: go(std::integral_constant<int, 1>{}); break;
+        case 2: go(std::integral_constant<int, 2>{}); break;
+        case 4: go(std::integral_constant<int, 4>{}); break;
+        case 8: go(std::integral_constant<int, 8>{}); break;
+        case 16: go(std::integral_constant<int, 16>{}); break;
+        case 32: go(std::integral_constant<int, 32>{}); break;
+        default: go(std::integral_constant<int, 64>{}); break;
+        }
         return (int)g;
     }
     return (int)gD;

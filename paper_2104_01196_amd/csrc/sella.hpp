@@ -119,7 +119,9 @@ struct Product {
 // FILL_UNSORTED: A's rows are not strictly sorted, which only the CSR arrays
 // or sliced ELL can hold.  Neither makes a product read out of bounds.
 int prepare_product(Product &W, const gs2_csr &A, int fmt, hipStream_t s, int *flag = nullptr, bool time = true);
-int product_dot(const Product &W, const double *z, double *w, const int *stop, double *part, hipStream_t s);
+// beside: bytes that are read between two products.
+int product_dot(const Product &W, const double *z, double *w, const int *stop, double *part, double beside,
+                hipStream_t s);
 int product_resid(const Product &W, const double *x, const double *b, double *r, double *part, hipStream_t s);
 
 // Building blocks of the copy (sella.hip); the Krylov solver picks among
@@ -147,10 +149,10 @@ int sella_fill_values(SellA &S, const gs2_csr &A, bool with_col, hipStream_t s, 
 // ybuf[i] = (A z)[r0 + i] for the RB rows of the workgroup starting at r0
 // (0 past n), into LDS.  The workgroup's NW wavefronts take consecutive
 // groups of RB / C / NW slices; each wavefront works on four slices at once
-// so that their loads are in flight together.  The matrix is streamed with
+// so that their loads are in flight together.  NT: the matrix is streamed with
 // non-temporal loads, which leaves the caches to the gathered z.  Ends with
 // a barrier.
-template <int K, int RB, int NW>
+template <int K, int RB, int NW, bool NT = true>
 __device__ __forceinline__ void sella_rows(const SellAView A, int64_t n, int64_t r0, const double *__restrict__ z,
                                            double *ybuf)
 {
@@ -180,7 +182,8 @@ __device__ __forceinline__ void sella_rows(const SellAView A, int64_t n, int64_t
             for (int u = 0; u < U; ++u) {
                 if (t < steps[u]) {
                     const int64_t p = beg[u] + (int64_t)t * WAVE + ln;
-                    acc[u] += __builtin_nontemporal_load(&A.val[p]) * z[__builtin_nontemporal_load(&A.col[p])];
+                    if constexpr (NT) acc[u] += __builtin_nontemporal_load(&A.val[p]) * z[__builtin_nontemporal_load(&A.col[p])];
+                    else acc[u] += A.val[p] * z[A.col[p]];
                 }
             }
         }
