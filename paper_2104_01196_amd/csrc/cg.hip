@@ -313,10 +313,12 @@ static int cg_impl(const gs2_csr &A, const double *b, double *x, double rtol, in
     // layout that suits it (as gmres_solve's): 20 against 46 us per
     // product on a 120^3 7-point matrix, 77 against 89 us per iteration on 300,000
     // rows of 15 random entries.  On the CSR arrays where there is no
-    // handle, no memory for a copy, or rows that are no longer strictly sorted.
+    // handle, no memory for a copy, rows that are no longer strictly sorted, or a
+    // few rows much longer than the others (prepare_product).
     bool copied = P != nullptr;
     auto copy = [&]() -> int {
         const int e = prepare_product(W->prod, A, P->h.spmv_fmt, s, &st->flag, false);
+        if (e == GS2_OK) copied = W->prod.built();
         if (e != GS2_ERR_NOMEM) return e;
         (void)hipGetLastError();
         copied = false;

@@ -1247,6 +1247,14 @@ int prepare_product(Product &W, const gs2_csr &A, int fmt, hipStream_t s, int *f
         return sella_fill_values(S, A, false, s, flag);
     sella_free(S);
     W.fmt_req = -1;
+    // Conjugate gradients have the CSR arrays, with several lanes per row, to fall back
+    // on: a row a few times as long as the others is taken by as few lanes as those in
+    // sliced ELL.  An iteration in us on CSR and on sliced ELL, 200,000 rows of 7 entries,
+    // one of them with 28, 48, 168, 1008: 57.8 and 59.5, 58.1 and 69.8, 62.6 and
+    // 134, 115 and 566; of 15, one with 53, 93, 173: 85.3 and 80.6, 85.1 and 90.6, 85.4 and
+    // 112.  Remembered by the sizes only: the arrays are right for any pattern.
+    const bool csr_better = !time && fmt == GS2_FORMAT_AUTO;
+    if (csr_better && W.csr_n == A.n && W.csr_nnz == A.nnz) return GS2_OK;
     std::vector<int> offs;
     Pattern pat;
     if (fmt != GS2_FORMAT_SELL) GS2_TRY(scan_pattern(A, nullptr, nullptr, nullptr, nullptr, W.pat, pat, s));
@@ -1255,6 +1263,11 @@ int prepare_product(Product &W, const gs2_csr &A, int fmt, hipStream_t s, int *f
     const bool sorted = fmt != GS2_FORMAT_SELL && !pat.err;
     const bool dia_ok = sorted && fmt != GS2_FORMAT_BLOCK3 && sella_dia_offsets(A, pat, offs);
     const bool b3_ok = sorted && !dia_ok && fmt != GS2_FORMAT_DIA && sella_b3_offsets(A, pat, offs);
+    if (csr_better && !dia_ok && !b3_ok && pat.maxlen + 1 > std::max(24.0, 4.0 * (double)A.nnz / (double)A.n)) {
+        W.csr_n = A.n;
+        W.csr_nnz = A.nnz;
+        return GS2_OK;
+    }
     const int K0 = sella_rule_lanes(A);
     int sel = K0, tuned = 0;
     const std::string key = "A_" + size_key(A.n, A.nnz, pat.maxlen) + "_d" +

@@ -104,6 +104,8 @@ struct Product {
     SellA A;
     int fmt_req = -1; // the layout request it was built for
     int timings = 0;  // choices timed for it
+    int64_t csr_n = -1, csr_nnz = -1; // sizes for which there is no copy (not `time`)
+    bool built() const { return A.val || A.dval; }
     double *in = nullptr, *out = nullptr, *part = nullptr;
     PatternDev *pat = nullptr;
 };
@@ -118,6 +120,9 @@ struct Product {
 // FILL_CHANGED: built for another pattern, to be built anew (fmt_req = -1);
 // FILL_UNSORTED: A's rows are not strictly sorted, which only the CSR arrays
 // or sliced ELL can hold.  Neither makes a product read out of bounds.
+//
+// Without `time`, no layout is timed and none is built (W.built()) where the CSR
+// arrays are better.
 int prepare_product(Product &W, const gs2_csr &A, int fmt, hipStream_t s, int *flag = nullptr, bool time = true);
 // beside: bytes that are read between two products.
 int product_dot(const Product &W, const double *z, double *w, const int *stop, double *part, double beside,
