@@ -299,7 +299,7 @@ __device__ __forceinline__ Range row_range(const Rows &A, int part, int64_t i)
 // Stored entries of each slice of a part: 64 * ceil(longest row / K), one
 // lane per row.  The extra element at index nslices is zero so that an
 // exclusive scan yields the end.  With st, adds up the part's entries and their
-// smallest and largest col - row (one wavefront after the other: only where what
+// smallest and largest col - row (one workgroup after the other: only where what
 // the pattern scan found does not hold, with several blocks).
 struct PartStats {
     unsigned long long total;
@@ -323,17 +323,26 @@ __global__ __launch_bounds__(256) void k_slice_len(Rows A, int part, int64_t nsl
     int m = c;
     for (int o = 1; o < C; o <<= 1) m = max(m, __shfl_xor(m, o));
     if (st) {
-        int sum = c;
+        __shared__ int sum, los, his;
+        if (threadIdx.x == 0) sum = los = his = 0;
+        __syncthreads();
+        int t = c;
         for (int o = 1; o < WAVE; o <<= 1) {
-            sum += __shfl_xor(sum, o);
+            t += __shfl_xor(t, o);
             lo = min(lo, __shfl_xor(lo, o));
             hi = max(hi, __shfl_xor(hi, o));
         }
-        if (threadIdx.x % WAVE == 0 && sum) {
+        if (threadIdx.x % WAVE == 0 && t) {
+            atomicAdd(&sum, t);
+            atomicMin(&los, lo);
+            atomicMax(&his, hi);
+        }
+        __syncthreads();
+        if (threadIdx.x == 0 && sum) {
             atomicAdd(&st->total, (unsigned long long)sum);
-            // a plain read first: after a few wavefronts the extremes stand
-            if (lo < st->lo) atomicMin(&st->lo, lo);
-            if (hi > st->hi) atomicMax(&st->hi, hi);
+            // a plain read first: after a few workgroups the extremes stand
+            if (los < st->lo) atomicMin(&st->lo, los);
+            if (his > st->hi) atomicMax(&st->hi, his);
         }
     }
     if (row % C == 0 && row / C <= nslices) len[row / C] = row / C == nslices ? 0 : (int64_t)WAVE * ((m + K - 1) / K);
