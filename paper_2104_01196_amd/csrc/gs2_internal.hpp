@@ -254,7 +254,7 @@ constexpr uint16_t PERM_PAD16 = 0xffff;
 struct Perm {
     int64_t nchunks = 0;
     int32_t *rows = nullptr; // 64 nchunks row indices, -1 for none
-    int64_t *ptr = nullptr;  // nchunks + 1
+    int64_t *ptr = nullptr;  // nchunks + 1 (behind rows; col and off behind val)
     int32_t *col = nullptr;
     uint16_t *off = nullptr; // in place of col
     int off_min = 0;
@@ -304,6 +304,9 @@ struct Handle {
     // by color (color q's rows in chunks color_ptr[q] .. color_ptr[q + 1))
     int nlev_l = 0, nlev_u = 0, ncolors = 0;
     Perm PL, PU, PC;
+    // most main entries of a row of each chunk of PL and of PU, in their allocations
+    // (null: no row has more than 8 entries)
+    int32_t *mains_l = nullptr, *mains_u = nullptr;
     std::vector<int64_t> color_ptr, color_rows, color_nnz; // the last two: rows, and off-diagonal entries
     unsigned *tri_next = nullptr; // next chunk of the half sweeps in turn (3 counters)
     // one-launch applies of small systems: two sets of ne exchanged vectors,

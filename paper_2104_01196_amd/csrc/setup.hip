@@ -922,30 +922,39 @@ static int read_err(int *err, hipStream_t s)
 
 void free_perm(Perm &P)
 {
-    for (void *p : {(void *)P.rows, (void *)P.ptr, (void *)P.col, (void *)P.off, P.val})
+    for (void *p : {(void *)P.rows, P.val}) // the others lie behind these
         if (p) (void)hipFree(p);
     P = Perm{};
 }
 
 // Stored entries of each chunk: 64 times the longest of its rows (off-diagonal
-// entries); zero at index nchunks, so that an exclusive scan yields the end.
+// entries); zero at index nchunks, so that an exclusive scan yields the end.  And
+// the most main entries of its rows.
 __global__ __launch_bounds__(256) void k_perm_len(int64_t nchunks, const int32_t *__restrict__ rows,
-                                                  const int32_t *__restrict__ rp, int64_t *__restrict__ len)
+                                                  const int32_t *__restrict__ rp, const int32_t *__restrict__ lcnt,
+                                                  int lower, int64_t *__restrict__ len, int32_t *__restrict__ mains)
 {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t c = g / WAVE;
     if (c > nchunks) return;
     const int i = c < nchunks ? rows[g] : -1;
     int m = i < 0 ? 0 : rp[i + 1] - rp[i] - 1;
-    for (int o = 1; o < WAVE; o <<= 1) m = max(m, __shfl_xor(m, o));
-    if (g % WAVE == 0) len[c] = (int64_t)WAVE * m;
+    int mc = i < 0 ? 0 : lower ? lcnt[i] : m - lcnt[i];
+    for (int o = 1; o < WAVE; o <<= 1) {
+        m = max(m, __shfl_xor(m, o));
+        mc = max(mc, __shfl_xor(mc, o));
+    }
+    if (g % WAVE == 0) {
+        len[c] = (int64_t)WAVE * m;
+        if (mains && c < nchunks) mains[c] = mc;
+    }
 }
 
-// One thread per position: the row's entries, the main triangle's first
-// (lower = 1: the lower triangle is the main one), scaled and rounded as in
-// k_fill.  A main entry's column goes through `place` when it is given.
+// One workgroup per chunk, a thread per position and every fourth entry: the row's
+// entries, the main triangle's first (lower = 1: the lower triangle is the main
+// one), scaled and rounded as in k_fill.  A main entry's column goes through `place` when it is given.
 template <typename VT>
-__global__ __launch_bounds__(256) void k_perm_fill(int64_t nchunks, const int32_t *__restrict__ rows,
+__global__ __launch_bounds__(256) void k_perm_fill(const int32_t *__restrict__ rows,
                                                    const int64_t *__restrict__ ptr, const int32_t *__restrict__ rp,
                                                    const int32_t *__restrict__ ci, const double *__restrict__ va,
                                                    const int32_t *__restrict__ lcnt, int lower,
@@ -954,18 +963,17 @@ __global__ __launch_bounds__(256) void k_perm_fill(int64_t nchunks, const int32_
                                                    int32_t *__restrict__ col, uint16_t *__restrict__ off, int off_min,
                                                    VT *__restrict__ val)
 {
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t c = g / WAVE;
-    if (c >= nchunks) return;
-    const int i = rows[g];
+    const int64_t c = blockIdx.x;
+    const int ln = threadIdx.x % WAVE;
+    const int i = rows[c * WAVE + ln];
     const int64_t beg = ptr[c];
     const int steps = (int)((ptr[c + 1] - beg) / WAVE);
     const int b = i < 0 ? 0 : rp[i], lc = i < 0 ? 0 : lcnt[i], tot = i < 0 ? 0 : rp[i + 1] - b - 1, uc = tot - lc;
     const int mc = lower ? lc : uc;
     const double srow = i < 0 ? 0.0 : sl[i];
     int ovf = 0; // the natural-order triangles report it
-    for (int t = 0; t < steps; ++t) {
-        const int64_t pos = beg + (int64_t)t * WAVE + g % WAVE;
+    for (int t = threadIdx.x / WAVE; t < steps; t += 256 / WAVE) {
+        const int64_t pos = beg + (int64_t)t * WAVE + ln;
         if (t >= tot) {
             if (off) off[pos] = PERM_PAD16;
             else col[pos] = PERM_PAD;
@@ -982,57 +990,65 @@ __global__ __launch_bounds__(256) void k_perm_fill(int64_t nchunks, const int32_
 }
 
 // The rows in the given order (-1: no row), 64 per chunk, with their entries;
-// by_place: the main entries name positions of this order instead of rows;
+// by_place: the main entries name positions of this order instead of rows; mains,
+// if not null: the chunks' longest main parts;
 // span: the pattern's smallest and largest col - row, for 16-bit offsets where
 // they fit (null: columns).
 static int build_perm(Handle &h, Perm &P, std::vector<int32_t> &order, int lower, bool by_place, const gs2_csr &A,
-                      const int32_t *lcnt, const Pattern *span, hipStream_t s)
+                      const int32_t *lcnt, const Pattern *span, int32_t **mains, hipStream_t s)
 {
+    // three allocations (0.1 ms each): what stays of the rows, what stays of their
+    // entries, and what goes with this scope
     struct Tmp {
-        int32_t *place = nullptr;
         int64_t *len = nullptr;
+        int32_t *place = nullptr;
         ~Tmp()
         {
-            if (place) (void)hipFree(place);
             if (len) (void)hipFree(len);
         }
     } tmp;
-    if (by_place) {
-        std::vector<int32_t> place(h.n);
+    std::vector<int32_t> place(by_place ? h.n : 0);
+    if (by_place)
         for (size_t q = 0; q < order.size(); ++q)
             if (order[q] >= 0) place[order[q]] = (int32_t)q;
-        GS2_TRY_HIP(hipMalloc(&tmp.place, sizeof(int32_t) * place.size()));
-        GS2_TRY_HIP(hipMemcpyAsync(tmp.place, place.data(), sizeof(int32_t) * place.size(), hipMemcpyHostToDevice, s));
-        GS2_TRY_HIP(hipStreamSynchronize(s));
-    }
     order.resize((order.size() + WAVE - 1) / WAVE * WAVE, -1);
     P.nchunks = (int64_t)order.size() / WAVE;
     int64_t total = 0;
-    GS2_TRY_HIP(hipMalloc(&P.rows, sizeof(int32_t) * order.size()));
-    GS2_TRY_HIP(hipMalloc(&P.ptr, sizeof(int64_t) * (P.nchunks + 1)));
+    const size_t lens = aligned(sizeof(int64_t) * (P.nchunks + 1 + scan_tmp(P.nchunks + 1)));
+    GS2_TRY_HIP(hipMalloc(&tmp.len, lens + sizeof(int32_t) * place.size()));
+    if (by_place) {
+        tmp.place = (int32_t *)((char *)tmp.len + lens);
+        GS2_TRY_HIP(hipMemcpyAsync(tmp.place, place.data(), sizeof(int32_t) * place.size(), hipMemcpyHostToDevice, s));
+    }
+    const size_t rb = aligned(sizeof(int32_t) * order.size()), pb = aligned(sizeof(int64_t) * (P.nchunks + 1));
+    GS2_TRY_HIP(hipMalloc(&P.rows, rb + pb + (mains ? sizeof(int32_t) * P.nchunks : 0)));
+    P.ptr = (int64_t *)((char *)P.rows + rb);
+    if (mains) *mains = (int32_t *)((char *)P.rows + rb + pb);
     GS2_TRY_HIP(hipMemcpyAsync(P.rows, order.data(), sizeof(int32_t) * order.size(), hipMemcpyHostToDevice, s));
-    GS2_TRY_HIP(hipMalloc(&tmp.len, sizeof(int64_t) * (P.nchunks + 1 + scan_tmp(P.nchunks + 1))));
-    k_perm_len<<<(unsigned)(((P.nchunks + 1) * WAVE + 255) / 256), 256, 0, s>>>(P.nchunks, P.rows, A.rowptr, tmp.len);
+    k_perm_len<<<(unsigned)(((P.nchunks + 1) * WAVE + 255) / 256), 256, 0, s>>>(P.nchunks, P.rows, A.rowptr, lcnt, lower,
+                                                                                   tmp.len, mains ? *mains : nullptr);
     GS2_TRY(exclusive_scan_i64(tmp.len, P.ptr, P.nchunks + 1, tmp.len + P.nchunks + 1, s));
     GS2_TRY_HIP(hipMemcpyAsync(&total, P.ptr + P.nchunks, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    GS2_TRY_HIP(hipStreamSynchronize(s)); // `order` may go
+    GS2_TRY_HIP(hipStreamSynchronize(s)); // `order` and `place` may go
     const size_t vb = h.precision == GS2_FP64 ? 8 : h.precision == GS2_FP32 ? 4 : 2;
-    if (span && (int64_t)span->hi - span->lo < PERM_PAD16) {
+    const size_t cnt = (size_t)std::max<int64_t>(total, WAVE), vals = aligned(vb * cnt);
+    const bool narrow = span && (int64_t)span->hi - span->lo < PERM_PAD16;
+    GS2_TRY_HIP(hipMalloc(&P.val, vals + (narrow ? sizeof(uint16_t) : sizeof(int32_t)) * cnt));
+    if (narrow) {
         P.off_min = span->lo;
-        GS2_TRY_HIP(hipMalloc(&P.off, sizeof(uint16_t) * std::max<int64_t>(total, WAVE)));
+        P.off = (uint16_t *)((char *)P.val + vals);
     } else {
-        GS2_TRY_HIP(hipMalloc(&P.col, sizeof(int32_t) * std::max<int64_t>(total, WAVE)));
+        P.col = (int32_t *)((char *)P.val + vals);
     }
-    GS2_TRY_HIP(hipMalloc(&P.val, vb * std::max<int64_t>(total, WAVE)));
-    const unsigned g = (unsigned)((P.nchunks * WAVE + 255) / 256);
+    const unsigned g = (unsigned)P.nchunks;
     if (h.precision == GS2_FP64)
-        k_perm_fill<double><<<g, 256, 0, s>>>(P.nchunks, P.rows, P.ptr, A.rowptr, A.colind, A.val, lcnt, lower,
+        k_perm_fill<double><<<g, 256, 0, s>>>(P.rows, P.ptr, A.rowptr, A.colind, A.val, lcnt, lower,
                                               tmp.place, h.sl, h.sr, P.col, P.off, P.off_min, (double *)P.val);
     else if (h.precision == GS2_FP32)
-        k_perm_fill<float><<<g, 256, 0, s>>>(P.nchunks, P.rows, P.ptr, A.rowptr, A.colind, A.val, lcnt, lower,
+        k_perm_fill<float><<<g, 256, 0, s>>>(P.rows, P.ptr, A.rowptr, A.colind, A.val, lcnt, lower,
                                              tmp.place, h.sl, h.sr, P.col, P.off, P.off_min, (float *)P.val);
     else
-        k_perm_fill<_Float16><<<g, 256, 0, s>>>(P.nchunks, P.rows, P.ptr, A.rowptr, A.colind, A.val, lcnt, lower,
+        k_perm_fill<_Float16><<<g, 256, 0, s>>>(P.rows, P.ptr, A.rowptr, A.colind, A.val, lcnt, lower,
                                                 tmp.place, h.sl, h.sr, P.col, P.off, P.off_min, (_Float16 *)P.val);
     GS2_TRY_HIP(hipGetLastError());
     GS2_TRY_HIP(hipStreamSynchronize(s)); // tmp goes with this scope
@@ -1082,7 +1098,7 @@ static int build_colors(Handle &h, const gs2_csr &A, const int32_t *lcnt, const 
     }
     std::vector<int32_t> rows(ptr[ncol] * WAVE, -1);
     for (int64_t i = 0; i < n; ++i) rows[pos[color[i]]++] = (int32_t)i;
-    GS2_TRY(build_perm(h, h.PC, rows, 1, false, A, lcnt, &span, s));
+    GS2_TRY(build_perm(h, h.PC, rows, 1, false, A, lcnt, &span, nullptr, s));
     h.ncolors = ncol;
     h.color_ptr = std::move(ptr);
     h.color_rows = std::move(cnt);
@@ -1119,7 +1135,8 @@ static int build_levels(Handle &h, const gs2_csr &A, const int32_t *lcnt, const 
         for (int l = 0; l < nlev; ++l) pos[l + 1] += pos[l];
         std::vector<int32_t> rows(n);
         for (int64_t i = 0; i < n; ++i) rows[pos[lev[i]]++] = (int32_t)i;
-        GS2_TRY(build_perm(h, lower ? h.PL : h.PU, rows, lower, true, A, lcnt, nullptr, s));
+        GS2_TRY(build_perm(h, lower ? h.PL : h.PU, rows, lower, true, A, lcnt, nullptr,
+                           span.maxlen <= 8 ? nullptr : lower ? &h.mains_l : &h.mains_u, s));
         (lower ? h.nlev_l : h.nlev_u) = nlev;
     }
     return build_colors(h, A, lcnt, rp, ci, span, s);

@@ -13,6 +13,7 @@
 // needs no SpMV.  Every pass reads its triangle exactly once.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "dcgs_state.hpp"
 #include "gs2_internal.hpp"
@@ -282,20 +283,29 @@ __global__ void k_fill_zero(const int *__restrict__ stop, int64_t n, AT *__restr
 // it, row update) against 8 us for a launch per level.  96^3 Laplacian, 286
 // levels per half sweep, symmetric sweep: 4.57 ms with a launch per level,
 // 0.82 ms here.
+//
+// Long rows: what a row still reads once its last dependency is there is on the
+// chain too.  A first half sweep leaves out the other triangle's entries (mains),
+// and more than TRI_LONG entries a row on average are taken 16 at a time instead of 8.
+// Forward and symmetric sweep in float64, ms, a launch per level, without either, and
+// with both: elasticity (81 entries a row) of 8^3 nodes 1.18, 1.83, 0.85 and 3.21,
+// 4.23, 2.84, of 36^3 18.7, 9.2, 4.3 and 59, 23, 15; 60,000 rows of 15 4.1, 2.3, 1.1 and
+// 9.0, 4.8, 3.5.
 constexpr int TRI_TB = 256;
+constexpr int TRI_LONG = 12;
 constexpr unsigned TRI_WAIT_POLLS = 1u << 22; // looks, half a microsecond or more each
 
-template <typename VT, typename AT>
+template <typename VT, typename AT, int U, bool MAINS>
 __global__ __launch_bounds__(TRI_TB) void k_tri_sweep(const int *__restrict__ stop, int64_t n, Perm P,
                                                       const AT *__restrict__ xold, AT *__restrict__ xnew, AT *xpos,
                                                       AT *__restrict__ xfill,
                                                       const double *__restrict__ v, const double *__restrict__ sl,
                                                       const double *__restrict__ sr, AT w, double *__restrict__ z,
-                                                      unsigned *next, unsigned *next_after)
+                                                      unsigned *next, unsigned *next_after,
+                                                      const int32_t *__restrict__ mains)
 {
     using BT = typename Bits<AT>::T;
     constexpr BT NR = Bits<AT>::not_ready;
-    constexpr int U = 8; // entries per block: a 7-point row in one
     if (stop && *stop) return;
     const int lane = threadIdx.x & (WAVE - 1);
     BT *xb = reinterpret_cast<BT *>(xpos);
@@ -311,7 +321,8 @@ __global__ __launch_bounds__(TRI_TB) void k_tri_sweep(const int *__restrict__ st
         const int pos = (int)(ch * WAVE) + lane;
         const int i = P.rows[pos];
         const int64_t beg = P.ptr[ch];
-        const int steps = (int)((P.ptr[ch + 1] - beg) / WAVE);
+        // without a previous iterate a row's main entries, which come first, are all
+        const int steps = xold || !MAINS ? (int)((P.ptr[ch + 1] - beg) / WAVE) : mains[ch];
         if (xfill && pos < n) reinterpret_cast<BT *>(xfill)[pos] = NR;
         const AT r = i < 0 ? AT(0) : (AT)(v[i] * sl[i]), xo = (xold && i >= 0) ? xold[i] : AT(0);
         const double s_out = (z && i >= 0) ? sr[i] : 0.0;
@@ -1356,10 +1367,16 @@ struct Launch {
             const bool last = t == H - 1;
             Prof pr(s, PK_TRI, (double)((fwd || t ? h.L.nnz : 0) + (!fwd || t ? h.U.nnz : 0)) * (sizeof(VT) + 4) +
                                    (double)h.n * (16.0 + 2 * sizeof(AT) + (last ? 16.0 : sizeof(AT))));
-            k_tri_sweep<VT, AT><<<tri_grid(P.nchunks, fwd ? h.nlev_l : h.nlev_u), TRI_TB, 0, s>>>(
-                h.stop, h.n, P, t ? byrow[(t + 1) % 2] : nullptr, last ? nullptr : byrow[t % 2], bypos[t % 2],
-                last ? nullptr : bypos[(t + 1) % 2], v, h.sl, h.sr, (AT)omega, last ? z : nullptr,
-                h.tri_next + t % 3, h.tri_next + (t + 1) % 3);
+            const int32_t *mains = fwd ? h.mains_l : h.mains_u;
+            auto go = [&](auto u, auto counted) {
+                k_tri_sweep<VT, AT, decltype(u)::value, decltype(counted)::value><<<tri_grid(P.nchunks, fwd ? h.nlev_l : h.nlev_u), TRI_TB, 0, s>>>(
+                    h.stop, h.n, P, t ? byrow[(t + 1) % 2] : nullptr, last ? nullptr : byrow[t % 2], bypos[t % 2],
+                    last ? nullptr : bypos[(t + 1) % 2], v, h.sl, h.sr, (AT)omega, last ? z : nullptr,
+                    h.tri_next + t % 3, h.tri_next + (t + 1) % 3, mains);
+            };
+            if (!mains) go(std::integral_constant<int, 8>{}, std::false_type{});
+            else if (h.L.nnz + h.U.nnz <= TRI_LONG * h.n) go(std::integral_constant<int, 8>{}, std::true_type{});
+            else go(std::integral_constant<int, 16>{}, std::true_type{});
         }
         return GS2_OK;
     }
