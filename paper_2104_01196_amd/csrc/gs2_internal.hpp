@@ -348,13 +348,14 @@ int64_t scan_tmp(int64_t m);
 // What one pass over a CSR pattern finds (scan_pattern): error bits, entries
 // of the strict triangles, the longest row without its diagonal, the smallest
 // and largest col - row, the distinct col - row (0 among them if a diagonal
-// entry exists) and, for n a multiple of 3, the distinct node offsets
+// entry exists), the entries more than 1024 columns from the diagonal (far) and,
+// for n a multiple of 3, the distinct node offsets
 // c/3 - r/3 below and above the diagonal; all ascending.  many_d / many_b:
 // more than two triangles of DIA_MAX could hold, lists not complete; nor are
 // they where err is set (an entry whose column does not increase is left out).
 struct Pattern {
     int err = 0, maxlen = 0, lo = 0, hi = 0;
-    int64_t nl = 0, nu = 0;
+    int64_t nl = 0, nu = 0, far = 0;
     bool many_d = false, many_b = false;
     std::vector<int> d, bl, bu;
 };
@@ -389,7 +390,15 @@ constexpr int SMALL_MAX_EX = 8;
 // a trip.  60000 rows of 16 others, SGS2(1,1): 8.6 us in one launch, 13.3 pass
 // by pass (float32: 11.8, 14.0); of 24 others 11.5, 13.4 (float32: 21.0, 14.0).
 constexpr int SMALL_MAX_ROW = 16;
+// Without a stencil's few distances, entries far from the diagonal cost a line past
+// the caches each; passes launched one by one find them in an L2.  SGS2(1,1), a call in
+// us pass by pass and in one launch, random columns: float64, 78,000 far entries
+// 12.5 and 12.3, 104,000 12.5 and 14.3, 209,000 13.4 and 16.8, 350,000 16.3 and 22.0;
+// float32, 232,000 17.5 and 17.3, 313,000 16.7 and 17.3.  (Two entries a row, both
+// gathered at once, 116,000 far: 13.6 and 12.4.)
+constexpr int64_t SMALL_FAR_64 = 80000, SMALL_FAR_32 = 280000;
 size_t small_bytes(const Handle &h);
+bool small_suits(const Handle &h, const Pattern &pat);
 void small_init(Handle &h, void *mem, hipStream_t s);
 bool small_apply(Handle &h, bool jr, int sweeps, double omega, const double *v, double *z, hipStream_t s);
 

@@ -35,11 +35,11 @@ static int flags_to_status(int f)
 // given up.  64^3 elasticity (61 M entries): 0.50 ms, where the checks alone
 // with one thread per row took 2.0 ms and the offsets a copy of the pattern
 // and a loop on the host.  90 x 84 x 77 diffusion (4 M entries): 0.11 ms.
-constexpr int PT_SLOTS = 128, PT_MOST = 2 * DIA_MAX + 1, PT_EMPTY = INT32_MIN;
+constexpr int PT_SLOTS = 128, PT_MOST = 2 * DIA_MAX + 1, PT_EMPTY = INT32_MIN, PT_FAR = 1024;
 
 struct PatternDev {
     int err, maxlen, lo, hi, many_d, many_b;
-    unsigned long long nl, nu;
+    unsigned long long nl, nu, far;
     int d[PT_SLOTS], bl[PT_SLOTS], bu[PT_SLOTS];
 };
 size_t pattern_dev_bytes() { return aligned(sizeof(PatternDev)); }
@@ -50,7 +50,7 @@ __global__ void k_pattern_init(PatternDev *st)
     if (t < PT_SLOTS) st->d[t] = st->bl[t] = st->bu[t] = PT_EMPTY;
     if (t == 0) {
         st->err = st->maxlen = st->lo = st->hi = st->many_d = st->many_b = 0;
-        st->nl = st->nu = 0;
+        st->nl = st->nu = st->far = 0;
     }
 }
 
@@ -78,18 +78,18 @@ __global__ __launch_bounds__(256) void k_scan_pattern(int64_t n, int64_t nnz, co
                                                       PatternDev *st)
 {
     __shared__ int td[PT_SLOTS], tl[PT_SLOTS], tu[PT_SLOTS], many[2], sums[4];
-    __shared__ unsigned long long cnt[2];
+    __shared__ unsigned long long cnt[3];
     const int t = threadIdx.x, q = t % LN;
     for (int k = t; k < PT_SLOTS; k += 256) td[k] = tl[k] = tu[k] = PT_EMPTY;
     if (t == 0) {
         many[0] = st->many_d;
         many[1] = n % 3 != 0 || st->many_b;
         sums[0] = sums[1] = sums[2] = sums[3] = 0;
-        cnt[0] = cnt[1] = 0;
+        cnt[0] = cnt[1] = cnt[2] = 0;
     }
     __syncthreads();
     int f = 0, longest = 0, lo = 0, hi = 0;
-    unsigned long long nls = 0, nus = 0;
+    unsigned long long nls = 0, nus = 0, far = 0;
     if (blockIdx.x == 0 && t == 0 && (rp[0] != 0 || rp[n] != nnz)) f |= ERRF_BAD_CSR;
     const int64_t step = (int64_t)gridDim.x * (256 / LN);
     for (int64_t i = (int64_t)blockIdx.x * (256 / LN) + t / LN; i < n; i += step) {
@@ -122,6 +122,7 @@ __global__ __launch_bounds__(256) void k_scan_pattern(int64_t n, int64_t nnz, co
             const int d = (int)(c - i);
             lo = min(lo, d);
             hi = max(hi, d);
+            far += abs(d) > PT_FAR;
             if (!many[0] && !table_add(td, d)) many[0] = 1;
             if (!many[1] && d != 0 && !table_add(d < 0 ? tl : tu, c / 3 - node)) many[1] = 1;
         }
@@ -152,6 +153,7 @@ __global__ __launch_bounds__(256) void k_scan_pattern(int64_t n, int64_t nnz, co
     if (hi) atomicMax(&sums[3], hi);
     if (nls) atomicAdd(&cnt[0], nls);
     if (nus) atomicAdd(&cnt[1], nus);
+    if (far) atomicAdd(&cnt[2], far);
     __syncthreads();
     if (t == 0) {
         if (sums[0]) atomicOr(&st->err, sums[0]);
@@ -161,6 +163,7 @@ __global__ __launch_bounds__(256) void k_scan_pattern(int64_t n, int64_t nnz, co
         if (sums[3] > st->hi) atomicMax(&st->hi, sums[3]);
         atomicAdd(&st->nl, cnt[0]);
         atomicAdd(&st->nu, cnt[1]);
+        if (cnt[2]) atomicAdd(&st->far, cnt[2]);
     }
     // the keys into the device's tables (found by a plain read after the first workgroups)
     if (t < PT_SLOTS) {
@@ -212,6 +215,7 @@ int scan_pattern(const gs2_csr &A, int32_t *lcnt, int32_t *ucnt, double *sl, dou
     out.hi = h.hi;
     out.nl = (int64_t)h.nl;
     out.nu = (int64_t)h.nu;
+    out.far = (int64_t)h.far;
     out.many_d = h.many_d != 0;
     out.many_b = A.n % 3 != 0 || h.many_b != 0;
     table_list(h.d, out.d, out.many_d);
@@ -1182,7 +1186,7 @@ int setup_handle(Handle &h, const gs2_csr &A, const gs2_options &o, hipStream_t 
     GS2_TRY(scan_pattern(A, sc.lcnt, sc.ucnt, h.sl, h.sr, sc.dev, sc.pat, s));
     GS2_TRY(flags_to_status(sc.pat.err));
 
-    if (sc.pat.maxlen > SMALL_MAX_ROW) h.ep = nullptr; // pass by pass
+    if (!small_suits(h, sc.pat)) h.ep = nullptr; // pass by pass
     // row-length statistics of L (U has the same count for symmetric patterns)
     const double avg = n ? (double)(A.nnz - n) / (2.0 * n) : 0.0;
     const int maxlen = sc.pat.maxlen;
